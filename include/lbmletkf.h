@@ -215,7 +215,10 @@ lbmletkf_status run_cycle(lbmletkf_ctx* ctx, void* d_f, int32_t nsteps, const do
  * Jacobi eigensolver can stop at its sweep cap without converging.
  *   max_sweeps         cap of the analysis eigensolvers' Jacobi sweeps, 1..100
  *                      (default 30; converged solves take 4-8); a node that
- *                      reaches it is counted and its weights are used as they are;
+ *                      reaches it is counted and its weights are used as they are.
+ *                      At 30 and above the analysis may solve without iterating
+ *                      (the same weights to rounding; a node whose matrix is not
+ *                      finite is counted as one at the cap);
  *   diverge_limit      run_cycle's divergence threshold on the analysis RMSE and
  *                      spread (same units as the velocity; <= 0 or inf: none,
  *                      the default);

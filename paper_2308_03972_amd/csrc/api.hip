@@ -65,7 +65,7 @@ struct Ctx {
     bool distinct_points = true;  // no two observation points on one node
     // health checks (lbmletkf_set_checks): Jacobi sweep cap, divergence limit on
     // the analysis spread and RMSE (<= 0: none), check inside every run_cycle
-    int max_sweeps = 30;
+    int max_sweeps = kDefaultSweeps;
     double diverge_limit = 0.0;
     bool check_every_cycle = false;
     // precision form: the apply kernels' contractions on BF16 matrix cores
@@ -1155,6 +1155,7 @@ int coarse_size(int n, int g) {
 
 struct BatchGroup {
     int route;  // LBMLETKF_ROUTE_ENSEMBLE or LBMLETKF_ROUTE_OBSERVATION
+    bool direct = true;  // direct_solver() of its problems' sweep caps
     int n;      // eigenproblem size
     int stream; // 0: the launch stream, k > 0: side stream k - 1
     int4* eig_waves = nullptr;
@@ -1172,6 +1173,7 @@ struct Batch {
     std::vector<void*> f;
     int nsteps = 0;
     int storage = 0;
+    std::vector<char> direct;     // direct_solver() of each context's cap, taken at create
     bool mfma_transform = false;  // every context's setting, taken at create
     lbmletkf_batch_config cfg{};
     char* ws = nullptr;
@@ -1203,8 +1205,8 @@ struct BatchLayout {
 };
 
 // Work-queue counters of the batched analysis: 16 per group, at most one group
-// per (route, eigenproblem size <= 64).
-constexpr int kQueueInts = 16 * 2 * 65;
+// per (route, solver, eigenproblem size <= 64).
+constexpr int kQueueInts = 16 * 4 * 65;
 
 BatchLayout batch_layout(const std::vector<Ctx*>& ctx) {
     BatchLayout L{};
@@ -1232,7 +1234,7 @@ BatchLayout batch_layout(const std::vector<Ctx*>& ctx) {
     L.yo = take(nobs * sizeof(double));
     L.queue = take(kQueueInts * sizeof(int));
     // groups: node lists, eigen waves, apply/ensemble waves, G buffers (+ alignment slack
-    // for up to 64 groups of four arrays)
+    // for up to 64 groups of four arrays: 17 + 6 sizes by two solvers)
     L.group_bytes = nodes * (sizeof(int) + sizeof(int4) + sizeof(int2)) + gdoubles * sizeof(double) +
                     64 * 4 * kAlign;
     L.groups = take(L.group_bytes);
@@ -1294,20 +1296,24 @@ lbmletkf_status batch_tasks(Batch* b, hipStream_t s) {
     return e == hipSuccess ? LBMLETKF_OK : hip_fail(e, "batch tasks");
 }
 
-// Analysis groups for the bucket granularity: one group per (route, size) across problems.
+// Analysis groups for the bucket granularity: one group per (route, size, solver) across
+// problems.
 lbmletkf_status batch_groups(Batch* b, hipStream_t s) {
     const int n = (int)b->ctx.size();
     const int g = b->cfg.bucket_granularity;
     struct Range { int k, offset, count; };
-    std::vector<std::vector<Range>> obs(65);
-    std::vector<std::vector<int>> ens(65);
+    // index: size, + 65 for the iterative solver
+    std::vector<std::vector<Range>> obs(2 * 65);
+    std::vector<std::vector<int>> ens(2 * 65);
     for (int k = 0; k < n; ++k) {
         const Ctx* c = b->ctx[k];
         if (c->route == LBMLETKF_ROUTE_OBSERVATION) {
             for (const Bucket& bk : c->buckets)
-                if (bk.count > 0) obs[coarse_size(bk.n, g)].push_back({k, bk.offset, bk.count});
+                if (bk.count > 0)
+                    obs[coarse_size(bk.n, g) + (b->direct[k] ? 0 : 65)].push_back(
+                        {k, bk.offset, bk.count});
         } else {
-            ens[c->n_eig].push_back(k);
+            ens[c->n_eig + (b->direct[k] ? 0 : 65)].push_back(k);
         }
     }
     b->groups.clear();
@@ -1322,19 +1328,22 @@ lbmletkf_status batch_groups(Batch* b, hipStream_t s) {
     struct NodeCopy { int* dst; const int* src; size_t count; };
     std::vector<NodeCopy> node_copies;  // issued once the layout is known to fit
     hipError_t e = hipSuccess;
-    for (int sz = 0; sz <= 64; ++sz) {
-        if (!obs[sz].empty()) {
+    for (int key = 0; key < 2 * 65; ++key) {
+        const int sz = key % 65;
+        const bool direct = key < 65;
+        if (!obs[key].empty()) {
             BatchGroup grp;
+            grp.direct = direct;
             grp.route = LBMLETKF_ROUTE_OBSERVATION;
             grp.n = sz;
             int total = 0;
-            for (const Range& r : obs[sz]) total += r.count;
+            for (const Range& r : obs[key]) total += r.count;
             grp.nodes = reinterpret_cast<int*>(take((size_t)total * sizeof(int)));
             std::vector<int4> ew;
             std::vector<int2> aw;
-            const int segs = obs_segments(sz);
+            const int segs = obs_segments(sz, direct);
             int base = 0;
-            for (const Range& r : obs[sz]) {
+            for (const Range& r : obs[key]) {
                 node_copies.push_back({grp.nodes + base, b->ctx[r.k]->nodes() + r.offset,
                                        (size_t)r.count});
                 for (int i = 0; i < r.count; i += segs) ew.push_back(make_int4(r.k, base + i, base + r.count, 0));
@@ -1351,12 +1360,13 @@ lbmletkf_status batch_groups(Batch* b, hipStream_t s) {
             host_waves.push_back(std::move(aw));
             b->groups.push_back(grp);
         }
-        if (!ens[sz].empty()) {
+        if (!ens[key].empty()) {
             BatchGroup grp;
+            grp.direct = direct;
             grp.route = LBMLETKF_ROUTE_ENSEMBLE;
             grp.n = sz;
             std::vector<int2> w;
-            for (int k : ens[sz]) {
+            for (int k : ens[key]) {
                 const Ctx* c = b->ctx[k];
                 const int plane = c->dims.nx * c->dims.ny;
                 for (int i = 0; i < plane; i += ens_segments(sz)) w.push_back(make_int2(k, i));
@@ -1426,12 +1436,12 @@ hipError_t batch_analysis(Batch* b, const AnalysisParams* params, hipStream_t s)
         if (grp.route == LBMLETKF_ROUTE_OBSERVATION && queue)
             e = launch_analysis_obs_batch_queue(params, grp.eig_waves, grp.n_eig, grp.waves,
                                                 grp.n_waves, grp.nodes, grp.n, grp.gbuf,
-                                                b->storage, b->mfma_transform,
+                                                b->storage, b->mfma_transform, grp.direct,
                                                 b->d_queue + 16 * (&grp - b->groups.data()), sk);
         else if (grp.route == LBMLETKF_ROUTE_OBSERVATION)
             e = launch_analysis_obs_batch(params, grp.eig_waves, grp.n_eig, grp.waves, grp.n_waves,
                                           grp.nodes, grp.n, grp.gbuf, b->storage,
-                                          b->mfma_transform, sk);
+                                          b->mfma_transform, grp.direct, sk);
         else
             e = launch_analysis_ens_batch(params, grp.waves, grp.n_waves, grp.n, grp.nz_max,
                                           b->storage, sk);
@@ -1599,6 +1609,7 @@ lbmletkf_status lbmletkf_batch_create(lbmletkf_ctx* const* ctxs, void* const* d_
     b->nsteps = nsteps;
     b->storage = v[0]->storage();
     b->mfma_transform = v[0]->mfma_transform;
+    for (const Ctx* c : v) b->direct.push_back(direct_solver(c->max_sweeps) ? 1 : 0);
     b->ws = reinterpret_cast<char*>(d_workspace);
     b->ws_bytes = bytes;
     b->d_params = reinterpret_cast<AnalysisParams*>(b->ws + L.params);

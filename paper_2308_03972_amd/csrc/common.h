@@ -216,22 +216,27 @@ hipError_t launch_analysis_obs(const AnalysisParams& p, const int* nodes, int co
 int obs_size_for(int n);              // instantiated size >= n, or 0
 int obs_lds_bytes(int n);             // the larger of the two kernels' LDS
 size_t obs_gbuf_doubles(int n, int count);
-int obs_segments(int n);              // nodes per wavefront of the eigen kernel
+int obs_segments(int n, bool direct); // nodes per block of the eigen kernel
+// The analysis solves its small symmetric problems without iterating unless the caller
+// set a Jacobi sweep cap below the default: such a cap asks for the iterative solver.
+constexpr int kDefaultSweeps = 30;
+inline bool direct_solver(int max_sweeps) { return max_sweeps >= kDefaultSweeps; }
 // Batched observation route for one eigenproblem size n over many problems:
 // eigen wavefront w handles eig_waves[w] = (problem, first item, end of that
 // problem's items, -); apply wavefront w handles apply_waves[w] = (problem, item);
 // items index the shared node list and G buffer; d_params[problem] is that
-// problem's AnalysisParams.
+// problem's AnalysisParams; direct: direct_solver() of every problem of the group.
 hipError_t launch_analysis_obs_batch(const AnalysisParams* d_params, const int4* d_eig_waves,
                                      int n_eig, const int2* d_apply_waves, int n_apply,
                                      const int* d_nodes, int n, double* gbuf, int storage,
-                                     bool mfma_transform, hipStream_t s);
+                                     bool mfma_transform, bool direct, hipStream_t s);
 // The same with persistent launches that take the wave lists' entries from
 // queues: counters[0..7] (eigen) and counters[8..15] (apply), zero on entry.
 hipError_t launch_analysis_obs_batch_queue(const AnalysisParams* d_params, const int4* d_eig_waves,
                                            int n_eig, const int2* d_apply_waves, int n_apply,
                                            const int* d_nodes, int n, double* gbuf, int storage,
-                                           bool mfma_transform, int* counters, hipStream_t s);
+                                           bool mfma_transform, bool direct, int* counters,
+                                           hipStream_t s);
 // Zero n ints with a kernel (capturable in a graph, unlike hipMemsetAsync).
 hipError_t launch_zero_ints(int* v, int n, hipStream_t s);
 int diag_blocks_for(int plane);

@@ -22,6 +22,7 @@
 // memory-bound state pass, so each runs at its own occupancy.
 #include "common.h"
 #include "device_util.h"
+#include "sym_direct.h"
 
 namespace lbmletkf {
 namespace {
@@ -165,6 +166,74 @@ __device__ __forceinline__ void eig_body(const AnalysisParams p, const int* node
             out[(size_t)j * N + i] = g;
         }
         out[(size_t)N * N + i] = h;
+    }
+}
+
+// The same G and h without an eigendecomposition (sym_direct.h): G = -sqrt(beta)/a F(X)
+// and h = X^{-1} d~ / a with X = I + S/a.  One wavefront: the nodes
+// nodes[item0 + 0 .. 3] (item < end), a row of 16 lanes each.
+template <int N>
+__device__ __forceinline__ void direct_body(const AnalysisParams p, const int* nodes, int item0,
+                                            int end, double* gout) {
+    using D = Direct<N>;
+    constexpr int NS = D::NS;
+    extern __shared__ double lds[];
+    const int lane = threadIdx.x;
+    const int r = lane & 15;
+    const int item = item0 + (lane >> 4);
+    const bool valid = item < end;
+    const int node = valid ? nodes[item] : 0;
+    int q[NS];
+    double w[NS], b[NS];
+#pragma unroll
+    for (int h = 0; h < NS; ++h) {
+        q[h] = 0;
+        w[h] = b[h] = 0.0;
+        if (valid && r + 16 * h < N) local_obs(p, node, r + 16 * h, &q[h], &w[h], &b[h]);
+    }
+    // an observation of weight 0 (or a missing one) takes the index of one that counts,
+    // so that the products below meet no other node's values; a node without any
+    // reads (finite) localization weights in place of K
+    const unsigned long long on = __ballot(w[0] != 0.0);
+    const int mask = (int)(on >> (lane & 48)) & 0xffff;
+    const int qf = __builtin_amdgcn_ds_bpermute(((lane & 48) + (mask ? __ffs(mask) - 1 : 0)) * 4, q[0]);
+    const double* krow[NS];
+#pragma unroll
+    for (int h = 0; h < NS; ++h) {
+        if (w[h] == 0.0) q[h] = mask ? qf : 0;
+        krow[h] = mask ? p.K + (size_t)q[h] * p.nobs : p.loc_g;
+    }
+    // S = diag(w) K diag(w): all loads in flight together, then the weights
+    double A[NS][N];
+    auto load = [&](auto self, auto J) -> void {
+        constexpr int j = decltype(J)::value;
+        const int qj = __builtin_amdgcn_mov_dpp(q[j / 16], 0x150 + j % 16, 0xF, 0xF, true);
+#pragma unroll
+        for (int h = 0; h < NS; ++h) A[h][j] = krow[h][qj];
+        if constexpr (j + 1 < N) self(self, std::integral_constant<int, j + 1>());
+    };
+    load(load, std::integral_constant<int, 0>());
+    auto weigh = [&](auto self, auto J) -> void {
+        constexpr int j = decltype(J)::value;
+        const double wj = row_bcast<j % 16>(w[j / 16]);
+#pragma unroll
+        for (int h = 0; h < NS; ++h) A[h][j] *= w[h] * wj;
+        if constexpr (j + 1 < N) self(self, std::integral_constant<int, j + 1>());
+    };
+    weigh(weigh, std::integral_constant<int, 0>());
+    const double ia = 1.0 / p.a;
+    double* out = gout + (size_t)(valid ? item : item0) * (N * N + N);
+    const bool finite = sym_direct<N, false>(A, b, ia, -p.sqrt_beta * ia, lds, out, valid, lane);
+    if (__any(valid && !finite) && lane == 0) atomicAdd(p.eig_fail, 1);
+    if (valid) {
+#pragma unroll
+        for (int h = 0; h < NS; ++h) {
+            const int i = r + 16 * h;
+            if (i >= N) continue;
+#pragma unroll
+            for (int j = 0; j < N; ++j) out[(size_t)j * N + i] = A[h][j];
+            out[(size_t)N * N + i] = b[h] * ia;
+        }
     }
 }
 
@@ -424,39 +493,60 @@ __device__ __forceinline__ void eig_body_split(const AnalysisParams p, const int
 template <int N>
 constexpr bool kSplitRows = N > 32;
 
-template <int N>
-constexpr int eig_threads() { return kSplitRows<N> ? 2 * kWave : kWave; }
+// Whether a launch solves without iterating (direct_body): sizes up to 32 unless the
+// caller lowered the Jacobi sweep cap, which asks for the iterative solver and its
+// count of nodes that reach the cap.
+template <int N, bool DIRECT>
+constexpr bool kDirect = DIRECT && N <= 32;
 
-template <int N>
-constexpr int eig_waves() { return N <= 16 ? 4 : (N <= 22 ? 3 : 1); }
+template <int N, bool DIRECT>
+constexpr int eig_threads() { return !kDirect<N, DIRECT> && kSplitRows<N> ? 2 * kWave : kWave; }
 
-template <int N>
+template <int N, bool DIRECT>
+constexpr int eig_waves() {
+    if (kDirect<N, DIRECT>) return N <= 14 ? 4 : (N <= 20 ? 3 : 2);
+    return N <= 16 ? 4 : (N <= 22 ? 3 : 1);
+}
+
+template <int N, bool DIRECT>
 constexpr int eig_lds_doubles() {
-    if constexpr (kSplitRows<N>) return SplitLayout<N>::total;
+    if constexpr (kDirect<N, DIRECT>) return 4 * Direct<N>::kNodeDoubles;
+    else if constexpr (kSplitRows<N>) return SplitLayout<N>::total;
     else return EigLayout<N>::total;
 }
 
-template <int N>
-__global__ __launch_bounds__(eig_threads<N>()) __attribute__((amdgpu_waves_per_eu(eig_waves<N>())))
+// Nodes per block of the eigen kernel.
+template <int N, bool DIRECT>
+constexpr int eig_segs() { return kDirect<N, DIRECT> ? 4 : 64 / N; }
+
+template <int N, bool DIRECT>
+__device__ __forceinline__ void eig_node(const AnalysisParams p, const int* nodes, int item0,
+                                         int end, double* gout) {
+    if constexpr (kDirect<N, DIRECT>) direct_body<N>(p, nodes, item0, end, gout);
+    else if constexpr (kSplitRows<N>) eig_body_split<N>(p, nodes, item0, end, gout);
+    else eig_body<N>(p, nodes, item0, end, gout);
+}
+
+template <int N, bool DIRECT>
+__global__ __launch_bounds__((eig_threads<N, DIRECT>()))
+    __attribute__((amdgpu_waves_per_eu(eig_waves<N, DIRECT>())))
 void analysis_eig_kernel(AnalysisParams p, const int* nodes, int count, double* gout) {
-    if constexpr (kSplitRows<N>)
-        eig_body_split<N>(p, nodes, xcd_remap(blockIdx.x, gridDim.x), count, gout);
-    else
-        eig_body<N>(p, nodes, xcd_remap(blockIdx.x, gridDim.x) * EigLayout<N>::SEGS, count, gout);
+    eig_node<N, DIRECT>(p, nodes, xcd_remap(blockIdx.x, gridDim.x) * eig_segs<N, DIRECT>(), count,
+                        gout);
 }
 
 // Batched form: wavefront w takes waves[w] = (problem, first item, end of the
 // problem's items); the items of all problems share one node list and one G buffer.
-template <int N>
-__global__ __launch_bounds__(eig_threads<N>()) __attribute__((amdgpu_waves_per_eu(eig_waves<N>())))
+template <int N, bool DIRECT>
+__global__ __launch_bounds__((eig_threads<N, DIRECT>()))
+    __attribute__((amdgpu_waves_per_eu(eig_waves<N, DIRECT>())))
 void analysis_eig_batch_kernel(const AnalysisParams* P, const int4* waves, int nwaves,
                                const int* nodes, double* gout) {
     const int w = xcd_remap(blockIdx.x, gridDim.x);
     if (w >= nwaves) return;
     const int4 d = waves[w];
     const AnalysisParams p = P[d.x];
-    if constexpr (kSplitRows<N>) eig_body_split<N>(p, nodes, d.y, d.z, gout);
-    else eig_body<N>(p, nodes, d.y, d.z, gout);
+    eig_node<N, DIRECT>(p, nodes, d.y, d.z, gout);
 }
 
 // Dynamic LDS beyond 64 KiB needs the kernel's permission (set once per kernel).
@@ -895,8 +985,9 @@ __device__ __forceinline__ int queue_take(int* counters, int* next, int lo) {
     return *next;
 }
 
-template <int N>
-__global__ __launch_bounds__(eig_threads<N>()) __attribute__((amdgpu_waves_per_eu(eig_waves<N>())))
+template <int N, bool DIRECT>
+__global__ __launch_bounds__((eig_threads<N, DIRECT>()))
+    __attribute__((amdgpu_waves_per_eu(eig_waves<N, DIRECT>())))
 void analysis_eig_queue_kernel(const AnalysisParams* P, const int4* waves, int nwaves,
                                const int* nodes, double* gout, int* counters) {
     __shared__ int next;
@@ -911,8 +1002,7 @@ void analysis_eig_queue_kernel(const AnalysisParams* P, const int4* waves, int n
             if (w > w0) __syncthreads();
             const int4 d = waves[w];
             const AnalysisParams p = P[d.x];
-            if constexpr (kSplitRows<N>) eig_body_split<N>(p, nodes, d.y, d.z, gout);
-            else eig_body<N>(p, nodes, d.y, d.z, gout);
+            eig_node<N, DIRECT>(p, nodes, d.y, d.z, gout);
         }
     }
 }
@@ -955,18 +1045,27 @@ inline int persistent_blocks(int threads, int items) {
     return g < items ? g : items;           // items < g: one block per entry
 }
 
+// The eigen launch of one size: the direct solver, or the Jacobi solver where the size
+// or the sweep cap asks for it.
+template <int N, bool DIRECT>
+hipError_t launch_eig_n(const AnalysisParams& p, const int* nodes, int count, double* gbuf,
+                        hipStream_t s) {
+    const size_t bytes = (size_t)eig_lds_doubles<N, DIRECT>() * sizeof(double);
+    constexpr int segs = eig_segs<N, DIRECT>();
+    static bool lds_ok = false;
+    hipError_t e = allow_lds(analysis_eig_kernel<N, DIRECT>, bytes, &lds_ok);
+    if (e != hipSuccess) return e;
+    analysis_eig_kernel<N, DIRECT><<<(count + segs - 1) / segs, eig_threads<N, DIRECT>(), bytes,
+                                     s>>>(p, nodes, count, gbuf);
+    return hipGetLastError();
+}
+
 template <int N>
 hipError_t launch_n(const AnalysisParams& p, const int* nodes, int count, double* gbuf,
                     hipStream_t s) {
     if (count == 0) return hipSuccess;
-    const size_t eig_bytes = (size_t)eig_lds_doubles<N>() * sizeof(double);
-    const int segs = kSplitRows<N> ? 1 : EigLayout<N>::SEGS;
-    const int eig_blocks = (count + segs - 1) / segs;
-    static bool lds_ok = false;
-    hipError_t e = allow_lds(analysis_eig_kernel<N>, eig_bytes, &lds_ok);
-    if (e != hipSuccess) return e;
-    analysis_eig_kernel<N><<<eig_blocks, eig_threads<N>(), eig_bytes, s>>>(p, nodes, count, gbuf);
-    e = hipGetLastError();
+    hipError_t e = direct_solver(p.max_sweeps) ? launch_eig_n<N, true>(p, nodes, count, gbuf, s)
+                                               : launch_eig_n<N, false>(p, nodes, count, gbuf, s);
     if (e != hipSuccess) return e;
     const size_t app_bytes = (size_t)apply_lds_doubles(N) * sizeof(double);
     if (p.storage == kStoreF32Dev && p.mfma_transform && kMfmaApply<N>)
@@ -978,18 +1077,38 @@ hipError_t launch_n(const AnalysisParams& p, const int* nodes, int count, double
     return hipGetLastError();
 }
 
+template <int N, bool DIRECT>
+hipError_t launch_eig_batch_n(const AnalysisParams* d_params, const int4* d_eig_waves, int n_eig,
+                              const int* d_nodes, double* gbuf, int* counters, hipStream_t s) {
+    const size_t bytes = (size_t)eig_lds_doubles<N, DIRECT>() * sizeof(double);
+    hipError_t e;
+    if (counters) {
+        static bool lds_ok = false;
+        e = allow_lds(analysis_eig_queue_kernel<N, DIRECT>, bytes, &lds_ok);
+        if (e != hipSuccess) return e;
+        const int ge = persistent_blocks(eig_threads<N, DIRECT>(), n_eig);
+        analysis_eig_queue_kernel<N, DIRECT><<<ge, eig_threads<N, DIRECT>(), bytes, s>>>(
+            d_params, d_eig_waves, n_eig, d_nodes, gbuf, counters);
+    } else {
+        static bool lds_ok = false;
+        e = allow_lds(analysis_eig_batch_kernel<N, DIRECT>, bytes, &lds_ok);
+        if (e != hipSuccess) return e;
+        analysis_eig_batch_kernel<N, DIRECT><<<n_eig, eig_threads<N, DIRECT>(), bytes, s>>>(
+            d_params, d_eig_waves, n_eig, d_nodes, gbuf);
+    }
+    return hipGetLastError();
+}
+
 template <int N>
 hipError_t launch_batch_n(const AnalysisParams* d_params, const int4* d_eig_waves, int n_eig,
                           const int2* d_apply_waves, int n_apply, const int* d_nodes,
-                          double* gbuf, int storage, bool mfma_transform, hipStream_t s) {
+                          double* gbuf, int storage, bool mfma_transform, bool direct,
+                          hipStream_t s) {
     if (n_eig == 0) return hipSuccess;
-    const size_t eig_bytes = (size_t)eig_lds_doubles<N>() * sizeof(double);
-    static bool lds_ok = false;
-    hipError_t e = allow_lds(analysis_eig_batch_kernel<N>, eig_bytes, &lds_ok);
-    if (e != hipSuccess) return e;
-    analysis_eig_batch_kernel<N><<<n_eig, eig_threads<N>(), eig_bytes, s>>>(
-        d_params, d_eig_waves, n_eig, d_nodes, gbuf);
-    e = hipGetLastError();
+    hipError_t e = direct ? launch_eig_batch_n<N, true>(d_params, d_eig_waves, n_eig, d_nodes, gbuf,
+                                                        nullptr, s)
+                          : launch_eig_batch_n<N, false>(d_params, d_eig_waves, n_eig, d_nodes,
+                                                         gbuf, nullptr, s);
     if (e != hipSuccess) return e;
     const size_t app_bytes = (size_t)apply_lds_doubles(N) * sizeof(double);
     if (storage == kStoreF32Dev && mfma_transform && kMfmaApply<N>)
@@ -1007,17 +1126,13 @@ hipError_t launch_batch_n(const AnalysisParams* d_params, const int4* d_eig_wave
 template <int N>
 hipError_t launch_batch_queue_n(const AnalysisParams* d_params, const int4* d_eig_waves, int n_eig,
                                 const int2* d_apply_waves, int n_apply, const int* d_nodes,
-                                double* gbuf, int storage, bool mfma_transform, int* counters,
-                                hipStream_t s) {
+                                double* gbuf, int storage, bool mfma_transform, bool direct,
+                                int* counters, hipStream_t s) {
     if (n_eig == 0) return hipSuccess;
-    const size_t eig_bytes = (size_t)eig_lds_doubles<N>() * sizeof(double);
-    static bool lds_ok = false;
-    hipError_t e = allow_lds(analysis_eig_queue_kernel<N>, eig_bytes, &lds_ok);
-    if (e != hipSuccess) return e;
-    const int ge = persistent_blocks(eig_threads<N>(), n_eig);
-    analysis_eig_queue_kernel<N><<<ge, eig_threads<N>(), eig_bytes, s>>>(
-        d_params, d_eig_waves, n_eig, d_nodes, gbuf, counters);
-    e = hipGetLastError();
+    hipError_t e = direct ? launch_eig_batch_n<N, true>(d_params, d_eig_waves, n_eig, d_nodes, gbuf,
+                                                        counters, s)
+                          : launch_eig_batch_n<N, false>(d_params, d_eig_waves, n_eig, d_nodes,
+                                                         gbuf, counters, s);
     if (e != hipSuccess) return e;
     const size_t app_bytes = (size_t)apply_lds_doubles(N) * sizeof(double);
     auto go = [&](auto kernel) {
@@ -1050,7 +1165,7 @@ int obs_size_for(int n) {
 
 int obs_lds_bytes(int n) {
     switch (n) {
-#define X(v) case v: return (eig_lds_doubles<v>() > apply_lds_doubles(v) ? eig_lds_doubles<v>() \
+#define X(v) case v: return (eig_lds_doubles<v, false>() > apply_lds_doubles(v) ? eig_lds_doubles<v, false>() \
                                                                         : apply_lds_doubles(v)) * \
                             (int)sizeof(double);
         LBMLETKF_OBS_SIZES(X)
@@ -1083,17 +1198,26 @@ hipError_t launch_zero_ints(int* v, int n, hipStream_t s) {
     return hipGetLastError();
 }
 
-int obs_segments(int n) { return n > 0 ? 64 / n : 0; }
+int obs_segments(int n, bool direct) {
+    switch (n) {
+#define X(v) case v: return direct ? eig_segs<v, true>() : eig_segs<v, false>();
+        LBMLETKF_OBS_SIZES(X)
+#undef X
+        default: return 0;
+    }
+}
 
 hipError_t launch_analysis_obs_batch_queue(const AnalysisParams* d_params, const int4* d_eig_waves,
                                            int n_eig, const int2* d_apply_waves, int n_apply,
                                            const int* d_nodes, int n, double* gbuf, int storage,
-                                           bool mfma_transform, int* counters, hipStream_t s) {
+                                           bool mfma_transform, bool direct, int* counters,
+                                           hipStream_t s) {
     switch (n) {
 #define X(v)                                                                                \
     case v:                                                                                 \
         return launch_batch_queue_n<v>(d_params, d_eig_waves, n_eig, d_apply_waves, n_apply, \
-                                       d_nodes, gbuf, storage, mfma_transform, counters, s);
+                                       d_nodes, gbuf, storage, mfma_transform, direct,        \
+                                       counters, s);
         LBMLETKF_OBS_SIZES(X)
 #undef X
         default: return hipErrorInvalidValue;
@@ -1103,12 +1227,12 @@ hipError_t launch_analysis_obs_batch_queue(const AnalysisParams* d_params, const
 hipError_t launch_analysis_obs_batch(const AnalysisParams* d_params, const int4* d_eig_waves,
                                      int n_eig, const int2* d_apply_waves, int n_apply,
                                      const int* d_nodes, int n, double* gbuf, int storage,
-                                     bool mfma_transform, hipStream_t s) {
+                                     bool mfma_transform, bool direct, hipStream_t s) {
     switch (n) {
 #define X(v)                                                                                   \
     case v:                                                                                    \
         return launch_batch_n<v>(d_params, d_eig_waves, n_eig, d_apply_waves, n_apply, d_nodes, \
-                                 gbuf, storage, mfma_transform, s);
+                                 gbuf, storage, mfma_transform, direct, s);
         LBMLETKF_OBS_SIZES(X)
 #undef X
         default: return hipErrorInvalidValue;

@@ -1,0 +1,478 @@
+// Direct (iteration-free) functions of small symmetric matrices for the analysis:
+// Householder tridiagonalisation, a sum of shifted tridiagonal inverses
+// (sqrt_poles.h) and the back transformation, four nodes per wavefront.
+//
+// Layout: a node owns a row of 16 lanes; lane r holds rows r and r + 16 (N > 16) of
+// its N x N matrix in registers.  Everything one lane needs of another's comes
+// through v_fmac_f64_dpp row_newbcast, which broadcasts lane j of the row as the
+// multiplicand: a matrix-vector product or a rank-2 update is one instruction per
+// entry with no LDS traffic, where a Jacobi round costs six FP64 operations per entry
+// and both halves of an LDS exchange, N rounds per sweep, five to six sweeps.
+#pragma once
+#include <type_traits>
+
+#include "common.h"
+#include "device_util.h"
+#include "sqrt_poles.h"
+
+namespace lbmletkf {
+namespace dev {
+
+// ---------------------------------------------------------------------------
+// broadcasts inside the row of 16 lanes
+// ---------------------------------------------------------------------------
+template <int L>
+__device__ __forceinline__ double row_bcast(double x) {
+    return __builtin_amdgcn_mov_dpp(x, 0x150 + L, 0xF, 0xF, true);
+}
+
+// Value of lane l (0..15, wave-uniform) of each row, through the LDS crossbar.
+__device__ __forceinline__ double row_bcast_dyn(double x, int l, int lane) {
+    const int addr = ((lane & 48) + l) * 4;
+    const int lo = __builtin_amdgcn_ds_bpermute(addr, __double2loint(x));
+    const int hi = __builtin_amdgcn_ds_bpermute(addr, __double2hiint(x));
+    return __hiloint2double(hi, lo);
+}
+
+// The v_fmac_f64_dpp blocks: written as assembly because the compiler does not fold
+// a 64-bit row_newbcast into the multiply-add.  A DPP operand written by one of the
+// two preceding VALU instructions is a hazard the compiler does not see inside an
+// assembly block, so every block opens with two wait states.
+#define LBM_FMAC_DPP(d, s, y, l) \
+    "v_fmac_f64_dpp %" #d ", %" #s ", %" #y " row_newbcast:%" #l " row_mask:0xf bank_mask:0xf\n\t"
+
+// a[k] += bcast(x, L + k) * y, k < CNT
+template <int L, int CNT>
+__device__ __forceinline__ void fmac_axpy(double* a, double x, double y) {
+    if constexpr (CNT >= 8) {
+        asm("s_nop 1\n\t" LBM_FMAC_DPP(0, 8, 9, 10) LBM_FMAC_DPP(1, 8, 9, 11)
+                LBM_FMAC_DPP(2, 8, 9, 12) LBM_FMAC_DPP(3, 8, 9, 13) LBM_FMAC_DPP(4, 8, 9, 14)
+                    LBM_FMAC_DPP(5, 8, 9, 15) LBM_FMAC_DPP(6, 8, 9, 16) LBM_FMAC_DPP(7, 8, 9, 17)
+            : "+&v"(a[0]), "+&v"(a[1]), "+&v"(a[2]), "+&v"(a[3]), "+&v"(a[4]), "+&v"(a[5]),
+              "+&v"(a[6]), "+&v"(a[7])
+            : "v"(x), "v"(y), "n"(L), "n"(L + 1), "n"(L + 2), "n"(L + 3), "n"(L + 4), "n"(L + 5),
+              "n"(L + 6), "n"(L + 7));
+        if constexpr (CNT > 8) fmac_axpy<L + 8, CNT - 8>(a + 8, x, y);
+    } else if constexpr (CNT >= 4) {
+        asm("s_nop 1\n\t" LBM_FMAC_DPP(0, 4, 5, 6) LBM_FMAC_DPP(1, 4, 5, 7)
+                LBM_FMAC_DPP(2, 4, 5, 8) LBM_FMAC_DPP(3, 4, 5, 9)
+            : "+&v"(a[0]), "+&v"(a[1]), "+&v"(a[2]), "+&v"(a[3])
+            : "v"(x), "v"(y), "n"(L), "n"(L + 1), "n"(L + 2), "n"(L + 3));
+        if constexpr (CNT > 4) fmac_axpy<L + 4, CNT - 4>(a + 4, x, y);
+    } else if constexpr (CNT >= 2) {
+        asm("s_nop 1\n\t" LBM_FMAC_DPP(0, 2, 3, 4) LBM_FMAC_DPP(1, 2, 3, 5)
+            : "+&v"(a[0]), "+&v"(a[1])
+            : "v"(x), "v"(y), "n"(L), "n"(L + 1));
+        if constexpr (CNT > 2) fmac_axpy<L + 2, CNT - 2>(a + 2, x, y);
+    } else if constexpr (CNT == 1) {
+        asm("s_nop 1\n\t" LBM_FMAC_DPP(0, 1, 2, 3) : "+&v"(a[0]) : "v"(x), "v"(y), "n"(L));
+    }
+}
+
+// s0 + s1 += sum_k bcast(x, L + k) * a[k], k < CNT (two partial sums)
+template <int L, int CNT>
+__device__ __forceinline__ void fmac_dot(const double* a, double x, double& s0, double& s1) {
+    if constexpr (CNT >= 8) {
+        asm("s_nop 1\n\t" LBM_FMAC_DPP(0, 2, 3, 11) LBM_FMAC_DPP(1, 2, 4, 12)
+                LBM_FMAC_DPP(0, 2, 5, 13) LBM_FMAC_DPP(1, 2, 6, 14) LBM_FMAC_DPP(0, 2, 7, 15)
+                    LBM_FMAC_DPP(1, 2, 8, 16) LBM_FMAC_DPP(0, 2, 9, 17) LBM_FMAC_DPP(1, 2, 10, 18)
+            : "+&v"(s0), "+&v"(s1)
+            : "v"(x), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]),
+              "v"(a[7]), "n"(L), "n"(L + 1), "n"(L + 2), "n"(L + 3), "n"(L + 4), "n"(L + 5),
+              "n"(L + 6), "n"(L + 7));
+        if constexpr (CNT > 8) fmac_dot<L + 8, CNT - 8>(a + 8, x, s0, s1);
+    } else if constexpr (CNT >= 4) {
+        asm("s_nop 1\n\t" LBM_FMAC_DPP(0, 2, 3, 7) LBM_FMAC_DPP(1, 2, 4, 8)
+                LBM_FMAC_DPP(0, 2, 5, 9) LBM_FMAC_DPP(1, 2, 6, 10)
+            : "+&v"(s0), "+&v"(s1)
+            : "v"(x), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "n"(L), "n"(L + 1), "n"(L + 2),
+              "n"(L + 3));
+        if constexpr (CNT > 4) fmac_dot<L + 4, CNT - 4>(a + 4, x, s0, s1);
+    } else if constexpr (CNT >= 2) {
+        asm("s_nop 1\n\t" LBM_FMAC_DPP(0, 2, 3, 5) LBM_FMAC_DPP(1, 2, 4, 6)
+            : "+&v"(s0), "+&v"(s1)
+            : "v"(x), "v"(a[0]), "v"(a[1]), "n"(L), "n"(L + 1));
+        if constexpr (CNT > 2) fmac_dot<L + 2, CNT - 2>(a + 2, x, s0, s1);
+    } else if constexpr (CNT == 1) {
+        asm("s_nop 1\n\t" LBM_FMAC_DPP(0, 1, 2, 3) : "+&v"(s0) : "v"(x), "v"(a[0]), "n"(L));
+    }
+}
+
+// The same over columns 0 .. W - 1 of a vector kept as NS registers per lane.
+template <int W, int NS>
+__device__ __forceinline__ void row_axpy(double* a, const double (&x)[NS], double y) {
+    fmac_axpy<0, (W < 16 ? W : 16)>(a, x[0], y);
+    if constexpr (W > 16) fmac_axpy<0, W - 16>(a + 16, x[1], y);
+}
+template <int W, int NS>
+__device__ __forceinline__ double row_dot(const double* a, const double (&x)[NS]) {
+    double s0 = 0.0, s1 = 0.0;
+    fmac_dot<0, (W < 16 ? W : 16)>(a, x[0], s0, s1);
+    if constexpr (W > 16) fmac_dot<0, W - 16>(a + 16, x[1], s0, s1);
+    return s0 + s1;
+}
+
+// Two chains of the tridiagonal inverse's recurrence at once: for k < CNT
+//   ua[k] += bcast(g[k], P) * (k ? ua[k - 1] : pa),  ub[k] likewise with lane P + 1.
+template <int P, int CNT>
+__device__ __forceinline__ void fmac_chain(double* ua, double* ub, const double* g, double pa,
+                                           double pb) {
+    if constexpr (CNT >= 4) {
+        asm("s_nop 1\n\t" LBM_FMAC_DPP(0, 8, 12, 14) LBM_FMAC_DPP(4, 8, 13, 15)
+                LBM_FMAC_DPP(1, 9, 0, 14) LBM_FMAC_DPP(5, 9, 4, 15) LBM_FMAC_DPP(2, 10, 1, 14)
+                    LBM_FMAC_DPP(6, 10, 5, 15) LBM_FMAC_DPP(3, 11, 2, 14)
+                        LBM_FMAC_DPP(7, 11, 6, 15)
+            : "+&v"(ua[0]), "+&v"(ua[1]), "+&v"(ua[2]), "+&v"(ua[3]), "+&v"(ub[0]), "+&v"(ub[1]),
+              "+&v"(ub[2]), "+&v"(ub[3])
+            : "v"(g[0]), "v"(g[1]), "v"(g[2]), "v"(g[3]), "v"(pa), "v"(pb), "n"(P), "n"(P + 1));
+        if constexpr (CNT > 4) fmac_chain<P, CNT - 4>(ua + 4, ub + 4, g + 4, ua[3], ub[3]);
+    } else if constexpr (CNT >= 2) {
+        asm("s_nop 1\n\t" LBM_FMAC_DPP(0, 4, 6, 8) LBM_FMAC_DPP(2, 4, 7, 9)
+                LBM_FMAC_DPP(1, 5, 0, 8) LBM_FMAC_DPP(3, 5, 2, 9)
+            : "+&v"(ua[0]), "+&v"(ua[1]), "+&v"(ub[0]), "+&v"(ub[1])
+            : "v"(g[0]), "v"(g[1]), "v"(pa), "v"(pb), "n"(P), "n"(P + 1));
+        if constexpr (CNT > 2) fmac_chain<P, CNT - 2>(ua + 2, ub + 2, g + 2, ua[1], ub[1]);
+    } else if constexpr (CNT == 1) {
+        asm("s_nop 1\n\t" LBM_FMAC_DPP(0, 2, 3, 5) LBM_FMAC_DPP(1, 2, 4, 6)
+            : "+&v"(ua[0]), "+&v"(ub[0])
+            : "v"(g[0]), "v"(pa), "v"(pb), "n"(P), "n"(P + 1));
+    }
+}
+#undef LBM_FMAC_DPP
+
+__device__ __forceinline__ double row_sum(double v) { return group_reduce<16>(v, OpAdd()); }
+
+// x^{-1/2} and 1 / x of normal positive x: the hardware estimate and one cubic
+// correction step (y (1 + e/2 + 3 e^2/8), e = 1 - x y^2; y (1 + e + e^2), e = 1 - x y).
+__device__ __forceinline__ double fast_rsqrt(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+__device__ __forceinline__ double fast_rcp(double x) {
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, y, 1.0);
+    return fma(y, fma(e, e, e), y);
+}
+
+template <int N>
+struct Direct {
+    static_assert(N >= 8 && N <= 32 && N % 2 == 0, "one or two matrix rows per lane");
+    static constexpr int NS = (N + 15) / 16;      // matrix rows per lane
+    static constexpr int ZS = N + 1;              // stride of the LDS tables (odd)
+    static constexpr int kNodeDoubles = 16 * ZS;  // per node: pole table, then the transposes
+    static constexpr int kTop = (N - 1 + 3) / 4 * 4;  // first phase's width
+};
+
+// One phase of the tridiagonalisation: the columns n - 1 for n = min(N, W + 1) down to
+// max(3, W - 2) are eliminated on rows and columns < W (n - 1 <= W).  The reflector of
+// step n, H = I - v v^T on indices 0 .. n - 2 (|v|^2 = 2, or v = 0), goes to
+// vs[(n - 3) * N + i]; d and e receive the diagonal and the coupling (i, i + 1); b
+// becomes H b.  Widths in steps of four keep the code small (each phase is a loop)
+// at the price of a few columns that are no longer needed.
+template <int N, int W>
+__device__ __forceinline__ void tri_phase(double (&A)[Direct<N>::NS][N],
+                                          double (&d)[Direct<N>::NS], double (&e)[Direct<N>::NS],
+                                          double (&b)[Direct<N>::NS], double* vs, bool store,
+                                          int lane) {
+    constexpr int NS = Direct<N>::NS;
+    constexpr int WC = W < N ? W : N;              // columns and rows of the support
+    constexpr int SW = (WC + 15) / 16;             // row slots of the support
+    constexpr int SX = W / 16 + 1 < NS ? W / 16 + 1 : NS;  // slots that hold a row n - 1
+    constexpr int HI = W + 1 < N ? W + 1 : N;
+    constexpr int LO = W - 2 > 3 ? W - 2 : 3;
+    const int r = lane & 15;
+#pragma unroll 1
+    for (int n = HI; n >= LO; --n) {
+        double x[SW], v[SW], p[SW];
+#pragma unroll
+        for (int h = 0; h < SX; ++h) {
+            // column n - 1: a sum over the phase's columns with weights 1 and 0 (a select
+            // would index the registers dynamically, through scratch memory); columns
+            // beyond n - 1 hold finite values, H S H continued to all rows
+            double xr = A[h][LO - 1] * (n == LO ? 1.0 : 0.0);
+#pragma unroll
+            for (int c = LO; c < HI; ++c) xr = fma(A[h][c], n - 1 == c ? 1.0 : 0.0, xr);
+            d[h] = r + 16 * h == n - 1 ? xr : d[h];
+            if (h < SW) x[h < SW ? h : 0] = r + 16 * h < n - 1 ? xr : 0.0;
+        }
+        double s2 = x[0] * x[0];
+        if constexpr (SW > 1) s2 = fma(x[1], x[1], s2);
+        constexpr int PS = (W - 1) / 16 < SW ? (W - 1) / 16 : SW - 1;  // slot of row n - 2
+        const double x1 = row_bcast_dyn(x[PS], (n - 2) & 15, lane);
+        s2 = row_sum(s2);
+        const bool some = s2 > 1e-290;
+        const double norm = s2 * fast_rsqrt(s2);
+        const double rb = some ? fast_rsqrt(fma(fabs(x1), norm, s2)) : 0.0;
+        const double alpha = some ? -copysign(norm, x1) : x1;
+        const double shift = some ? copysign(norm, x1) : 0.0;
+#pragma unroll
+        for (int h = 0; h < SW; ++h) {
+            const bool piv = r + 16 * h == n - 2;
+            e[h] = piv ? alpha : e[h];
+            v[h] = (x[h] + (piv ? shift : 0.0)) * rb;
+            if (store && r + 16 * h < N) vs[(size_t)(n - 3) * N + r + 16 * h] = v[h];
+        }
+        double c = 0.0, cb = 0.0;
+#pragma unroll
+        for (int h = 0; h < SW; ++h) {
+            p[h] = row_dot<WC, SW>(A[h], v);
+            c = fma(v[h], p[h], c);
+            cb = fma(v[h], b[h], cb);
+        }
+        c = row_sum(c);
+        cb = row_sum(cb);
+#pragma unroll
+        for (int h = 0; h < SW; ++h) {
+            const double w = fma(-c, v[h], p[h]);
+            b[h] = fma(-cb, v[h], b[h]);
+            row_axpy<WC, SW>(A[h], p, -v[h]);
+            row_axpy<WC, SW>(A[h], v, -w);
+        }
+    }
+}
+
+// The reflectors of one phase applied from both sides, G <- H G H, in ascending n, and
+// hv <- H hv.
+template <int N, int W>
+__device__ __forceinline__ void back_phase(double (&G)[Direct<N>::NS][N],
+                                           double (&hv)[Direct<N>::NS], const double* vs,
+                                           int lane) {
+    constexpr int NS = Direct<N>::NS;
+    constexpr int WC = W < N ? W : N;
+    constexpr int SW = (WC + 15) / 16;
+    constexpr int HI = W + 1 < N ? W + 1 : N;
+    constexpr int LO = W - 2 > 3 ? W - 2 : 3;
+    const int r = lane & 15;
+#pragma unroll 1
+    for (int n = LO; n <= HI; ++n) {
+        double v[SW], p[NS];
+#pragma unroll
+        for (int h = 0; h < SW; ++h)
+            v[h] = r + 16 * h < N ? vs[(size_t)(n - 3) * N + r + 16 * h] : 0.0;
+        double c = 0.0, ch = 0.0;
+#pragma unroll
+        for (int h = 0; h < NS; ++h) {
+            p[h] = row_dot<WC, SW>(G[h], v);
+            if (h < SW) {
+                c = fma(v[h < SW ? h : 0], p[h], c);
+                ch = fma(v[h < SW ? h : 0], hv[h], ch);
+            }
+        }
+        c = row_sum(c);
+        ch = row_sum(ch);
+#pragma unroll
+        for (int h = 0; h < NS; ++h) {
+            if (h < SW) {
+                const double vh = v[h < SW ? h : 0];
+                hv[h] = fma(-ch, vh, hv[h]);
+                row_axpy<N, NS>(G[h], p, -vh);
+                row_axpy<WC, SW>(G[h], v, -fma(-c, vh, p[h]));
+            } else {
+                row_axpy<WC, SW>(G[h], v, -p[h]);
+            }
+        }
+    }
+}
+
+template <int N, int W>
+__device__ __forceinline__ void tri_all(double (&A)[Direct<N>::NS][N], double (&d)[Direct<N>::NS],
+                                        double (&e)[Direct<N>::NS], double (&b)[Direct<N>::NS],
+                                        double* vs, bool store, int lane) {
+    tri_phase<N, W>(A, d, e, b, vs, store, lane);
+    if constexpr (W > 4) tri_all<N, W - 4>(A, d, e, b, vs, store, lane);
+}
+template <int N, int W>
+__device__ __forceinline__ void back_all(double (&G)[Direct<N>::NS][N], double (&hv)[Direct<N>::NS],
+                                         const double* vs, int lane) {
+    if constexpr (W > 4) back_all<N, W - 4>(G, hv, vs, lane);
+    back_phase<N, W>(G, hv, vs, lane);
+}
+
+// Sum over each row of 16 lanes (FP32).
+__device__ __forceinline__ float row_sum_f32(float m) {
+    m += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(m), 0xB1, 0xF, 0xF, true));
+    m += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(m), 0x4E, 0xF, 0xF, true));
+    m += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(m), 0x141, 0xF, 0xF, true));
+    m += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(m), 0x140, 0xF, 0xF, true));
+    return m;
+}
+
+// Pole class of a wavefront: kappa = 1 + the largest norm of its four nodes, each
+// norm^2 given as a sum over the node's lanes; a NaN does not count.
+__device__ __forceinline__ int pole_class(float part) {
+    const float n2 = row_sum_f32(part);
+    float w = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        w = fmaxf(w, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(n2), 16 * k)));
+    // kappa <= 2^e: the exponent of 1 + norm (a little enlarged against FP32 rounding),
+    // rounded up
+    const float kappa = 1.0f + 1.0001f * __builtin_amdgcn_sqrtf(w);
+    const int e = ((__float_as_int(kappa) + 0x7fffff) >> 23) - 127;
+    int k = 0;
+    while (k < kPoleClasses - 1 && kPoleLog2[k] < e) ++k;
+    return __builtin_amdgcn_readfirstlane(k);
+}
+
+// For the four nodes of a wavefront, with X = I + S/a (rows of S in A, S >= 0):
+//   A <- scale * F(X)   (scale * X^{-1/2} if ROOT),   b <- X^{-1} b.
+// lds: 4 * Direct<N>::kNodeDoubles doubles; vs: this node's scratch of (N - 2) * N
+// doubles in device memory (written and read by the same lanes; `store` false for a
+// row without a node).  Returns false if a node's matrix is not finite.
+template <int N, bool ROOT>
+__device__ __forceinline__ bool sym_direct(double (&A)[Direct<N>::NS][N],
+                                           double (&b)[Direct<N>::NS], double ia, double scale,
+                                           double* lds, double* vs, bool store, int lane) {
+    using D = Direct<N>;
+    constexpr int NS = D::NS;
+    constexpr int ZS = D::ZS;
+    const int r = lane & 15;
+    double* zt = lds + (size_t)(lane >> 4) * D::kNodeDoubles;  // [16][ZS]
+    double d[NS], e[NS];
+#pragma unroll
+    for (int h = 0; h < NS; ++h) d[h] = e[h] = 0.0;
+    tri_all<N, D::kTop>(A, d, e, b, vs, store, lane);
+    // rows 0 and 1 are left: d_0, d_1, e_0
+    d[0] = r == 0 ? A[0][0] : (r == 1 ? A[0][1] : d[0]);
+    e[0] = r == 0 ? A[0][1] : e[0];
+    // the Frobenius norm of T / a bounds its largest eigenvalue
+    bool finite = true;
+    float f2 = 0.0f;
+#pragma unroll
+    for (int h = 0; h < NS; ++h) {
+        d[h] *= ia;
+        e[h] *= ia;
+        finite = finite && fabs(d[h]) + fabs(e[h]) < 1e300;
+        const float df = (float)d[h], ef = (float)e[h];
+        f2 += df * df + 2.0f * ef * ef;
+    }
+    const int cls = pole_class(f2);
+    const int p0 = kPoleOffset[cls], np = kPoleOffset[cls + 1] - p0;
+
+#pragma unroll
+    for (int h = 0; h < NS; ++h)
+#pragma unroll
+        for (int j = 0; j < N; ++j) A[h][j] = 0.0;
+    double hv[NS];
+    // fifteen poles at a time, lane r = pole (lane 15: t^2 = 0, the inverse itself):
+    // X + t^2 = U Gamma U^T from the bottom row up, then its inverse's diagonal from
+    // the top row down (both recurrences have positive terms only)
+#pragma unroll 1
+    for (int pb = 0; pb < np; pb += 15) {
+        const int pi = pb + r < np && r < 15 ? p0 + pb + r : -1;
+        const double t2 = pi >= 0 ? kSqrtPoles[pi < 0 ? 0 : pi].t2 : 0.0;
+        double cw = pi >= 0 ? kSqrtPoles[pi < 0 ? 0 : pi].c * scale : 0.0;
+        if constexpr (ROOT) cw *= 1.0 + t2;
+        const double base = 1.0 + t2;
+        double g[N], rg[N], y[N];
+        auto col = [](const double (&v)[NS], auto J) {
+            constexpr int j = decltype(J)::value;
+            return row_bcast<j % 16>(v[j / 16]);
+        };
+        auto down = [&](auto self, auto J) -> void {
+            constexpr int j = decltype(J)::value;
+            double gam = base + col(d, J);
+            const double bj = col(b, J);
+            if constexpr (j == N - 1) {
+                g[j] = 0.0;
+                y[j] = bj;
+            } else {
+                const double ej = col(e, J);
+                g[j] = -ej * rg[j + 1];
+                gam = fma(g[j], ej, gam);
+                y[j] = fma(g[j], y[j + 1], bj);
+            }
+            rg[j] = fast_rcp(gam);
+            if constexpr (j > 0) self(self, std::integral_constant<int, j - 1>());
+        };
+        down(down, std::integral_constant<int, N - 1>());
+        wave_lds_sync();
+        {
+            double z = rg[0], hh = y[0] * rg[0];
+            zt[r * ZS] = r == 15 ? hh : z * cw;
+#pragma unroll
+            for (int j = 0; j < N - 1; ++j) {
+                z = fma(g[j], g[j] * z, rg[j + 1]);
+                hh = fma(g[j], hh, y[j + 1] * rg[j + 1]);
+                zt[r * ZS + j + 1] = r == 15 ? hh : z * cw;
+            }
+        }
+        wave_lds_sync();
+#pragma unroll
+        for (int h = 0; h < NS; ++h) hv[h] = r + 16 * h < N ? zt[15 * ZS + r + 16 * h] : 0.0;
+        // upper triangle, row i: z_ii, then z_{i,j+1} = g_j z_{i,j}; four poles per pass,
+        // after which the rows' lanes rotate by four
+        const int left = np - pb < 15 ? np - pb : 15;
+#pragma unroll 1
+        for (int q = 0; q < left; q += 4) {
+#pragma unroll
+            for (int pr = 0; pr < 4; pr += 2) {
+                double wa[NS], wb[NS];
+#pragma unroll
+                for (int h = 0; h < NS; ++h) {
+                    const int i = r + 16 * h < N ? r + 16 * h : 0;
+                    wa[h] = zt[(q + pr) * ZS + i];
+                    wb[h] = zt[(q + pr + 1) * ZS + i];
+                    if (q + pr + 1 == 15) wb[h] = 0.0;
+                }
+#pragma unroll
+                for (int h = 0; h < NS; ++h) {
+                    double ua[N], ub[N];
+#pragma unroll
+                    for (int j = 16 * h; j < N; ++j) {
+                        const bool own = j < 16 * h + 16 && r == j - 16 * h;
+                        ua[j] = own ? wa[h] : 0.0;
+                        ub[j] = own ? wb[h] : 0.0;
+                    }
+                    if (h == 0) {
+                        if (pr == 0) fmac_chain<0, N - 1>(ua + 1, ub + 1, g, ua[0], ub[0]);
+                        else fmac_chain<2, N - 1>(ua + 1, ub + 1, g, ua[0], ub[0]);
+                    } else if constexpr (NS > 1) {
+                        if (pr == 0)
+                            fmac_chain<0, N - 17>(ua + 17, ub + 17, g + 16, ua[16], ub[16]);
+                        else
+                            fmac_chain<2, N - 17>(ua + 17, ub + 17, g + 16, ua[16], ub[16]);
+                    }
+#pragma unroll
+                    for (int j = 16 * h; j < N; ++j) A[h][j] += ua[j] + ub[j];
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < N - 1; ++j) {
+                const int lo = __builtin_amdgcn_mov_dpp(__double2loint(g[j]), 0x12C, 0xF, 0xF, true);
+                const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(g[j]), 0x12C, 0xF, 0xF, true);
+                g[j] = __hiloint2double(hi, lo);
+            }
+        }
+        wave_lds_sync();
+    }
+    // lower triangle: the lower rows' columns come from rows 0..15 (one transpose), the
+    // rest of rows 16.. from themselves (a second)
+#pragma unroll
+    for (int j = 0; j < N; ++j) zt[r * ZS + j] = A[0][j];
+    if (r < N) zt[r * ZS + r] = 0.0;
+    wave_lds_sync();
+#pragma unroll
+    for (int j = 0; j < (N < 16 ? N : 16); ++j)
+#pragma unroll
+        for (int h = 0; h < NS; ++h) A[h][j] += r + 16 * h < N ? zt[j * ZS + r + 16 * h] : 0.0;
+    if constexpr (NS > 1) {
+        wave_lds_sync();
+        if (r + 16 < N) {
+#pragma unroll
+            for (int j = 16; j < N; ++j) zt[r * ZS + j] = A[1][j];
+            zt[r * ZS + r + 16] = 0.0;
+        }
+        wave_lds_sync();
+#pragma unroll
+        for (int j = 16; j < N; ++j) A[1][j] += r + 16 < N ? zt[(j - 16) * ZS + r + 16] : 0.0;
+    }
+#pragma unroll
+    for (int h = 0; h < NS; ++h) b[h] = hv[h];
+    back_all<N, D::kTop>(A, b, vs, lane);
+    return finite;
+}
+
+}  // namespace dev
+}  // namespace lbmletkf
