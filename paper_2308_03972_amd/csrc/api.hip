@@ -1369,7 +1369,7 @@ lbmletkf_status batch_groups(Batch* b, hipStream_t s) {
             for (int k : ens[key]) {
                 const Ctx* c = b->ctx[k];
                 const int plane = c->dims.nx * c->dims.ny;
-                for (int i = 0; i < plane; i += ens_segments(sz)) w.push_back(make_int2(k, i));
+                for (int i = 0; i < plane; i += ens_segments(sz, direct)) w.push_back(make_int2(k, i));
                 grp.nz_max = std::max(grp.nz_max, c->obs.nvar * c->lmax);
                 grp.cost += (double)plane * ens_node_cost(sz);
             }
@@ -1444,7 +1444,7 @@ hipError_t batch_analysis(Batch* b, const AnalysisParams* params, hipStream_t s)
                                           b->mfma_transform, grp.direct, sk);
         else
             e = launch_analysis_ens_batch(params, grp.waves, grp.n_waves, grp.n, grp.nz_max,
-                                          b->storage, sk);
+                                          b->storage, grp.direct, sk);
     }
     for (int k = 0; k < Batch::kSide && e == hipSuccess; ++k) {
         if (!used[k]) continue;

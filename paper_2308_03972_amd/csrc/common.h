@@ -202,12 +202,13 @@ hipError_t launch_diag_nodes_final(const double* diag_node, int plane, double* p
 hipError_t launch_analysis_ens(const AnalysisParams& p, int n, hipStream_t s);
 int ens_size_for(int n);              // instantiated size >= n, or 0
 int ens_lds_bytes(int n, int nz);
-int ens_segments(int n);              // nodes per wavefront of the ensemble route
+int ens_segments(int n, bool direct); // nodes per wavefront of the ensemble route
 // Batched ensemble route: wavefront w handles waves[w] = (problem, first node of
-// its ens_segments(n) consecutive nodes of that problem); nz_max
+// its ens_segments(n, direct) consecutive nodes of that problem); nz_max
 // is the largest nvar * lmax among the problems.
 hipError_t launch_analysis_ens_batch(const AnalysisParams* d_params, const int2* d_waves,
-                                     int nwaves, int n, int nz_max, int storage, hipStream_t s);
+                                     int nwaves, int n, int nz_max, int storage, bool direct,
+                                     hipStream_t s);
 // Observation route (l x l dual, size n >= l) for the `count` nodes listed in
 // `nodes`; gbuf holds obs_gbuf_doubles(n, count) doubles (per-node G and h
 // passed from the eigen kernel to the apply kernel).
@@ -221,6 +222,18 @@ int obs_segments(int n, bool direct); // nodes per block of the eigen kernel
 // set a Jacobi sweep cap below the default: such a cap asks for the iterative solver.
 constexpr int kDefaultSweeps = 30;
 inline bool direct_solver(int max_sweeps) { return max_sweeps >= kDefaultSweeps; }
+// The direct solver's launches (letkf_direct.hip): G and h of the observation route's
+// nodes, per wave list entry or (counters != NULL) as a work queue, and the whole
+// ensemble-route analysis.
+int direct_segments(int n);           // observation-route nodes per block
+hipError_t launch_eig_direct(const AnalysisParams& p, const int* nodes, int count, int n,
+                             double* gbuf, hipStream_t s);
+hipError_t launch_eig_direct_batch(const AnalysisParams* d_params, const int4* d_eig_waves,
+                                   int n_eig, const int* d_nodes, int n, double* gbuf,
+                                   int* counters, hipStream_t s);
+hipError_t launch_ens_direct(const AnalysisParams& p, int n, hipStream_t s);
+hipError_t launch_ens_direct_batch(const AnalysisParams* d_params, const int2* d_waves, int nwaves,
+                                   int n, int storage, hipStream_t s);
 // Batched observation route for one eigenproblem size n over many problems:
 // eigen wavefront w handles eig_waves[w] = (problem, first item, end of that
 // problem's items, -); apply wavefront w handles apply_waves[w] = (problem, item);
@@ -239,6 +252,20 @@ hipError_t launch_analysis_obs_batch_queue(const AnalysisParams* d_params, const
                                            hipStream_t s);
 // Zero n ints with a kernel (capturable in a graph, unlike hipMemsetAsync).
 hipError_t launch_zero_ints(int* v, int n, hipStream_t s);
+// Blocks of a persistent launch: enough wavefronts to fill every CU (16 per CU,
+// the most any of these kernels keeps resident), at most `items`; blocks
+// beyond what fits start later and find the queue drained or nearly so.
+inline int persistent_blocks(int threads, int items) {
+    static int cus = 0;
+    if (cus == 0) {
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+            cus = 256;
+    }
+    const int g = cus * 16 * 64 / threads;  // a multiple of 8: every XCD range has blocks
+    return g < items ? g : items;           // items < g: one block per entry
+}
 int diag_blocks_for(int plane);
 // Bytes of diag_partial_kernel's per-block records for a grid of `plane` nodes.
 size_t diag_partial_bytes(int plane);

@@ -517,6 +517,39 @@ __device__ __forceinline__ void node_diag_record(const double (&f)[9], bool mem,
     }
 }
 
+// Local observation j of `node`: index q into the observation vector, weight
+// sqrt(g / sigma^2) (R_loc^-1/2) and its innovation scaled by that weight.
+__device__ __forceinline__ void local_obs(const AnalysisParams& p, int node, int j, int* q,
+                                          double* w, double* d) {
+    *q = 0;
+    *w = 0.0;
+    if (d) *d = 0.0;
+    if (j >= p.nvar * p.lmax) return;
+    const int slot = j / p.nvar, var = j - slot * p.nvar;
+    const int k = p.loc_pt[(size_t)node * p.lmax + slot];
+    if (k < 0) return;
+    *q = k * p.nvar + var;
+    *w = sqrt(p.loc_g[(size_t)node * p.lmax + slot] * p.rinv[var]);
+    if (d) *d = *w * p.dvec[*q];
+}
+
+// Work-queue form of the batched kernels: a persistent grid whose blocks take
+// entries of the group's wave list from queues in device memory until they are
+// exhausted.  The list is cut into eight contiguous ranges, one per XCD (block
+// b runs on XCD b mod 8), each with its own counter that a block advances by
+// kQueueChunk entries with one lane's vector atomic add: one counter for the
+// whole device would serialise every block's add across the XCDs.  Every block
+// leaves once its counter has passed the end of its range; each entry is
+// processed exactly as in the one-launch-per-wave form.
+constexpr int kQueueChunk = 4;
+
+__device__ __forceinline__ int queue_take(int* counters, int* next, int lo) {
+    __syncthreads();  // the previous entries' LDS use ends before `next` is rewritten
+    if (threadIdx.x == 0) *next = lo + atomicAdd(counters + blockIdx.x % 8, kQueueChunk);
+    __syncthreads();
+    return *next;
+}
+
 // Block b runs on XCD b % 8; give each XCD a contiguous range of work items
 // so that nodes sharing cache lines meet in the same L2.
 __device__ __forceinline__ int xcd_remap(int b, int nblocks) {

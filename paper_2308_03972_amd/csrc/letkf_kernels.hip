@@ -687,7 +687,9 @@ hipError_t launch_ens_batch(const AnalysisParams* P, const int2* waves, int nwav
 }  // namespace
 
 hipError_t launch_analysis_ens_batch(const AnalysisParams* d_params, const int2* d_waves,
-                                     int nwaves, int n, int nz_max, int storage, hipStream_t s) {
+                                     int nwaves, int n, int nz_max, int storage, bool direct,
+                                     hipStream_t s) {
+    if (direct) return launch_ens_direct_batch(d_params, d_waves, nwaves, n, storage, s);
     switch (n) {
         case 8: return launch_ens_batch<8>(d_params, d_waves, nwaves, nz_max, storage, s);
         case 16: return launch_ens_batch<16>(d_params, d_waves, nwaves, nz_max, storage, s);
@@ -708,7 +710,7 @@ int ens_size_for(int n) {
 
 int ens_lds_bytes(int n, int nz) { return ens_lds_doubles(n, nz) * (int)sizeof(double); }
 
-int ens_segments(int n) { return ens_segs(n); }
+int ens_segments(int n, bool direct) { return direct ? (n <= 32 ? 4 : 1) : ens_segs(n); }
 
 hipError_t launch_observe(const void* f, const int* pts, int npts, int nvar, double* yf,
                           LbmDims d, int storage, hipStream_t s) {
@@ -745,7 +747,7 @@ hipError_t launch_local_table(const int* pts, int npts, double d_cut, int lmax, 
 }
 
 hipError_t launch_analysis_ens(const AnalysisParams& p, int n, hipStream_t s) {
-    return launch_ens_sized(p, n, s);
+    return direct_solver(p.max_sweeps) ? launch_ens_direct(p, n, s) : launch_ens_sized(p, n, s);
 }
 
 int diag_blocks_for(int plane) { return (plane + kDiagNodes - 1) / kDiagNodes; }

@@ -13,16 +13,16 @@
 //
 // Two kernels per group of nodes with the same eigenproblem size N (the
 // smallest instantiated even size >= l):
-//   analysis_eig_kernel<N>  64/N nodes per wavefront (a segment of N lanes per
-//     node): local observations, S, the Jacobi eigensolver, and per node the
-//     l x l matrix G and the vector h, written to a buffer;
+//   the solver, which writes per node the l x l matrix G and the vector h to a
+//     buffer: without iterating (letkf_direct.hip), or, when the caller lowered the
+//     Jacobi sweep cap, analysis_eig_kernel<N> here, 64/N nodes per wavefront (a segment
+//     of N lanes per node): local observations, S, the Jacobi eigensolver, G and h;
 //   analysis_apply_kernel   one node per wavefront, lane = member: x_bar, dX,
 //     B, B G, B h and the update of the nine populations.
-// Splitting keeps the register- and LDS-heavy eigensolver apart from the
+// Splitting keeps the register- and LDS-heavy solver apart from the
 // memory-bound state pass, so each runs at its own occupancy.
 #include "common.h"
 #include "device_util.h"
-#include "sym_direct.h"
 
 namespace lbmletkf {
 namespace {
@@ -51,22 +51,6 @@ struct EigLayout {
     static constexpr int kObs = 2 * SEGS * N + (SEGS * N + 1) / 2;  // sw, dt, q
     static constexpr int total = kRows + kVec + kObs;
 };
-
-// Local observation j of `node`: index q into the observation vector, weight
-// sqrt(g / sigma^2) (R_loc^-1/2) and its innovation scaled by that weight.
-__device__ __forceinline__ void local_obs(const AnalysisParams& p, int node, int j, int* q,
-                                          double* w, double* d) {
-    *q = 0;
-    *w = 0.0;
-    if (d) *d = 0.0;
-    if (j >= p.nvar * p.lmax) return;
-    const int slot = j / p.nvar, var = j - slot * p.nvar;
-    const int k = p.loc_pt[(size_t)node * p.lmax + slot];
-    if (k < 0) return;
-    *q = k * p.nvar + var;
-    *w = sqrt(p.loc_g[(size_t)node * p.lmax + slot] * p.rinv[var]);
-    if (d) *d = *w * p.dvec[*q];
-}
 
 // One wavefront: the nodes nodes[item0 + seg] (seg < SEGS, item < end) of one problem.
 template <int N>
@@ -166,74 +150,6 @@ __device__ __forceinline__ void eig_body(const AnalysisParams p, const int* node
             out[(size_t)j * N + i] = g;
         }
         out[(size_t)N * N + i] = h;
-    }
-}
-
-// The same G and h without an eigendecomposition (sym_direct.h): G = -sqrt(beta)/a F(X)
-// and h = X^{-1} d~ / a with X = I + S/a.  One wavefront: the nodes
-// nodes[item0 + 0 .. 3] (item < end), a row of 16 lanes each.
-template <int N>
-__device__ __forceinline__ void direct_body(const AnalysisParams p, const int* nodes, int item0,
-                                            int end, double* gout) {
-    using D = Direct<N>;
-    constexpr int NS = D::NS;
-    extern __shared__ double lds[];
-    const int lane = threadIdx.x;
-    const int r = lane & 15;
-    const int item = item0 + (lane >> 4);
-    const bool valid = item < end;
-    const int node = valid ? nodes[item] : 0;
-    int q[NS];
-    double w[NS], b[NS];
-#pragma unroll
-    for (int h = 0; h < NS; ++h) {
-        q[h] = 0;
-        w[h] = b[h] = 0.0;
-        if (valid && r + 16 * h < N) local_obs(p, node, r + 16 * h, &q[h], &w[h], &b[h]);
-    }
-    // an observation of weight 0 (or a missing one) takes the index of one that counts,
-    // so that the products below meet no other node's values; a node without any
-    // reads (finite) localization weights in place of K
-    const unsigned long long on = __ballot(w[0] != 0.0);
-    const int mask = (int)(on >> (lane & 48)) & 0xffff;
-    const int qf = __builtin_amdgcn_ds_bpermute(((lane & 48) + (mask ? __ffs(mask) - 1 : 0)) * 4, q[0]);
-    const double* krow[NS];
-#pragma unroll
-    for (int h = 0; h < NS; ++h) {
-        if (w[h] == 0.0) q[h] = mask ? qf : 0;
-        krow[h] = mask ? p.K + (size_t)q[h] * p.nobs : p.loc_g;
-    }
-    // S = diag(w) K diag(w): all loads in flight together, then the weights
-    double A[NS][N];
-    auto load = [&](auto self, auto J) -> void {
-        constexpr int j = decltype(J)::value;
-        const int qj = __builtin_amdgcn_mov_dpp(q[j / 16], 0x150 + j % 16, 0xF, 0xF, true);
-#pragma unroll
-        for (int h = 0; h < NS; ++h) A[h][j] = krow[h][qj];
-        if constexpr (j + 1 < N) self(self, std::integral_constant<int, j + 1>());
-    };
-    load(load, std::integral_constant<int, 0>());
-    auto weigh = [&](auto self, auto J) -> void {
-        constexpr int j = decltype(J)::value;
-        const double wj = row_bcast<j % 16>(w[j / 16]);
-#pragma unroll
-        for (int h = 0; h < NS; ++h) A[h][j] *= w[h] * wj;
-        if constexpr (j + 1 < N) self(self, std::integral_constant<int, j + 1>());
-    };
-    weigh(weigh, std::integral_constant<int, 0>());
-    const double ia = 1.0 / p.a;
-    double* out = gout + (size_t)(valid ? item : item0) * (N * N + N);
-    const bool finite = sym_direct<N, false>(A, b, ia, -p.sqrt_beta * ia, lds, out, valid, lane);
-    if (__any(valid && !finite) && lane == 0) atomicAdd(p.eig_fail, 1);
-    if (valid) {
-#pragma unroll
-        for (int h = 0; h < NS; ++h) {
-            const int i = r + 16 * h;
-            if (i >= N) continue;
-#pragma unroll
-            for (int j = 0; j < N; ++j) out[(size_t)j * N + i] = A[h][j];
-            out[(size_t)N * N + i] = b[h] * ia;
-        }
     }
 }
 
@@ -493,60 +409,39 @@ __device__ __forceinline__ void eig_body_split(const AnalysisParams p, const int
 template <int N>
 constexpr bool kSplitRows = N > 32;
 
-// Whether a launch solves without iterating (direct_body): sizes up to 32 unless the
-// caller lowered the Jacobi sweep cap, which asks for the iterative solver and its
-// count of nodes that reach the cap.
-template <int N, bool DIRECT>
-constexpr bool kDirect = DIRECT && N <= 32;
+template <int N>
+constexpr int eig_threads() { return kSplitRows<N> ? 2 * kWave : kWave; }
 
-template <int N, bool DIRECT>
-constexpr int eig_threads() { return !kDirect<N, DIRECT> && kSplitRows<N> ? 2 * kWave : kWave; }
+template <int N>
+constexpr int eig_waves() { return N <= 16 ? 4 : (N <= 22 ? 3 : 1); }
 
-template <int N, bool DIRECT>
-constexpr int eig_waves() {
-    if (kDirect<N, DIRECT>) return N <= 14 ? 4 : (N <= 20 ? 3 : 2);
-    return N <= 16 ? 4 : (N <= 22 ? 3 : 1);
-}
-
-template <int N, bool DIRECT>
+template <int N>
 constexpr int eig_lds_doubles() {
-    if constexpr (kDirect<N, DIRECT>) return 4 * Direct<N>::kNodeDoubles;
-    else if constexpr (kSplitRows<N>) return SplitLayout<N>::total;
+    if constexpr (kSplitRows<N>) return SplitLayout<N>::total;
     else return EigLayout<N>::total;
 }
 
-// Nodes per block of the eigen kernel.
-template <int N, bool DIRECT>
-constexpr int eig_segs() { return kDirect<N, DIRECT> ? 4 : 64 / N; }
-
-template <int N, bool DIRECT>
-__device__ __forceinline__ void eig_node(const AnalysisParams p, const int* nodes, int item0,
-                                         int end, double* gout) {
-    if constexpr (kDirect<N, DIRECT>) direct_body<N>(p, nodes, item0, end, gout);
-    else if constexpr (kSplitRows<N>) eig_body_split<N>(p, nodes, item0, end, gout);
-    else eig_body<N>(p, nodes, item0, end, gout);
-}
-
-template <int N, bool DIRECT>
-__global__ __launch_bounds__((eig_threads<N, DIRECT>()))
-    __attribute__((amdgpu_waves_per_eu(eig_waves<N, DIRECT>())))
+template <int N>
+__global__ __launch_bounds__(eig_threads<N>()) __attribute__((amdgpu_waves_per_eu(eig_waves<N>())))
 void analysis_eig_kernel(AnalysisParams p, const int* nodes, int count, double* gout) {
-    eig_node<N, DIRECT>(p, nodes, xcd_remap(blockIdx.x, gridDim.x) * eig_segs<N, DIRECT>(), count,
-                        gout);
+    if constexpr (kSplitRows<N>)
+        eig_body_split<N>(p, nodes, xcd_remap(blockIdx.x, gridDim.x), count, gout);
+    else
+        eig_body<N>(p, nodes, xcd_remap(blockIdx.x, gridDim.x) * EigLayout<N>::SEGS, count, gout);
 }
 
 // Batched form: wavefront w takes waves[w] = (problem, first item, end of the
 // problem's items); the items of all problems share one node list and one G buffer.
-template <int N, bool DIRECT>
-__global__ __launch_bounds__((eig_threads<N, DIRECT>()))
-    __attribute__((amdgpu_waves_per_eu(eig_waves<N, DIRECT>())))
+template <int N>
+__global__ __launch_bounds__(eig_threads<N>()) __attribute__((amdgpu_waves_per_eu(eig_waves<N>())))
 void analysis_eig_batch_kernel(const AnalysisParams* P, const int4* waves, int nwaves,
                                const int* nodes, double* gout) {
     const int w = xcd_remap(blockIdx.x, gridDim.x);
     if (w >= nwaves) return;
     const int4 d = waves[w];
     const AnalysisParams p = P[d.x];
-    eig_node<N, DIRECT>(p, nodes, d.y, d.z, gout);
+    if constexpr (kSplitRows<N>) eig_body_split<N>(p, nodes, d.y, d.z, gout);
+    else eig_body<N>(p, nodes, d.y, d.z, gout);
 }
 
 // Dynamic LDS beyond 64 KiB needs the kernel's permission (set once per kernel).
@@ -968,26 +863,8 @@ __global__ __launch_bounds__(64) void analysis_apply_batch_kernel(const Analysis
     apply_node<N, T, MF>(p, nodes, d.y, gin);
 }
 
-// Work-queue form of the batched kernels: a persistent grid whose blocks take
-// entries of the group's wave list from queues in device memory until they are
-// exhausted.  The list is cut into eight contiguous ranges, one per XCD (block
-// b runs on XCD b mod 8), each with its own counter that a block advances by
-// kQueueChunk entries with one lane's vector atomic add: one counter for the
-// whole device would serialise every block's add across the XCDs.  Every block
-// leaves once its counter has passed the end of its range; each entry is
-// processed exactly as in the one-launch-per-wave form.
-constexpr int kQueueChunk = 4;
-
-__device__ __forceinline__ int queue_take(int* counters, int* next, int lo) {
-    __syncthreads();  // the previous entries' LDS use ends before `next` is rewritten
-    if (threadIdx.x == 0) *next = lo + atomicAdd(counters + blockIdx.x % 8, kQueueChunk);
-    __syncthreads();
-    return *next;
-}
-
-template <int N, bool DIRECT>
-__global__ __launch_bounds__((eig_threads<N, DIRECT>()))
-    __attribute__((amdgpu_waves_per_eu(eig_waves<N, DIRECT>())))
+template <int N>
+__global__ __launch_bounds__(eig_threads<N>()) __attribute__((amdgpu_waves_per_eu(eig_waves<N>())))
 void analysis_eig_queue_kernel(const AnalysisParams* P, const int4* waves, int nwaves,
                                const int* nodes, double* gout, int* counters) {
     __shared__ int next;
@@ -1002,7 +879,8 @@ void analysis_eig_queue_kernel(const AnalysisParams* P, const int4* waves, int n
             if (w > w0) __syncthreads();
             const int4 d = waves[w];
             const AnalysisParams p = P[d.x];
-            eig_node<N, DIRECT>(p, nodes, d.y, d.z, gout);
+            if constexpr (kSplitRows<N>) eig_body_split<N>(p, nodes, d.y, d.z, gout);
+            else eig_body<N>(p, nodes, d.y, d.z, gout);
         }
     }
 }
@@ -1030,33 +908,17 @@ __global__ __launch_bounds__(64) void analysis_apply_queue_kernel(const Analysis
     }
 }
 
-// Blocks of a persistent launch: enough wavefronts to fill every CU (16 per CU,
-// the most any of these kernels keeps resident), at most `items`; blocks
-// beyond what fits start later and find the queue drained or nearly so.
-inline int persistent_blocks(int threads, int items) {
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-            cus = 256;
-    }
-    const int g = cus * 16 * 64 / threads;  // a multiple of 8: every XCD range has blocks
-    return g < items ? g : items;           // items < g: one block per entry
-}
-
-// The eigen launch of one size: the direct solver, or the Jacobi solver where the size
-// or the sweep cap asks for it.
-template <int N, bool DIRECT>
-hipError_t launch_eig_n(const AnalysisParams& p, const int* nodes, int count, double* gbuf,
-                        hipStream_t s) {
-    const size_t bytes = (size_t)eig_lds_doubles<N, DIRECT>() * sizeof(double);
-    constexpr int segs = eig_segs<N, DIRECT>();
+// The eigen launch of one size with the Jacobi solver.
+template <int N>
+hipError_t launch_jacobi_n(const AnalysisParams& p, const int* nodes, int count, double* gbuf,
+                           hipStream_t s) {
+    const size_t bytes = (size_t)eig_lds_doubles<N>() * sizeof(double);
+    constexpr int segs = kSplitRows<N> ? 1 : 64 / N;
     static bool lds_ok = false;
-    hipError_t e = allow_lds(analysis_eig_kernel<N, DIRECT>, bytes, &lds_ok);
+    hipError_t e = allow_lds(analysis_eig_kernel<N>, bytes, &lds_ok);
     if (e != hipSuccess) return e;
-    analysis_eig_kernel<N, DIRECT><<<(count + segs - 1) / segs, eig_threads<N, DIRECT>(), bytes,
-                                     s>>>(p, nodes, count, gbuf);
+    analysis_eig_kernel<N><<<(count + segs - 1) / segs, eig_threads<N>(), bytes, s>>>(p, nodes,
+                                                                                      count, gbuf);
     return hipGetLastError();
 }
 
@@ -1064,8 +926,8 @@ template <int N>
 hipError_t launch_n(const AnalysisParams& p, const int* nodes, int count, double* gbuf,
                     hipStream_t s) {
     if (count == 0) return hipSuccess;
-    hipError_t e = direct_solver(p.max_sweeps) ? launch_eig_n<N, true>(p, nodes, count, gbuf, s)
-                                               : launch_eig_n<N, false>(p, nodes, count, gbuf, s);
+    hipError_t e = direct_solver(p.max_sweeps) ? launch_eig_direct(p, nodes, count, N, gbuf, s)
+                                               : launch_jacobi_n<N>(p, nodes, count, gbuf, s);
     if (e != hipSuccess) return e;
     const size_t app_bytes = (size_t)apply_lds_doubles(N) * sizeof(double);
     if (p.storage == kStoreF32Dev && p.mfma_transform && kMfmaApply<N>)
@@ -1077,23 +939,24 @@ hipError_t launch_n(const AnalysisParams& p, const int* nodes, int count, double
     return hipGetLastError();
 }
 
-template <int N, bool DIRECT>
-hipError_t launch_eig_batch_n(const AnalysisParams* d_params, const int4* d_eig_waves, int n_eig,
-                              const int* d_nodes, double* gbuf, int* counters, hipStream_t s) {
-    const size_t bytes = (size_t)eig_lds_doubles<N, DIRECT>() * sizeof(double);
+// The batched eigen launch with the Jacobi solver, per wave or (counters) as a queue.
+template <int N>
+hipError_t launch_jacobi_batch_n(const AnalysisParams* d_params, const int4* d_eig_waves, int n_eig,
+                                 const int* d_nodes, double* gbuf, int* counters, hipStream_t s) {
+    const size_t bytes = (size_t)eig_lds_doubles<N>() * sizeof(double);
     hipError_t e;
     if (counters) {
         static bool lds_ok = false;
-        e = allow_lds(analysis_eig_queue_kernel<N, DIRECT>, bytes, &lds_ok);
+        e = allow_lds(analysis_eig_queue_kernel<N>, bytes, &lds_ok);
         if (e != hipSuccess) return e;
-        const int ge = persistent_blocks(eig_threads<N, DIRECT>(), n_eig);
-        analysis_eig_queue_kernel<N, DIRECT><<<ge, eig_threads<N, DIRECT>(), bytes, s>>>(
-            d_params, d_eig_waves, n_eig, d_nodes, gbuf, counters);
+        analysis_eig_queue_kernel<N><<<persistent_blocks(eig_threads<N>(), n_eig), eig_threads<N>(),
+                                       bytes, s>>>(d_params, d_eig_waves, n_eig, d_nodes, gbuf,
+                                                   counters);
     } else {
         static bool lds_ok = false;
-        e = allow_lds(analysis_eig_batch_kernel<N, DIRECT>, bytes, &lds_ok);
+        e = allow_lds(analysis_eig_batch_kernel<N>, bytes, &lds_ok);
         if (e != hipSuccess) return e;
-        analysis_eig_batch_kernel<N, DIRECT><<<n_eig, eig_threads<N, DIRECT>(), bytes, s>>>(
+        analysis_eig_batch_kernel<N><<<n_eig, eig_threads<N>(), bytes, s>>>(
             d_params, d_eig_waves, n_eig, d_nodes, gbuf);
     }
     return hipGetLastError();
@@ -1105,10 +968,10 @@ hipError_t launch_batch_n(const AnalysisParams* d_params, const int4* d_eig_wave
                           double* gbuf, int storage, bool mfma_transform, bool direct,
                           hipStream_t s) {
     if (n_eig == 0) return hipSuccess;
-    hipError_t e = direct ? launch_eig_batch_n<N, true>(d_params, d_eig_waves, n_eig, d_nodes, gbuf,
-                                                        nullptr, s)
-                          : launch_eig_batch_n<N, false>(d_params, d_eig_waves, n_eig, d_nodes,
-                                                         gbuf, nullptr, s);
+    hipError_t e = direct ? launch_eig_direct_batch(d_params, d_eig_waves, n_eig, d_nodes, N, gbuf,
+                                                    nullptr, s)
+                          : launch_jacobi_batch_n<N>(d_params, d_eig_waves, n_eig, d_nodes, gbuf,
+                                                     nullptr, s);
     if (e != hipSuccess) return e;
     const size_t app_bytes = (size_t)apply_lds_doubles(N) * sizeof(double);
     if (storage == kStoreF32Dev && mfma_transform && kMfmaApply<N>)
@@ -1129,10 +992,10 @@ hipError_t launch_batch_queue_n(const AnalysisParams* d_params, const int4* d_ei
                                 double* gbuf, int storage, bool mfma_transform, bool direct,
                                 int* counters, hipStream_t s) {
     if (n_eig == 0) return hipSuccess;
-    hipError_t e = direct ? launch_eig_batch_n<N, true>(d_params, d_eig_waves, n_eig, d_nodes, gbuf,
-                                                        counters, s)
-                          : launch_eig_batch_n<N, false>(d_params, d_eig_waves, n_eig, d_nodes,
-                                                         gbuf, counters, s);
+    hipError_t e = direct ? launch_eig_direct_batch(d_params, d_eig_waves, n_eig, d_nodes, N, gbuf,
+                                                    counters, s)
+                          : launch_jacobi_batch_n<N>(d_params, d_eig_waves, n_eig, d_nodes, gbuf,
+                                                     counters, s);
     if (e != hipSuccess) return e;
     const size_t app_bytes = (size_t)apply_lds_doubles(N) * sizeof(double);
     auto go = [&](auto kernel) {
@@ -1165,7 +1028,7 @@ int obs_size_for(int n) {
 
 int obs_lds_bytes(int n) {
     switch (n) {
-#define X(v) case v: return (eig_lds_doubles<v, false>() > apply_lds_doubles(v) ? eig_lds_doubles<v, false>() \
+#define X(v) case v: return (eig_lds_doubles<v>() > apply_lds_doubles(v) ? eig_lds_doubles<v>() \
                                                                         : apply_lds_doubles(v)) * \
                             (int)sizeof(double);
         LBMLETKF_OBS_SIZES(X)
@@ -1199,12 +1062,7 @@ hipError_t launch_zero_ints(int* v, int n, hipStream_t s) {
 }
 
 int obs_segments(int n, bool direct) {
-    switch (n) {
-#define X(v) case v: return direct ? eig_segs<v, true>() : eig_segs<v, false>();
-        LBMLETKF_OBS_SIZES(X)
-#undef X
-        default: return 0;
-    }
+    return direct ? direct_segments(n) : (n > 0 ? 64 / n : 0);
 }
 
 hipError_t launch_analysis_obs_batch_queue(const AnalysisParams* d_params, const int4* d_eig_waves,
@@ -1216,7 +1074,7 @@ hipError_t launch_analysis_obs_batch_queue(const AnalysisParams* d_params, const
 #define X(v)                                                                                \
     case v:                                                                                 \
         return launch_batch_queue_n<v>(d_params, d_eig_waves, n_eig, d_apply_waves, n_apply, \
-                                       d_nodes, gbuf, storage, mfma_transform, direct,        \
+                                       d_nodes, gbuf, storage, mfma_transform, direct,      \
                                        counters, s);
         LBMLETKF_OBS_SIZES(X)
 #undef X

@@ -162,19 +162,46 @@ struct Direct {
     static constexpr int ZS = N + 1;              // stride of the LDS tables (odd)
     static constexpr int kNodeDoubles = 16 * ZS;  // per node: pole table, then the transposes
     static constexpr int kTop = (N - 1 + 3) / 4 * 4;  // first phase's width
+    // the pole recurrence's values between its two passes: in registers up to N = 20,
+    // beyond that in the LDS table (registers would spill)
+    static constexpr bool kValLds = N > 20;
+};
+
+// Where the reflectors wait for the back transformation: a device-memory scratch with
+// row n - 3 for step n (written and read by the same lanes), or LDS, step n's n - 1
+// entries packed.
+struct ReflGlobal {
+    double* p;
+    int stride;
+    bool on;  // false: a lane group without a node stores nothing
+    __device__ __forceinline__ void put(int n, int i, double v) const {
+        if (on && i < stride) p[(size_t)(n - 3) * stride + i] = v;
+    }
+    __device__ __forceinline__ double get(int n, int i) const {
+        return i < stride ? p[(size_t)(n - 3) * stride + i] : 0.0;
+    }
+};
+struct ReflLds {
+    double* p;
+    __host__ __device__ static constexpr int doubles(int n) { return n * (n - 1) / 2; }
+    __device__ __forceinline__ void put(int n, int i, double v) const {
+        if (i < n - 1) p[(n - 2) * (n - 1) / 2 + i] = v;
+    }
+    __device__ __forceinline__ double get(int n, int i) const {
+        return i < n - 1 ? p[(n - 2) * (n - 1) / 2 + i] : 0.0;
+    }
 };
 
 // One phase of the tridiagonalisation: the columns n - 1 for n = min(N, W + 1) down to
 // max(3, W - 2) are eliminated on rows and columns < W (n - 1 <= W).  The reflector of
 // step n, H = I - v v^T on indices 0 .. n - 2 (|v|^2 = 2, or v = 0), goes to
-// vs[(n - 3) * N + i]; d and e receive the diagonal and the coupling (i, i + 1); b
+// `vs`; d and e receive the diagonal and the coupling (i, i + 1); b
 // becomes H b.  Widths in steps of four keep the code small (each phase is a loop)
 // at the price of a few columns that are no longer needed.
-template <int N, int W>
+template <int N, int W, typename R>
 __device__ __forceinline__ void tri_phase(double (&A)[Direct<N>::NS][N],
                                           double (&d)[Direct<N>::NS], double (&e)[Direct<N>::NS],
-                                          double (&b)[Direct<N>::NS], double* vs, bool store,
-                                          int lane) {
+                                          double (&b)[Direct<N>::NS], const R& vs, int lane) {
     constexpr int NS = Direct<N>::NS;
     constexpr int WC = W < N ? W : N;              // columns and rows of the support
     constexpr int SW = (WC + 15) / 16;             // row slots of the support
@@ -211,7 +238,7 @@ __device__ __forceinline__ void tri_phase(double (&A)[Direct<N>::NS][N],
             const bool piv = r + 16 * h == n - 2;
             e[h] = piv ? alpha : e[h];
             v[h] = (x[h] + (piv ? shift : 0.0)) * rb;
-            if (store && r + 16 * h < N) vs[(size_t)(n - 3) * N + r + 16 * h] = v[h];
+            vs.put(n, r + 16 * h, v[h]);
         }
         double c = 0.0, cb = 0.0;
 #pragma unroll
@@ -234,10 +261,9 @@ __device__ __forceinline__ void tri_phase(double (&A)[Direct<N>::NS][N],
 
 // The reflectors of one phase applied from both sides, G <- H G H, in ascending n, and
 // hv <- H hv.
-template <int N, int W>
+template <int N, int W, typename R>
 __device__ __forceinline__ void back_phase(double (&G)[Direct<N>::NS][N],
-                                           double (&hv)[Direct<N>::NS], const double* vs,
-                                           int lane) {
+                                           double (&hv)[Direct<N>::NS], const R& vs, int lane) {
     constexpr int NS = Direct<N>::NS;
     constexpr int WC = W < N ? W : N;
     constexpr int SW = (WC + 15) / 16;
@@ -248,8 +274,7 @@ __device__ __forceinline__ void back_phase(double (&G)[Direct<N>::NS][N],
     for (int n = LO; n <= HI; ++n) {
         double v[SW], p[NS];
 #pragma unroll
-        for (int h = 0; h < SW; ++h)
-            v[h] = r + 16 * h < N ? vs[(size_t)(n - 3) * N + r + 16 * h] : 0.0;
+        for (int h = 0; h < SW; ++h) v[h] = vs.get(n, r + 16 * h);
         double c = 0.0, ch = 0.0;
 #pragma unroll
         for (int h = 0; h < NS; ++h) {
@@ -275,16 +300,16 @@ __device__ __forceinline__ void back_phase(double (&G)[Direct<N>::NS][N],
     }
 }
 
-template <int N, int W>
+template <int N, int W, typename R>
 __device__ __forceinline__ void tri_all(double (&A)[Direct<N>::NS][N], double (&d)[Direct<N>::NS],
                                         double (&e)[Direct<N>::NS], double (&b)[Direct<N>::NS],
-                                        double* vs, bool store, int lane) {
-    tri_phase<N, W>(A, d, e, b, vs, store, lane);
-    if constexpr (W > 4) tri_all<N, W - 4>(A, d, e, b, vs, store, lane);
+                                        const R& vs, int lane) {
+    tri_phase<N, W>(A, d, e, b, vs, lane);
+    if constexpr (W > 4) tri_all<N, W - 4>(A, d, e, b, vs, lane);
 }
-template <int N, int W>
+template <int N, int W, typename R>
 __device__ __forceinline__ void back_all(double (&G)[Direct<N>::NS][N], double (&hv)[Direct<N>::NS],
-                                         const double* vs, int lane) {
+                                         const R& vs, int lane) {
     if constexpr (W > 4) back_all<N, W - 4>(G, hv, vs, lane);
     back_phase<N, W>(G, hv, vs, lane);
 }
@@ -298,14 +323,43 @@ __device__ __forceinline__ float row_sum_f32(float m) {
     return m;
 }
 
-// Pole class of a wavefront: kappa = 1 + the largest norm of its four nodes, each
-// norm^2 given as a sum over the node's lanes; a NaN does not count.
+// Adds two poles' entries of one row of the tridiagonal inverse, columns J.. of the
+// slot that starts at column H: z_ii (wa, wb) on the diagonal, then z_{i,j+1} = g_j z_{i,j};
+// four columns at a time (pa, pb: the column before).
+template <int N, int H, int J>
+__device__ __forceinline__ void row_chain(double (&a)[N], const double (&g)[N], double wa, double wb,
+                                          double pa, double pb, int pr, int r) {
+    constexpr int C = N - J < 4 ? N - J : 4;
+    constexpr int F = J == H ? 1 : 0;  // the slot's first column has no predecessor
+    double ua[4] = {0.0, 0.0, 0.0, 0.0}, ub[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+        const bool own = J + k < H + 16 && r == J + k - H;
+        ua[k] = own ? wa : 0.0;
+        ub[k] = own ? wb : 0.0;
+    }
+    if (pr == 0)
+        fmac_chain<0, C - F>(ua + F, ub + F, g + (F ? J : J - 1), F ? ua[0] : pa, F ? ub[0] : pb);
+    else
+        fmac_chain<2, C - F>(ua + F, ub + F, g + (F ? J : J - 1), F ? ua[0] : pa, F ? ub[0] : pb);
+#pragma unroll
+    for (int k = 0; k < C; ++k) a[J + k] += ua[k] + ub[k];
+    if constexpr (J + C < N)
+        row_chain<N, H, J + C>(a, g, wa, wb, ua[C - 1], ub[C - 1], pr, r);
+}
+
+// Pole class of a wavefront: kappa = 1 + the largest norm of its four nodes (WAVE: of
+// its one node), norm^2 given as a sum over the node's lanes; a NaN does not count.
+template <bool WAVE>
 __device__ __forceinline__ int pole_class(float part) {
     const float n2 = row_sum_f32(part);
     float w = 0.0f;
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-        w = fmaxf(w, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(n2), 16 * k)));
+    for (int k = 0; k < 4; ++k) {
+        const float row = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(n2), 16 * k));
+        w = WAVE ? w + row : fmaxf(w, row);
+    }
+    if (!(w >= 0.0f)) w = 0.0f;
     // kappa <= 2^e: the exponent of 1 + norm (a little enlarged against FP32 rounding),
     // rounded up
     const float kappa = 1.0f + 1.0001f * __builtin_amdgcn_sqrtf(w);
@@ -317,13 +371,12 @@ __device__ __forceinline__ int pole_class(float part) {
 
 // For the four nodes of a wavefront, with X = I + S/a (rows of S in A, S >= 0):
 //   A <- scale * F(X)   (scale * X^{-1/2} if ROOT),   b <- X^{-1} b.
-// lds: 4 * Direct<N>::kNodeDoubles doubles; vs: this node's scratch of (N - 2) * N
-// doubles in device memory (written and read by the same lanes; `store` false for a
-// row without a node).  Returns false if a node's matrix is not finite.
-template <int N, bool ROOT>
+// lds: 4 * Direct<N>::kNodeDoubles doubles; vs: this node's reflector store.  Returns
+// false if a node's matrix is not finite.
+template <int N, bool ROOT, typename R>
 __device__ __forceinline__ bool sym_direct(double (&A)[Direct<N>::NS][N],
                                            double (&b)[Direct<N>::NS], double ia, double scale,
-                                           double* lds, double* vs, bool store, int lane) {
+                                           double* lds, const R& vs, int lane) {
     using D = Direct<N>;
     constexpr int NS = D::NS;
     constexpr int ZS = D::ZS;
@@ -332,7 +385,7 @@ __device__ __forceinline__ bool sym_direct(double (&A)[Direct<N>::NS][N],
     double d[NS], e[NS];
 #pragma unroll
     for (int h = 0; h < NS; ++h) d[h] = e[h] = 0.0;
-    tri_all<N, D::kTop>(A, d, e, b, vs, store, lane);
+    tri_all<N, D::kTop>(A, d, e, b, vs, lane);
     // rows 0 and 1 are left: d_0, d_1, e_0
     d[0] = r == 0 ? A[0][0] : (r == 1 ? A[0][1] : d[0]);
     e[0] = r == 0 ? A[0][1] : e[0];
@@ -347,7 +400,7 @@ __device__ __forceinline__ bool sym_direct(double (&A)[Direct<N>::NS][N],
         const float df = (float)d[h], ef = (float)e[h];
         f2 += df * df + 2.0f * ef * ef;
     }
-    const int cls = pole_class(f2);
+    const int cls = pole_class<false>(f2);
     const int p0 = kPoleOffset[cls], np = kPoleOffset[cls + 1] - p0;
 
 #pragma unroll
@@ -365,7 +418,11 @@ __device__ __forceinline__ bool sym_direct(double (&A)[Direct<N>::NS][N],
         double cw = pi >= 0 ? kSqrtPoles[pi < 0 ? 0 : pi].c * scale : 0.0;
         if constexpr (ROOT) cw *= 1.0 + t2;
         const double base = 1.0 + t2;
-        double g[N], rg[N], y[N];
+        // val_j = 1 / gamma_j, and on lane 15 y_j / gamma_j with U y = b: the same downward
+        // recurrence then gives z_jj on lanes 0..14 and the solution of X h = b on lane 15
+        const bool inv = r == 15;
+        double g[N], val[N];
+        double rg = 0.0, y = 0.0;
         auto col = [](const double (&v)[NS], auto J) {
             constexpr int j = decltype(J)::value;
             return row_bcast<j % 16>(v[j / 16]);
@@ -373,29 +430,32 @@ __device__ __forceinline__ bool sym_direct(double (&A)[Direct<N>::NS][N],
         auto down = [&](auto self, auto J) -> void {
             constexpr int j = decltype(J)::value;
             double gam = base + col(d, J);
-            const double bj = col(b, J);
             if constexpr (j == N - 1) {
                 g[j] = 0.0;
-                y[j] = bj;
+                y = col(b, J);
             } else {
                 const double ej = col(e, J);
-                g[j] = -ej * rg[j + 1];
+                g[j] = -ej * rg;
                 gam = fma(g[j], ej, gam);
-                y[j] = fma(g[j], y[j + 1], bj);
+                y = fma(g[j], y, col(b, J));
             }
-            rg[j] = fast_rcp(gam);
+            rg = fast_rcp(gam);
+            const double v = inv ? y * rg : rg;
+            if constexpr (D::kValLds) zt[r * ZS + j] = v;
+            else val[j] = v;
             if constexpr (j > 0) self(self, std::integral_constant<int, j - 1>());
         };
         down(down, std::integral_constant<int, N - 1>());
-        wave_lds_sync();
+        if constexpr (!D::kValLds) wave_lds_sync();
         {
-            double z = rg[0], hh = y[0] * rg[0];
-            zt[r * ZS] = r == 15 ? hh : z * cw;
+            const double cx = inv ? 1.0 : cw;
+            double z = 0.0;
 #pragma unroll
-            for (int j = 0; j < N - 1; ++j) {
-                z = fma(g[j], g[j] * z, rg[j + 1]);
-                hh = fma(g[j], hh, y[j + 1] * rg[j + 1]);
-                zt[r * ZS + j + 1] = r == 15 ? hh : z * cw;
+            for (int j = 0; j < N; ++j) {
+                const double v = D::kValLds ? zt[r * ZS + j] : val[j];
+                const double m = j == 0 ? 0.0 : (inv ? g[j - 1] : g[j - 1] * g[j - 1]);
+                z = fma(m, z, v);
+                zt[r * ZS + j] = z * cx;
             }
         }
         wave_lds_sync();
@@ -416,27 +476,9 @@ __device__ __forceinline__ bool sym_direct(double (&A)[Direct<N>::NS][N],
                     wb[h] = zt[(q + pr + 1) * ZS + i];
                     if (q + pr + 1 == 15) wb[h] = 0.0;
                 }
-#pragma unroll
-                for (int h = 0; h < NS; ++h) {
-                    double ua[N], ub[N];
-#pragma unroll
-                    for (int j = 16 * h; j < N; ++j) {
-                        const bool own = j < 16 * h + 16 && r == j - 16 * h;
-                        ua[j] = own ? wa[h] : 0.0;
-                        ub[j] = own ? wb[h] : 0.0;
-                    }
-                    if (h == 0) {
-                        if (pr == 0) fmac_chain<0, N - 1>(ua + 1, ub + 1, g, ua[0], ub[0]);
-                        else fmac_chain<2, N - 1>(ua + 1, ub + 1, g, ua[0], ub[0]);
-                    } else if constexpr (NS > 1) {
-                        if (pr == 0)
-                            fmac_chain<0, N - 17>(ua + 17, ub + 17, g + 16, ua[16], ub[16]);
-                        else
-                            fmac_chain<2, N - 17>(ua + 17, ub + 17, g + 16, ua[16], ub[16]);
-                    }
-#pragma unroll
-                    for (int j = 16 * h; j < N; ++j) A[h][j] += ua[j] + ub[j];
-                }
+                row_chain<N, 0, 0>(A[0], g, wa[0], wb[0], 0.0, 0.0, pr, r);
+                if constexpr (NS > 1)
+                    row_chain<N, 16, 16>(A[NS - 1], g, wa[NS - 1], wb[NS - 1], 0.0, 0.0, pr, r);
             }
 #pragma unroll
             for (int j = 0; j < N - 1; ++j) {
@@ -456,7 +498,10 @@ __device__ __forceinline__ bool sym_direct(double (&A)[Direct<N>::NS][N],
 #pragma unroll
     for (int j = 0; j < (N < 16 ? N : 16); ++j)
 #pragma unroll
-        for (int h = 0; h < NS; ++h) A[h][j] += r + 16 * h < N ? zt[j * ZS + r + 16 * h] : 0.0;
+        for (int h = 0; h < NS; ++h) {
+            const double t = zt[j * ZS + (r + 16 * h < N ? r + 16 * h : 0)];
+            A[h][j] += r + 16 * h < N ? t : 0.0;
+        }
     if constexpr (NS > 1) {
         wave_lds_sync();
         if (r + 16 < N) {
@@ -466,11 +511,347 @@ __device__ __forceinline__ bool sym_direct(double (&A)[Direct<N>::NS][N],
         }
         wave_lds_sync();
 #pragma unroll
-        for (int j = 16; j < N; ++j) A[1][j] += r + 16 < N ? zt[(j - 16) * ZS + r + 16] : 0.0;
+        for (int j = 16; j < N; ++j) {
+            const double t = zt[(j - 16) * ZS + (r + 16 < N ? r + 16 : 0)];
+            A[1][j] += r + 16 < N ? t : 0.0;
+        }
     }
 #pragma unroll
     for (int h = 0; h < NS; ++h) b[h] = hv[h];
     back_all<N, D::kTop>(A, b, vs, lane);
+    return finite;
+}
+
+// ---------------------------------------------------------------------------
+// one node per wavefront, 32 < N <= 64
+// ---------------------------------------------------------------------------
+// Lane (g, r) = (lane / 16, lane % 16) holds columns 16 g .. 16 g + 15 of the rows 16 h + r,
+// h < NS: NS x 16 doubles, half the registers of whole rows two to a lane, and still
+// every broadcast is a row_newbcast inside the lane's own row of 16.  A vector lives
+// "by element" (element = lane) as the broadcast operand and "by row" (element 16 h + r
+// in register h) as the lane's own factor; the two forms, and the sum of the four
+// column blocks' partial products, go through LDS.
+template <int N>
+struct DirectW {
+    static_assert(N > 32 && N <= 64 && N % 8 == 0, "three or four rows of 16");
+    static constexpr int NS = (N + 15) / 16;
+    static constexpr int ZS = 16 * NS + 1;
+    static constexpr int kTab = 16 * ZS;
+    // tables g, z, e; block products [16][4]; partial products [4][64]; two vectors
+    static constexpr int kDoubles = 3 * kTab + 64 + 256 + 128;
+};
+
+// x (element = lane) as rows: out[h] = element 16 h + r, through the LDS vector vec.
+template <int S>
+__device__ __forceinline__ void to_rows(double x, double (&out)[S], double* vec, int lane) {
+    wave_lds_sync();
+    vec[lane] = x;
+    wave_lds_sync();
+#pragma unroll
+    for (int h = 0; h < S; ++h) out[h] = vec[16 * h + (lane & 15)];
+}
+
+// Element lane of A v: the partial products over this lane's W columns, summed over
+// the first GR column blocks (the others' v is zero).
+template <int NS, int SP, int GR, int W>
+__device__ __forceinline__ double wave_matvec(const double (&A)[NS][16], double v, double* part,
+                                              int lane) {
+    double pr[SP];
+#pragma unroll
+    for (int h = 0; h < SP; ++h) {
+        double s0 = 0.0, s1 = 0.0;
+        fmac_dot<0, W>(A[h], v, s0, s1);
+        pr[h] = s0 + s1;
+    }
+    const int g = lane >> 4, r = lane & 15;
+    wave_lds_sync();
+    if (g < GR) {
+#pragma unroll
+        for (int h = 0; h < SP; ++h) part[64 * g + 16 * h + r] = pr[h];
+    }
+    wave_lds_sync();
+    double p = 0.0;
+    if (lane < 16 * SP) {
+#pragma unroll
+        for (int k = 0; k < GR; ++k) p += part[64 * k + lane];
+    }
+    return p;
+}
+
+// The steps n - 1 = HI .. LO of the tridiagonalisation, pivot rows in slot S (supports
+// within slots 0 .. S); W columns per block (less than 16 only for S = 0).
+template <int N, int S, int HI, int LO, int W, typename R>
+__device__ __forceinline__ void wtri_phase(double (&A)[DirectW<N>::NS][16], double& d, double& e,
+                                           double& b, double* lds, const R& vs, int lane) {
+    using D = DirectW<N>;
+    constexpr int NS = D::NS;
+    double* part = lds + 3 * D::kTab + 64;
+    double* vec = part + 256;
+    const int g = lane >> 4, r = lane & 15;
+#pragma unroll 1
+    for (int n = HI + 1; n > LO; --n) {
+        // row n - 1 (by symmetry column n - 1): its 16-column pieces sit in the lanes
+        // (g, (n - 1) % 16)
+        wave_lds_sync();
+        if (r == ((n - 1) & 15) && g <= S) {
+#pragma unroll
+            for (int k = 0; k < 16; k += 2)
+                *reinterpret_cast<double2*>(vec + 16 * g + k) = make_double2(A[S][k], A[S][k + 1]);
+        }
+        wave_lds_sync();
+        const double raw = lane < n ? vec[lane] : 0.0;
+        d = lane == n - 1 ? raw : d;
+        const double x = lane < n - 1 ? raw : 0.0;
+        const double s2 = wave_sum(x * x);
+        const double x1 = lane_value(x, n - 2);
+        const bool some = s2 > 1e-290;
+        const double norm = s2 * fast_rsqrt(s2);
+        const double rb = some ? fast_rsqrt(fma(fabs(x1), norm, s2)) : 0.0;
+        const double alpha = some ? -copysign(norm, x1) : x1;
+        const double shift = some ? copysign(norm, x1) : 0.0;
+        const bool piv = lane == n - 2;
+        e = piv ? alpha : e;
+        const double v = (x + (piv ? shift : 0.0)) * rb;
+        vs.put(n, lane, v);
+        double vr[S + 1], p_r[S + 1];
+        to_rows<S + 1>(v, vr, vec + 64, lane);
+        const double p = wave_matvec<NS, S + 1, S + 1, W>(A, v, part, lane);
+        const double c = wave_sum(v * p);
+        b = fma(-wave_sum(v * b), v, b);
+        to_rows<S + 1>(p, p_r, vec, lane);
+#pragma unroll
+        for (int h = 0; h <= S; ++h) {
+            fmac_axpy<0, W>(A[h], p, -vr[h]);
+            fmac_axpy<0, W>(A[h], v, -fma(-c, vr[h], p_r[h]));
+        }
+    }
+}
+
+// The same steps of the back transformation, ascending.
+template <int N, int S, int HI, int LO, int W, typename R>
+__device__ __forceinline__ void wback_phase(double (&G)[DirectW<N>::NS][16], double& hv, double* lds,
+                                            const R& vs, int lane) {
+    using D = DirectW<N>;
+    constexpr int NS = D::NS;
+    double* part = lds + 3 * D::kTab + 64;
+    double* vec = part + 256;
+#pragma unroll 1
+    for (int n = LO + 1; n <= HI + 1; ++n) {
+        const double v = vs.get(n, lane);
+        double vr[S + 1], p_r[NS];
+        to_rows<S + 1>(v, vr, vec + 64, lane);
+        const double p = wave_matvec<NS, NS, S + 1, W>(G, v, part, lane);
+        const double c = wave_sum(v * p);
+        hv = fma(-wave_sum(v * hv), v, hv);
+        to_rows<NS>(p, p_r, vec, lane);
+#pragma unroll
+        for (int h = 0; h < NS; ++h) {
+            if (h <= S) {
+                const double vh = vr[h <= S ? h : 0];
+                fmac_axpy<0, 16>(G[h], p, -vh);
+                fmac_axpy<0, W>(G[h], v, -fma(-c, vh, p_r[h]));
+            } else {
+                fmac_axpy<0, W>(G[h], v, -p_r[h]);
+            }
+        }
+    }
+}
+
+template <int N, int S, typename R>
+__device__ __forceinline__ void wtri_all(double (&A)[DirectW<N>::NS][16], double& d, double& e,
+                                         double& b, double* lds, const R& vs, int lane) {
+    constexpr int HI = 16 * S + 15 < N - 1 ? 16 * S + 15 : N - 1;
+    if constexpr (S > 0) {
+        wtri_phase<N, S, HI, 16 * S, 16>(A, d, e, b, lds, vs, lane);
+        wtri_all<N, S - 1>(A, d, e, b, lds, vs, lane);
+    } else {
+        wtri_phase<N, 0, 15, 8, 16>(A, d, e, b, lds, vs, lane);
+        wtri_phase<N, 0, 7, 2, 8>(A, d, e, b, lds, vs, lane);
+    }
+}
+template <int N, int S, typename R>
+__device__ __forceinline__ void wback_all(double (&G)[DirectW<N>::NS][16], double& hv, double* lds,
+                                          const R& vs, int lane) {
+    constexpr int HI = 16 * S + 15 < N - 1 ? 16 * S + 15 : N - 1;
+    if constexpr (S > 0) {
+        wback_all<N, S - 1>(G, hv, lds, vs, lane);
+        wback_phase<N, S, HI, 16 * S, 16>(G, hv, lds, vs, lane);
+    } else {
+        wback_phase<N, 0, 7, 2, 8>(G, hv, lds, vs, lane);
+        wback_phase<N, 0, 15, 8, 16>(G, hv, lds, vs, lane);
+    }
+}
+
+// row_chain for one 16-column block: columns K.., `own`: the column of the row's diagonal in
+// this block, if 0..15; pa, pb: the previous column (for K = 0 the block's start value).
+template <int K>
+__device__ __forceinline__ void wave_chain(double (&a)[16], const double (&g)[16], double wa,
+                                           double wb, double pa, double pb, int pr, int own) {
+    double ua[4], ub[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const bool o = own == K + k;
+        ua[k] = o ? wa : (K + k == 0 ? pa : 0.0);
+        ub[k] = o ? wb : (K + k == 0 ? pb : 0.0);
+    }
+    constexpr int F = K == 0 ? 1 : 0;
+    if (pr == 0)
+        fmac_chain<0, 4 - F>(ua + F, ub + F, g + K - 1 + F, F ? ua[0] : pa, F ? ub[0] : pb);
+    else
+        fmac_chain<2, 4 - F>(ua + F, ub + F, g + K - 1 + F, F ? ua[0] : pa, F ? ub[0] : pb);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        a[K + k] += ua[k] + ub[k];
+        // summed here: otherwise the additions of all slots and poles are left to the end of
+        // the pass and their operands spill
+        asm volatile("" : "+v"(a[K + k]));
+    }
+    if constexpr (K < 12) wave_chain<K + 4>(a, g, wa, wb, ua[3], ub[3], pr, own);
+}
+
+// sym_direct for the one node of a wavefront (b: element = lane).  lds:
+// DirectW<N>::kDoubles doubles.
+template <int N, bool ROOT, typename R>
+__device__ __forceinline__ bool sym_direct_wave(double (&A)[DirectW<N>::NS][16], double& b,
+                                                double ia, double scale, double* lds, const R& vs,
+                                                int lane) {
+    using D = DirectW<N>;
+    constexpr int NS = D::NS;
+    constexpr int ZS = D::ZS;
+    double* gt = lds;                // [16 poles][ZS] g_j
+    double* zt = gt + D::kTab;       // 1 / gamma_j, then z_jj c (row 15: the solution of X h = b)
+    double* et = zt + D::kTab;       // products of g to the end of j's block, then z_jj c times them
+    double* pb = et + D::kTab;       // [16 poles][4] block products
+    const int g = lane >> 4, r = lane & 15;
+    double d = 0.0, e = 0.0;
+    wtri_all<N, NS - 1>(A, d, e, b, lds, vs, lane);
+    if (g == 0) {
+        d = r == 0 ? A[0][0] : (r == 1 ? A[0][1] : d);
+        e = r == 0 ? A[0][1] : e;
+    }
+    d *= ia;
+    e *= ia;
+    const bool finite = __all(fabs(d) + fabs(e) < 1e300);
+    const float df = (float)d, ef = (float)e;
+    const int cls = pole_class<true>(df * df + 2.0f * ef * ef);
+    const int p0 = kPoleOffset[cls], np = kPoleOffset[cls + 1] - p0;
+#pragma unroll
+    for (int h = 0; h < NS; ++h)
+#pragma unroll
+        for (int k = 0; k < 16; ++k) A[h][k] = 0.0;
+    double hv = 0.0;
+#pragma unroll 1
+    for (int pc = 0; pc < np; pc += 15) {
+        const int pi = pc + r < np && r < 15 ? p0 + pc + r : -1;
+        const double t2 = pi >= 0 ? kSqrtPoles[pi < 0 ? 0 : pi].t2 : 0.0;
+        double cw = pi >= 0 ? kSqrtPoles[pi < 0 ? 0 : pi].c * scale : 0.0;
+        if constexpr (ROOT) cw *= 1.0 + t2;
+        const double base = 1.0 + t2;
+        wave_lds_sync();
+        {
+            // as in sym_direct: 1 / gamma_j, on the lanes of pole 15 y_j / gamma_j
+            double rg = 0.0, y = 0.0, sp = 0.0;
+#pragma unroll 4
+            for (int j = N - 1; j >= 0; --j) {
+                const double ej = j == N - 1 ? 0.0 : lane_value(e, j);
+                const double gj = -ej * rg;
+                y = fma(gj, y, lane_value(b, j));
+                rg = fast_rcp(fma(gj, ej, base + lane_value(d, j)));
+                sp = (j & 15) == 15 ? gj : gj * sp;
+                if (g == 0) {
+                    gt[r * ZS + j] = gj;
+                    zt[r * ZS + j] = r == 15 ? y * rg : rg;
+                    et[r * ZS + j] = sp;
+                    if ((j & 15) == 0) pb[4 * r + (j >> 4)] = sp;
+                }
+            }
+        }
+        wave_lds_sync();
+        if (g == 0) {
+            double z = 0.0, m = 0.0;
+            const double cx = r == 15 ? 1.0 : cw;
+#pragma unroll 4
+            for (int j = 0; j < N; ++j) {
+                const double gj = gt[r * ZS + j];
+                z = fma(m, z, zt[r * ZS + j]);
+                et[r * ZS + j] *= z * cx;
+                zt[r * ZS + j] = z * cx;
+                m = r == 15 ? gj : gj * gj;
+            }
+        }
+        wave_lds_sync();
+        hv = lane < N ? zt[15 * ZS + lane] : 0.0;
+        double gc[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const double v = gt[r * ZS + 16 * (g < NS ? g : 0) + k];
+            gc[k] = 16 * g + k < N ? v : 0.0;
+        }
+        const int left = np - pc < 15 ? np - pc : 15;
+#pragma unroll 1
+        for (int q = 0; q < left; q += 4) {
+#pragma unroll
+            for (int pr = 0; pr < 4; pr += 2) {
+                const int pa = q + pr, pq = q + pr + 1;
+                // row 15 is the solution for b, not a pole (and may hold a NaN of b's)
+                const bool on = pq != 15;
+                const int el = lane < N ? lane : 0;
+                const double wa = zt[pa * ZS + el];
+                const double wq = zt[pq * ZS + el], wb = on ? wq : 0.0;
+#pragma unroll
+                for (int h = 0; h < NS; ++h) {
+                    // block g > h starts from row i's value at the end of its own block
+                    // times the products of the blocks in between
+                    double sa = 0.0, sb = 0.0;
+                    if (h + 1 < NS) {
+                        sa = et[pa * ZS + 16 * h + r];
+                        sb = et[pq * ZS + 16 * h + r];
+                        sb = on ? sb : 0.0;
+#pragma unroll
+                        for (int k = h + 1; k + 1 < NS; ++k) {
+                            sa *= g > k ? pb[4 * pa + k] : 1.0;
+                            sb *= g > k ? pb[4 * pq + k] : 1.0;
+                        }
+                    }
+                    const bool later = h + 1 < NS && g > h;
+                    double pa_ = later ? sa : 0.0, pb_ = later ? sb : 0.0;
+                    // (opaque, so that the sixteen lane masks are formed where they are used
+                    // instead of being kept in 128 scalar registers)
+                    int own = lane - 16 * h;
+                    asm volatile("" : "+v"(own));
+                    wave_chain<0>(A[h], gc, wa, wb, pa_, pb_, pr, own);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const int lo = __builtin_amdgcn_mov_dpp(__double2loint(gc[k]), 0x12C, 0xF, 0xF, true);
+                const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(gc[k]), 0x12C, 0xF, 0xF, true);
+                gc[k] = __hiloint2double(hi, lo);
+            }
+        }
+    }
+    // lower triangle, one slot of rows at a time: rows 16 s + r to LDS, their columns back
+    // to the lanes of group s
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        wave_lds_sync();
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if (g >= s && g < NS) zt[r * ZS + 16 * g + k] = A[s][k];
+        if (g == s) zt[r * ZS + lane] = 0.0;
+        wave_lds_sync();
+#pragma unroll
+        for (int h = s; h < NS; ++h) {
+            double t[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) t[k] = zt[k * ZS + 16 * h + r];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) A[h][k] += g == s ? t[k] : 0.0;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    b = hv;
+    wback_all<N, NS - 1>(A, b, lds, vs, lane);
     return finite;
 }
 

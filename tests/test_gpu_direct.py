@@ -97,3 +97,36 @@ def test_batch_of_both_solvers_equals_each_problem_alone():
         torch.cuda.synchronize()
         for a, s in zip(alone, states):
             np.testing.assert_array_equal(a, host(s))
+
+
+@pytest.mark.parametrize("route,M,nvar,side", [(2, 64, 2, 4), (2, 64, 3, 4), (1, 40, 2, 4),
+                                               (1, 16, 2, 4)])
+def test_nan_observation_stays_at_its_nodes(route, M, nvar, side):
+    """A NaN observation value reaches only the nodes whose local set holds it with a
+    positive weight: all others -- in the same wavefront too, for one and several
+    nodes per wavefront -- keep the clean analysis bit for bit, and no node counts as
+    a failed solve (y^o does not enter the matrix)."""
+    say(f"direct solver: NaN observation, route {route}, M {M}, nvar {nvar}")
+    n = 32
+    rng = np.random.default_rng(5)
+    fe = random_state(rng, M, n, n)
+    pts = np.array([(8 * i + 3, 8 * j + 1) for j in range(side) for i in range(side)], np.int32)
+    d_cut = 8.0 if nvar == 3 else 7.0
+    ctx = binding.Context(n, n, M, 0.55, 0.1, pts, nvar, (0.02,) * nvar, d_cut, 1.05, route=route)
+    outs = []
+    for bad in (False, True):
+        f = ctx.import_canonical(cuda(fe))
+        yf = ctx.observe(f)
+        yo = (yf.mean(dim=0) + 0.01).contiguous()
+        if bad:
+            yo[nvar * 5] = float("nan")
+        ctx.analyze(f, yf, yo)
+        outs.append(host(ctx.export_canonical(f)))
+    ctx.check()
+    ys, xs = np.mgrid[0:n, 0:n]
+    dx = np.minimum(abs(xs - pts[5, 0]), n - abs(xs - pts[5, 0]))
+    dy = np.minimum(abs(ys - pts[5, 1]), n - abs(ys - pts[5, 1]))
+    inside = dx * dx + dy * dy < 4 * d_cut ** 2
+    assert not np.isfinite(outs[1][:, :, pts[5, 1], pts[5, 0]]).any()
+    np.testing.assert_array_equal(outs[0][:, :, ~inside], outs[1][:, :, ~inside])
+    assert np.isfinite(outs[0]).all()
