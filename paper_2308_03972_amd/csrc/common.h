@@ -21,6 +21,13 @@ __host__ __device__ constexpr double w_of(int a) {
     return a == 0 ? 4.0 / 9.0 : (a <= 4 ? 1.0 / 9.0 : 1.0 / 36.0);
 }
 
+// The same for an index known only at run time (c + 1 in two bits each).
+__host__ __device__ __forceinline__ int cx_dyn(int a) { return (int)(0x8949u >> (2 * a) & 3u) - 1; }
+__host__ __device__ __forceinline__ int cy_dyn(int a) { return (int)(0x20895u >> (2 * a) & 3u) - 1; }
+__host__ __device__ __forceinline__ double w_dyn(int a) {
+    return a == 0 ? w_of(0) : (a <= 4 ? w_of(1) : w_of(5));
+}
+
 constexpr int kWave = 64;
 
 // Population storage layout: [node][a][member], node = y * nx + x, members
@@ -88,6 +95,9 @@ struct PopIO<double> {
     __device__ static void store_nt(double* p, int, double v) { __builtin_nontemporal_store(v, p); }
     // the value a store followed by a load gives back
     __device__ static double round(double v, int) { return v; }
+    // the stored element of value v (w: the lattice weight), and its value
+    __device__ static double pack(double v, double) { return v; }
+    __device__ static double unpack(double e, double) { return e; }
 };
 
 template <>
@@ -101,6 +111,8 @@ struct PopIO<float> {
         __builtin_nontemporal_store((float)(v - w_of(a)), p);
     }
     __device__ static double round(double v, int a) { return w_of(a) + (double)(float)(v - w_of(a)); }
+    __device__ static float pack(double v, double w) { return (float)(v - w); }
+    __device__ static double unpack(float e, double w) { return w + (double)e; }
 };
 
 inline size_t state_elem_bytes(int storage) { return storage == kStoreF32Dev ? 4 : 8; }
