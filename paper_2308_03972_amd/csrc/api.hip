@@ -653,16 +653,29 @@ lbmletkf_status lbm_ensemble_step(lbmletkf_ctx* ctx, void* d_f, int32_t nsteps, 
     void* a = d_f;
     void* b = c->fbuf();
     StageTimer all(c, kStageCollide, s, kPerCall, nsteps);
-    // pairs of steps in one launch where the ensemble allows it, a single step
-    // for an odd remainder
+    // several steps per launch where the plan gives them, spread evenly over an even
+    // number of launches (the result then lies in d_f and needs no copy); else pairs of
+    // steps where the ensemble allows it, a single step for an odd remainder
+    const StepPlan plan = step_plan(c->dims, c->storage());
     const bool two = two_step_supported(c->dims, c->storage());
+    int launches = plan.steps > 1 && nsteps > 1 ? (nsteps + plan.steps - 1) / plan.steps : 0;
+    if (launches & 1) ++launches;
     for (int k = 0; k < nsteps;) {
-        const int n = (two && nsteps - k >= 2) ? 2 : 1;
-        StageTimer t(c, kStageCollide, s, kPerLaunch, n);
-        hipError_t e = n == 2 ? launch_stream_collide2(a, b, c->force(), c->dims, c->lbm.tau0,
-                                                       c->lbm.cs, c->lbm.mu, c->storage(), s)
-                              : launch_stream_collide(a, b, c->force(), c->dims, c->lbm.tau0,
-                                                      c->lbm.cs, c->lbm.mu, c->storage(), s);
+        int n = (two && nsteps - k >= 2) ? 2 : 1;
+        hipError_t e;
+        if (launches > 0) {
+            n = (nsteps - k + launches - 1) / launches;
+            --launches;
+            StageTimer t(c, kStageCollide, s, kPerLaunch, n);
+            e = launch_stream_collide_tile(a, b, c->force(), c->dims, c->lbm.tau0, c->lbm.cs,
+                                           c->lbm.mu, c->storage(), s, plan, n);
+        } else {
+            StageTimer t(c, kStageCollide, s, kPerLaunch, n);
+            e = n == 2 ? launch_stream_collide2(a, b, c->force(), c->dims, c->lbm.tau0, c->lbm.cs,
+                                                c->lbm.mu, c->storage(), s)
+                       : launch_stream_collide(a, b, c->force(), c->dims, c->lbm.tau0, c->lbm.cs,
+                                               c->lbm.mu, c->storage(), s);
+        }
         if (e != hipSuccess) return hip_fail(e, "stream_collide");
         std::swap(a, b);
         k += n;
@@ -892,49 +905,58 @@ struct Sweep {
 };
 
 // Steps 1 .. last of the segment that starts at checkpoint t - 1, every state
-// kept; step `steps` (if last == steps) lands in checkpoint t.  Pairs of steps
-// run in one launch that also writes the pair's first state, where the
+// kept; step `steps` (if last == steps) lands in checkpoint t.  Several steps (the plan's,
+// or a pair) run in one launch that also writes the states in between, where the
 // ensemble allows it (the same bits as single steps).
 lbmletkf_status segment_steps(Ctx* c, const Sweep& sw, int t, int steps, int last, double cs,
                               hipStream_t s) {
-    const bool two = two_step_supported(c->dims, c->storage());
-    for (int j = 1; j <= last;) {
+    const StepPlan plan = step_plan(c->dims, c->storage());
+    const int most = plan.steps > 1 ? plan.steps : (two_step_supported(c->dims, c->storage()) ? 2 : 1);
+    int launches = (last + most - 1) / most;
+    for (int j = 1; j <= last; --launches) {
         const void* in = j == 1 ? sw.ckpt(t - 1) : sw.seg(j - 1);
+        const int n = plan.steps > 1 ? (last - j + launches) / launches : std::min(most, last - j + 1);
+        void* out = j + n - 1 == steps ? sw.ckpt_mut(t) : sw.seg(j + n - 1);
+        StageTimer tm(c, kStageCollide, s, kPerLaunch, n);
         hipError_t e;
-        if (two && j + 1 <= last) {
-            void* out = j + 1 == steps ? sw.ckpt_mut(t) : sw.seg(j + 1);
-            StageTimer tm(c, kStageCollide, s, kPerLaunch, 2);
+        if (plan.steps > 1 && n > 1)
+            e = launch_stream_collide_tile(in, out, c->force(), c->dims, c->lbm.tau0, cs, c->lbm.mu,
+                                           c->storage(), s, plan, n, sw.seg(j), sw.sb);
+        else if (n == 2)
             e = launch_stream_collide2(in, out, c->force(), c->dims, c->lbm.tau0, cs, c->lbm.mu,
                                        c->storage(), s, sw.seg(j));
-            j += 2;
-        } else {
-            void* out = j == steps ? sw.ckpt_mut(t) : sw.seg(j);
-            StageTimer tm(c, kStageCollide, s);
+        else
             e = launch_stream_collide(in, out, c->force(), c->dims, c->lbm.tau0, cs, c->lbm.mu,
                                       c->storage(), s);
-            j += 1;
-        }
         if (e != hipSuccess) return hip_fail(e, "stream_collide");
+        j += n;
     }
     return LBMLETKF_OK;
 }
 
 // The whole segment from checkpoint t - 1 to checkpoint t when its
-// intermediate states are not kept: pairs of steps in one launch where the
-// ensemble allows it (the same bits as single steps), a single step for an
-// odd remainder; states in between pass through the segment buffers.
+// intermediate states are not kept: as many steps per launch as the ensemble allows (the
+// same bits as single steps); states in between pass through the segment buffers.
 lbmletkf_status segment_advance(Ctx* c, const Sweep& sw, int t, int steps, double cs,
                                 hipStream_t s) {
-    const bool two = two_step_supported(c->dims, c->storage());
+    const StepPlan plan = step_plan(c->dims, c->storage());
+    const int most = plan.steps > 1 ? plan.steps : (two_step_supported(c->dims, c->storage()) ? 2 : 1);
+    int launches = (steps + most - 1) / most;
     const void* in = sw.ckpt(t - 1);
-    for (int j = 0; j < steps;) {
-        const int n = (two && steps - j >= 2) ? 2 : 1;
+    for (int j = 0; j < steps; --launches) {
+        const int n = plan.steps > 1 ? (steps - j + launches - 1) / launches : std::min(most, steps - j);
         void* out = j + n == steps ? sw.ckpt_mut(t) : sw.seg(j + n);
         StageTimer tm(c, kStageCollide, s, kPerLaunch, n);
-        hipError_t e = n == 2 ? launch_stream_collide2(in, out, c->force(), c->dims, c->lbm.tau0,
-                                                       cs, c->lbm.mu, c->storage(), s)
-                              : launch_stream_collide(in, out, c->force(), c->dims, c->lbm.tau0,
-                                                      cs, c->lbm.mu, c->storage(), s);
+        hipError_t e;
+        if (plan.steps > 1 && n > 1)
+            e = launch_stream_collide_tile(in, out, c->force(), c->dims, c->lbm.tau0, cs, c->lbm.mu,
+                                           c->storage(), s, plan, n);
+        else if (n == 2)
+            e = launch_stream_collide2(in, out, c->force(), c->dims, c->lbm.tau0, cs, c->lbm.mu,
+                                       c->storage(), s);
+        else
+            e = launch_stream_collide(in, out, c->force(), c->dims, c->lbm.tau0, cs, c->lbm.mu,
+                                      c->storage(), s);
         if (e != hipSuccess) return hip_fail(e, "stream_collide");
         in = out;
         j += n;

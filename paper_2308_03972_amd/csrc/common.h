@@ -139,6 +139,18 @@ bool two_step_supported(LbmDims d, int storage);
 hipError_t launch_stream_collide2(const void* fin, void* fout, const double* force, LbmDims d,
                                   double tau0, double cs, double mu, int storage, hipStream_t s,
                                   void* fmid = nullptr);
+// Up to `steps` steps in one launch on regions of `region`^2 nodes and `members` members
+// per block, `items` per thread (any ensemble size); steps = 0: not the faster way.
+struct StepPlan {
+    int steps, region, members, items;
+};
+StepPlan step_plan(LbmDims d, int storage);
+// `steps` <= pl.steps steps; with fmid != NULL the states after steps 1 .. steps - 1 go to
+// fmid, fmid + mid_bytes, ...  Same arithmetic and rounding as single steps.
+hipError_t launch_stream_collide_tile(const void* fin, void* fout, const double* force, LbmDims d,
+                                      double tau0, double cs, double mu, int storage, hipStream_t s,
+                                      const StepPlan& pl, int steps, void* fmid = nullptr,
+                                      size_t mid_bytes = 0);
 // One problem of a batched forecast step: its state buffers (storage layout),
 // force, sizes, relaxation parameters and its first tile in the batch.
 struct LbmTask {

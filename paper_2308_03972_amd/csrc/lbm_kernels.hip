@@ -20,6 +20,7 @@
 // |Pi| = sqrt(Pi_xx^2 + Pi_yy^2 + 2 Pi_xy^2), whose positive root is used.
 // The momentum flux of f^eq is rho/3 I + rho u u, so Pi needs no f^eq.
 #include "common.h"
+#include "device_util.h"
 
 namespace lbmletkf {
 namespace {
@@ -438,6 +439,127 @@ stream_collide2_batch_kernel(const LbmTask* __restrict__ tasks, int ntasks) {
 }
 
 // ---------------------------------------------------------------------------
+// Several steps per launch on square regions of any size and any member count: a block
+// takes MG members of a region of R x R nodes, pulls the first step from HBM and keeps
+// the results in LDS; each further step loses the region's outer ring, and after k steps
+// the inner T x T nodes (T = R - 2 (k - 1)) are written.  For ensembles that the 128-byte
+// member blocks above do not fit, and for problems so small that a step's launch costs
+// more than its work: 72 M bytes per node leave room for regions of 12-24 nodes, so that
+// k = 3-6 steps cost one read of R^2 and one write of T^2 nodes, one launch and k barriers.
+// One thread holds I items (a node, V members) through all steps, LDS is updated in place
+// between two barriers.  Same arithmetic and rounding as single steps, bit for bit.
+// Bound by latency (a launch, one round of loads, k barriers) on small problems and by
+// L2 requests of 32-byte pieces and FP64 issue on large ones (4.0 TB/s of the kernel's own
+// bytes at 400^2 x 24).  Shapes: step_plan below.
+// ---------------------------------------------------------------------------
+template <typename T, int V, int I>
+__global__ __launch_bounds__(1024) void stream_collide_tile_kernel(
+    const T* __restrict__ fin, T* __restrict__ fout, const double* __restrict__ force, int nx,
+    int ny, int members, double tau0, double smag, double mu, int R, int MG, int steps,
+    T* __restrict__ fmid, size_t mid_stride) {
+    extern __shared__ char lds_raw[];
+    T* const mid = reinterpret_cast<T*>(lds_raw);  // [9][R * R][MG]
+    typedef T vec __attribute__((ext_vector_type(V)));
+    const int halo = steps - 1, tile = R - 2 * halo;
+    const int groups = (members + MG - 1) / MG;
+    const int tiles_x = (nx + tile - 1) / tile;
+    const int b = dev::xcd_remap(blockIdx.x, gridDim.x);  // the groups of a tile share lines
+    const int t = b / groups, m0 = (b - t * groups) * MG;
+    const int x0 = (t % tiles_x) * tile, y0 = (t / tiles_x) * tile;
+    const int per = MG / V;  // items per node
+    const int plane = nx * ny, rr = R * R;
+    int rx[I], ry[I], m[I];
+    bool on[I];
+    size_t own[I];
+    double fx[I], fy[I];
+    T f[I][V][9];
+#pragma unroll
+    for (int i = 0; i < I; ++i) {
+        const int it = threadIdx.x + i * blockDim.x;
+        const int node_r = it / per;
+        m[i] = (it - node_r * per) * V;
+        ry[i] = node_r / R;
+        rx[i] = node_r - ry[i] * R;
+        on[i] = node_r < rr && m0 + m[i] < members;
+        int gx = (x0 - halo + rx[i]) % nx, gy = (y0 - halo + ry[i]) % ny;
+        gx = gx < 0 ? gx + nx : gx;
+        gy = gy < 0 ? gy + ny : gy;
+        const int node = gy * nx + gx;
+        own[i] = (size_t)node * 9 * members + m0 + m[i];
+        fx[i] = fy[i] = 0.0;
+        if (!on[i]) continue;
+        if (force) {
+            fx[i] = force[node];
+            fy[i] = force[plane + node];
+        }
+        const PullSlots<const T> src(fin, gx, wrap_dec(gx, nx), wrap_inc(gx, nx), gy,
+                                     wrap_dec(gy, ny), wrap_inc(gy, ny), nx, members, m0 + m[i]);
+#pragma unroll
+        for (int a = 0; a < 9; ++a) {
+            const vec v = *reinterpret_cast<const vec*>(src.at(a));
+#pragma unroll
+            for (int k = 0; k < V; ++k) f[i][k][a] = v[k];
+        }
+    }
+    for (int s = 1;; ++s) {
+        const int lo = s - 1, hi = R - lo;  // this step's nodes
+#pragma unroll
+        for (int i = 0; i < I; ++i) {
+            on[i] = on[i] && rx[i] >= lo && rx[i] < hi && ry[i] >= lo && ry[i] < hi;
+            if (!on[i]) continue;
+#pragma unroll
+            for (int k = 0; k < V; ++k) {
+                if constexpr (sizeof(T) == 8)
+                    collide_node(f[i][k], tau0, smag, fx[i], fy[i], mu);
+                else
+                    collide_node_dev(f[i][k], (float)tau0, (float)smag, (float)fx[i], (float)fy[i],
+                                     (float)mu);
+            }
+            const bool inner = rx[i] >= halo && rx[i] < halo + tile && ry[i] >= halo &&
+                               ry[i] < halo + tile && x0 + rx[i] - halo < nx &&
+                               y0 + ry[i] - halo < ny;
+            T* const dst = s == steps ? fout : (fmid ? fmid + (size_t)(s - 1) * mid_stride : nullptr);
+            if (inner && dst) {
+#pragma unroll
+                for (int a = 0; a < 9; ++a) {
+                    vec v;
+#pragma unroll
+                    for (int k = 0; k < V; ++k) v[k] = f[i][k][a];
+                    *reinterpret_cast<vec*>(dst + own[i] + (uint32_t)a * members) = v;
+                }
+            }
+        }
+        if (s == steps) return;
+        if (s > 1) __syncthreads();  // the previous step's values have been read
+#pragma unroll
+        for (int i = 0; i < I; ++i) {
+            if (!on[i]) continue;
+#pragma unroll
+            for (int a = 0; a < 9; ++a) {
+                vec v;
+#pragma unroll
+                for (int k = 0; k < V; ++k) v[k] = f[i][k][a];
+                *reinterpret_cast<vec*>(mid + ((size_t)a * rr + ry[i] * R + rx[i]) * MG + m[i]) = v;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < I; ++i) {
+            // the next step's nodes: their neighbours are this step's
+            const bool next = on[i] && rx[i] > lo && rx[i] < hi - 1 && ry[i] > lo && ry[i] < hi - 1;
+            if (!next) continue;
+#pragma unroll
+            for (int a = 0; a < 9; ++a) {
+                const vec v = *reinterpret_cast<const vec*>(
+                    mid + ((size_t)a * rr + (ry[i] - cy_of(a)) * R + rx[i] - cx_of(a)) * MG + m[i]);
+#pragma unroll
+                for (int k = 0; k < V; ++k) f[i][k][a] = v[k];
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // conversions between the member-fastest storage and x-fastest fields.  A block takes
 // `tile` consecutive nodes of one lattice row for `mg` members (128 bytes of one
 // population where the ensemble has that many) and all nine populations through an LDS
@@ -626,6 +748,90 @@ hipError_t launch_stream_collide(const void* fin, void* fout, const double* forc
 bool two_step_supported(LbmDims d, int storage) {
     // FP64: blocks of 16 members; FP32 deviations: 32 (or 16) members as pairs
     return d.members % kTwoMG == 0;
+}
+
+// The tiled multi-step launch of an ensemble, or k = 0 where pairs of steps on 128-byte
+// member blocks are as fast or faster.  Chosen from a sweep of every (members per block,
+// region, steps, items per thread) at grids 24^2 .. 400^2 and 1 .. 64 members; P =
+// node-members.  us per step, FP64 unless noted (single step / pair / this):
+//   256^2 x 1 11.2 / - / 2.6, 48^2 x 8 5.2 / - / 1.8, 150 x 97 x 20 10.6 / - / 7.3,
+//   256^2 x 24 44 / - / 28, 400^2 x 24 FP32 76 / - / 36;
+//   16 | M: 24^2 x 16 3.9 / 3.0 / 1.6, 48^2 x 32 4.8 / 3.5 / 2.9, but 96^2 x 16 5.8 / 3.7 / 3.7
+//   and 160^2 x 32 20.4 / 15.3 / 16: pairs from P = 1e5 on.  FP32 with 16 members (64-byte
+//   member blocks as pairs) stays here at any size: 256^2 x 16 17.8 / 14.2 / 10.6.
+// Small problems take few members and long chains (more blocks, fewer launches); large
+// ones four members (32 bytes, eight in FP32) and k = 3, where a longer chain's halo costs
+// more than it saves.
+StepPlan step_plan(LbmDims d, int storage) {
+    const double P = (double)d.nx * d.ny * d.members;
+    const int M = d.members;
+    const bool pairs = members_per_thread((int)state_elem_bytes(storage), M) == 2;
+    if (M % kTwoMG == 0 && P > 1e5 && !(pairs && M == 16)) return {0, 0, 0, 0};
+    auto balanced = [&](int most) { return (M + (M + most - 1) / most - 1) / ((M + most - 1) / most); };
+    if (pairs) {
+        if (M == 2) return P <= 1e5 ? StepPlan{6, 16, 2, 1} : StepPlan{4, 22, 2, 1};
+        if (P <= 2e4) return {6, 16, 2, 1};
+        if (P <= 6.4e4) return {5, 16, 4, 1};
+        if (P <= 1e5) return {4, 16, 4, 1};
+        if (M % 8 == 0 && P <= 9e5) return {P <= 2e5 ? 4 : 3, 16, 8, 1};
+        return {4, 22, 4, 1};
+    }
+    if (P <= 1e4 || (M == 1 && P <= 2e4)) return {6, 16, 1, 1};
+    if (M == 1) return P <= 1e5 ? StepPlan{5, 24, 1, 1} : StepPlan{4, 22, 1, 1};
+    if (P <= 3.2e4 || (M <= 3 && P <= 6.4e4)) return {5, 16, M == 3 ? 3 : 2, 1};
+    if (M <= 3) return {4, M == 2 ? 22 : 16, M, 1};
+    const int mg = balanced(4);
+    if (P <= 6.4e4) return {5, 16, mg, 1};
+    if (P <= 1e5) return {4, 16, mg, 1};
+    return {3, 16, mg, P <= 2.2e5 ? 1 : 2};
+}
+
+namespace {
+template <typename T, int V, int I>
+hipError_t launch_tile_t(const void* fin, void* fout, const double* force, LbmDims d, double tau0,
+                         double smag, double mu, hipStream_t s, const StepPlan& pl, int steps,
+                         void* fmid, size_t mid_bytes) {
+    const int tile = pl.region - 2 * (steps - 1);
+    const int blocks = ((d.nx + tile - 1) / tile) * ((d.ny + tile - 1) / tile) *
+                       ((d.members + pl.members - 1) / pl.members);
+    const int items = pl.region * pl.region * (pl.members / V);
+    const int threads = ((items + I - 1) / I + kWave - 1) / kWave * kWave;
+    const size_t lds = (size_t)9 * pl.region * pl.region * pl.members * sizeof(T);
+    constexpr size_t kMostLds = 80 * 1024;  // every plan's region: two blocks per CU
+    if (tile < 1 || threads > 1024 || lds > kMostLds || pl.members % V) return hipErrorInvalidValue;
+    static bool attr = false;
+    if (!attr) {
+        hipError_t e = hipFuncSetAttribute(
+            reinterpret_cast<const void*>(stream_collide_tile_kernel<T, V, I>),
+            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMostLds);
+        if (e != hipSuccess) return e;
+        attr = true;
+    }
+    stream_collide_tile_kernel<T, V, I><<<blocks, threads, lds, s>>>(
+        (const T*)fin, (T*)fout, force, d.nx, d.ny, d.members, tau0, smag, mu, pl.region, pl.members,
+        steps, (T*)fmid, mid_bytes / sizeof(T));
+    return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_stream_collide_tile(const void* fin, void* fout, const double* force, LbmDims d,
+                                      double tau0, double cs, double mu, int storage, hipStream_t s,
+                                      const StepPlan& pl, int steps, void* fmid,
+                                      size_t mid_bytes) {
+    if (pl.steps < 1 || steps < 1 || steps > pl.steps) return hipErrorInvalidValue;
+    const double smag = 18.0 * sqrt(2.0) * cs * cs;
+    if (storage != kStoreF32Dev)
+        return pl.items == 1 ? launch_tile_t<double, 1, 1>(fin, fout, force, d, tau0, smag, mu, s,
+                                                           pl, steps, fmid, mid_bytes)
+                             : launch_tile_t<double, 1, 2>(fin, fout, force, d, tau0, smag, mu, s,
+                                                           pl, steps, fmid, mid_bytes);
+    if (members_per_thread(4, d.members) == 2)
+        return launch_tile_t<float, 2, 1>(fin, fout, force, d, tau0, smag, mu, s, pl, steps, fmid,
+                                          mid_bytes);
+    return pl.items == 1 ? launch_tile_t<float, 1, 1>(fin, fout, force, d, tau0, smag, mu, s, pl,
+                                                      steps, fmid, mid_bytes)
+                         : launch_tile_t<float, 1, 2>(fin, fout, force, d, tau0, smag, mu, s, pl,
+                                                      steps, fmid, mid_bytes);
 }
 
 hipError_t launch_stream_collide2(const void* fin, void* fout, const double* force, LbmDims d,
