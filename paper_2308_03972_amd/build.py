@@ -13,8 +13,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbmletkf.so")
 SOURCES = ["api.hip", "lbm_kernels.hip", "letkf_kernels.hip", "letkf_obs.hip",
-           "letkf_direct.hip", "adjoint.hip",
-           "spectrum.hip"]
+           "letkf_direct.hip", "letkf_apply.hip", "adjoint.hip", "spectrum.hip"]
 ARCH = os.environ.get("LBMLETKF_ARCH", "gfx950")
 
 

@@ -1182,7 +1182,9 @@ struct BatchGroup {
     int stream; // 0: the launch stream, k > 0: side stream k - 1
     int4* eig_waves = nullptr;
     int n_eig = 0;
-    int2* waves = nullptr;  // apply waves (observation route) or node waves (ensemble route)
+    int2* apply_waves = nullptr;        // observation route: the update's wave list and
+    int n_apply[4] = {0, 0, 0, 0};      // its entries per class of 16 members
+    int2* waves = nullptr;  // ensemble route
     int n_waves = 0;
     int* nodes = nullptr;
     double* gbuf = nullptr;
@@ -1207,7 +1209,7 @@ struct Batch {
     std::vector<size_t> yo_off;
     char* gbase = nullptr;  // group region
     size_t gcap = 0;
-    int* d_queue = nullptr;  // [16 per group] work-queue counters (analysis_queue = 1)
+    int* d_queue = nullptr;  // [kGroupCounters per group] work-queue counters (analysis_queue = 1)
     std::vector<BatchGroup> groups;
     int ntiles = 0;
     int nblocks2 = 0;  // blocks of a batched two-step launch
@@ -1226,9 +1228,9 @@ struct BatchLayout {
     size_t params, tasks, yo, queue, groups, total, group_bytes;
 };
 
-// Work-queue counters of the batched analysis: 16 per group, at most one group
-// per (route, solver, eigenproblem size <= 64).
-constexpr int kQueueInts = 16 * 4 * 65;
+// Work-queue counters of the batched analysis: at most one group per (route, solver,
+// eigenproblem size <= 64).
+constexpr int kQueueInts = kGroupCounters * 4 * 65;
 
 BatchLayout batch_layout(const std::vector<Ctx*>& ctx) {
     BatchLayout L{};
@@ -1346,7 +1348,7 @@ lbmletkf_status batch_groups(Batch* b, hipStream_t s) {
         return b->gbase + at;
     };
     std::vector<std::vector<int4>> host_eig;
-    std::vector<std::vector<int2>> host_waves;
+    std::vector<std::vector<int2>> host_apply, host_waves;
     struct NodeCopy { int* dst; const int* src; size_t count; };
     std::vector<NodeCopy> node_copies;  // issued once the layout is known to fit
     hipError_t e = hipSuccess;
@@ -1362,24 +1364,32 @@ lbmletkf_status batch_groups(Batch* b, hipStream_t s) {
             for (const Range& r : obs[key]) total += r.count;
             grp.nodes = reinterpret_cast<int*>(take((size_t)total * sizeof(int)));
             std::vector<int4> ew;
-            std::vector<int2> aw;
+            std::vector<int2> aw[4];
             const int segs = obs_segments(sz, direct);
+            const int asegs = apply_on_matrix_cores(b->storage, b->mfma_transform, sz) ? 1 : 4;
             int base = 0;
             for (const Range& r : obs[key]) {
                 node_copies.push_back({grp.nodes + base, b->ctx[r.k]->nodes() + r.offset,
                                        (size_t)r.count});
                 for (int i = 0; i < r.count; i += segs) ew.push_back(make_int4(r.k, base + i, base + r.count, 0));
-                for (int i = 0; i < r.count; ++i) aw.push_back(make_int2(r.k, base + i));
+                for (int i = 0; i < r.count; i += asegs)
+                    aw[(b->ctx[r.k]->dims.members - 1) / 16].push_back(
+                        make_int2(4 * r.k + std::min(asegs, r.count - i) - 1, base + i));
                 grp.cost += (double)r.count * obs_node_cost(sz);
                 base += r.count;
             }
             grp.n_eig = (int)ew.size();
-            grp.n_waves = (int)aw.size();
+            std::vector<int2> all;
+            for (int m = 0; m < 4; ++m) {
+                grp.n_apply[m] = (int)aw[m].size();
+                all.insert(all.end(), aw[m].begin(), aw[m].end());
+            }
             grp.eig_waves = reinterpret_cast<int4*>(take(ew.size() * sizeof(int4)));
-            grp.waves = reinterpret_cast<int2*>(take(aw.size() * sizeof(int2)));
+            grp.apply_waves = reinterpret_cast<int2*>(take(all.size() * sizeof(int2)));
             grp.gbuf = reinterpret_cast<double*>(take(obs_gbuf_doubles(sz, total) * sizeof(double)));
             host_eig.push_back(std::move(ew));
-            host_waves.push_back(std::move(aw));
+            host_apply.push_back(std::move(all));
+            host_waves.emplace_back();
             b->groups.push_back(grp);
         }
         if (!ens[key].empty()) {
@@ -1398,12 +1408,13 @@ lbmletkf_status batch_groups(Batch* b, hipStream_t s) {
             grp.n_waves = (int)w.size();
             grp.waves = reinterpret_cast<int2*>(take(w.size() * sizeof(int2)));
             host_eig.emplace_back();
+            host_apply.emplace_back();
             host_waves.push_back(std::move(w));
             b->groups.push_back(grp);
         }
     }
     if (off > b->gcap) return fail(LBMLETKF_EWORKSPACE, "batch workspace too small for its groups");
-    if (16 * b->groups.size() > (size_t)kQueueInts)
+    if (kGroupCounters * b->groups.size() > (size_t)kQueueInts)
         return fail(LBMLETKF_EUNSUPPORTED, "more analysis groups than work-queue counters");
     for (const NodeCopy& nc : node_copies) {
         e = hipMemcpyAsync(nc.dst, nc.src, nc.count * sizeof(int), hipMemcpyDeviceToDevice, s);
@@ -1414,6 +1425,9 @@ lbmletkf_status batch_groups(Batch* b, hipStream_t s) {
         if (!host_eig[i].empty())
             e = hipMemcpyAsync(grp.eig_waves, host_eig[i].data(), host_eig[i].size() * sizeof(int4),
                                hipMemcpyHostToDevice, s);
+        if (e == hipSuccess && !host_apply[i].empty())
+            e = hipMemcpyAsync(grp.apply_waves, host_apply[i].data(),
+                               host_apply[i].size() * sizeof(int2), hipMemcpyHostToDevice, s);
         if (e == hipSuccess && !host_waves[i].empty())
             e = hipMemcpyAsync(grp.waves, host_waves[i].data(), host_waves[i].size() * sizeof(int2),
                                hipMemcpyHostToDevice, s);
@@ -1448,23 +1462,29 @@ hipError_t batch_analysis(Batch* b, const AnalysisParams* params, hipStream_t s)
     for (const BatchGroup& grp : b->groups)
         if (grp.stream > 0) used[grp.stream - 1] = true;
     const bool queue = b->cfg.analysis_queue == 1;
-    hipError_t e = queue ? launch_zero_ints(b->d_queue, 16 * (int)b->groups.size(), s) : hipSuccess;
+    hipError_t e = queue ? launch_zero_ints(b->d_queue, kGroupCounters * (int)b->groups.size(), s) : hipSuccess;
     if (e == hipSuccess) e = hipEventRecord(b->fork, s);
     for (int k = 0; k < Batch::kSide && e == hipSuccess; ++k)
         if (used[k]) e = hipStreamWaitEvent(b->side[k], b->fork, 0);
     for (const BatchGroup& grp : b->groups) {
         if (e != hipSuccess) break;
         hipStream_t sk = grp.stream == 0 ? s : b->side[grp.stream - 1];
-        if (grp.route == LBMLETKF_ROUTE_OBSERVATION && queue)
-            e = launch_analysis_obs_batch_queue(params, grp.eig_waves, grp.n_eig, grp.waves,
-                                                grp.n_waves, grp.nodes, grp.n, grp.gbuf,
-                                                b->storage, b->mfma_transform, grp.direct,
-                                                b->d_queue + 16 * (&grp - b->groups.data()), sk);
-        else if (grp.route == LBMLETKF_ROUTE_OBSERVATION)
-            e = launch_analysis_obs_batch(params, grp.eig_waves, grp.n_eig, grp.waves, grp.n_waves,
-                                          grp.nodes, grp.n, grp.gbuf, b->storage,
-                                          b->mfma_transform, grp.direct, sk);
-        else
+        if (grp.route == LBMLETKF_ROUTE_OBSERVATION) {
+            ObsBatchLaunch l{};
+            l.d_params = params;
+            l.eig_waves = grp.eig_waves;
+            l.apply_waves = grp.apply_waves;
+            l.nodes = grp.nodes;
+            l.gbuf = grp.gbuf;
+            l.n_eig = grp.n_eig;
+            for (int m = 0; m < 4; ++m) l.n_apply[m] = grp.n_apply[m];
+            l.n = grp.n;
+            l.storage = b->storage;
+            l.mfma_transform = b->mfma_transform;
+            l.direct = grp.direct;
+            l.counters = queue ? b->d_queue + kGroupCounters * (&grp - b->groups.data()) : nullptr;
+            e = launch_analysis_obs_batch(l, sk);
+        } else
             e = launch_analysis_ens_batch(params, grp.waves, grp.n_waves, grp.n, grp.nz_max,
                                           b->storage, grp.direct, sk);
     }

@@ -258,22 +258,44 @@ hipError_t launch_eig_direct_batch(const AnalysisParams* d_params, const int4* d
 hipError_t launch_ens_direct(const AnalysisParams& p, int n, hipStream_t s);
 hipError_t launch_ens_direct_batch(const AnalysisParams* d_params, const int2* d_waves, int nwaves,
                                    int n, int storage, hipStream_t s);
+// Whether the update of a group runs on the matrix cores (one node per wavefront) or as
+// launch_apply_rows (four).
+bool apply_on_matrix_cores(int storage, bool mfma_transform, int n);
+// One launch of the update from G and h (size n, gbuf as above): of `count` nodes of one
+// problem (p, waves = NULL), or of the entries waves[0 .. count) = (4 problem + items - 1,
+// first item), directly or (counters != NULL) from a queue; members: the most members
+// of a problem among them.
+struct ApplyLaunch {
+    const AnalysisParams* p;         // host, one problem
+    const AnalysisParams* d_params;  // device, batched
+    const int2* waves;
+    const int* nodes;
+    const double* gbuf;
+    int count, n, members, storage;
+    int* counters;
+};
+hipError_t launch_apply_rows(const ApplyLaunch& l, hipStream_t s);
 // Batched observation route for one eigenproblem size n over many problems:
-// eigen wavefront w handles eig_waves[w] = (problem, first item, end of that
-// problem's items, -); apply wavefront w handles apply_waves[w] = (problem, item);
-// items index the shared node list and G buffer; d_params[problem] is that
-// problem's AnalysisParams; direct: direct_solver() of every problem of the group.
-hipError_t launch_analysis_obs_batch(const AnalysisParams* d_params, const int4* d_eig_waves,
-                                     int n_eig, const int2* d_apply_waves, int n_apply,
-                                     const int* d_nodes, int n, double* gbuf, int storage,
-                                     bool mfma_transform, bool direct, hipStream_t s);
-// The same with persistent launches that take the wave lists' entries from
-// queues: counters[0..7] (eigen) and counters[8..15] (apply), zero on entry.
-hipError_t launch_analysis_obs_batch_queue(const AnalysisParams* d_params, const int4* d_eig_waves,
-                                           int n_eig, const int2* d_apply_waves, int n_apply,
-                                           const int* d_nodes, int n, double* gbuf, int storage,
-                                           bool mfma_transform, bool direct, int* counters,
-                                           hipStream_t s);
+// solver wavefront w handles eig_waves[w] = (problem, first item, end of that
+// problem's items, -), obs_segments(n, direct) items each; the update's wave list holds
+// (4 problem + items - 1, first item) for one item (matrix cores) or up to four each, the
+// n_apply[k] entries of problems with 16 k + 1 .. 16 (k + 1) members in order of k; items
+// index the shared node list and G buffer; d_params[problem] is that problem's AnalysisParams; direct: direct_solver()
+// of every problem of the group.  counters != NULL: persistent launches that take the
+// wave lists' entries from queues, counters[0 .. 7] (solver) and [8 (k + 1) .. 8 (k + 1) + 7]
+// (update of class k), zero on entry.
+constexpr int kGroupCounters = 40;
+struct ObsBatchLaunch {
+    const AnalysisParams* d_params;
+    const int4* eig_waves;
+    const int2* apply_waves;
+    const int* nodes;
+    double* gbuf;
+    int n_eig, n_apply[4], n, storage;
+    bool mfma_transform, direct;
+    int* counters;
+};
+hipError_t launch_analysis_obs_batch(const ObsBatchLaunch& b, hipStream_t s);
 // Zero n ints with a kernel (capturable in a graph, unlike hipMemsetAsync).
 hipError_t launch_zero_ints(int* v, int n, hipStream_t s);
 // Blocks of a persistent launch: enough wavefronts to fill every CU (16 per CU,

@@ -525,12 +525,88 @@ __device__ __forceinline__ void local_obs(const AnalysisParams& p, int node, int
     *w = 0.0;
     if (d) *d = 0.0;
     if (j >= p.nvar * p.lmax) return;
-    const int slot = j / p.nvar, var = j - slot * p.nvar;
+    const int slot = p.nvar == 2 ? j >> 1 : j / 3, var = j - slot * p.nvar;
     const int k = p.loc_pt[(size_t)node * p.lmax + slot];
     if (k < 0) return;
     *q = k * p.nvar + var;
     *w = sqrt(p.loc_g[(size_t)node * p.lmax + slot] * p.rinv[var]);
     if (d) *d = *w * p.dvec[*q];
+}
+
+// Sum over each row of 16 lanes.
+__device__ __forceinline__ double group_sum16(double v) { return group_reduce<16>(v, OpAdd()); }
+
+// The local observations of a node held by a row of 16 lanes (lane r: entries r + 16 h):
+// an entry of weight 0 -- missing, or on the rim of the localization -- takes the index of
+// one that counts.  Returns whether the node has any such (else all indices become 0).
+template <int NS>
+__device__ __forceinline__ bool weighted_indices(int (&q)[NS], const double (&w)[NS], int lane) {
+    int qf = 0;
+    bool any = false;
+#pragma unroll
+    for (int h = NS - 1; h >= 0; --h) {
+        const int mask = (int)(__ballot(w[h] != 0.0) >> (lane & 48)) & 0xffff;
+        const int first = mask ? __ffs(mask) - 1 : 0;
+        const int v = __builtin_amdgcn_ds_bpermute(((lane & 48) + first) * 4, q[h]);
+        qf = mask ? v : qf;
+        any = any || mask != 0;
+    }
+#pragma unroll
+    for (int h = 0; h < NS; ++h) q[h] = w[h] == 0.0 ? qf : q[h];
+    return any;
+}
+
+// node_diag_record for a node held by a row of 16 lanes, members r + 16 h.
+template <int NS>
+__device__ __forceinline__ void row_diag_record(const double (&f)[NS][9], const bool (&mem)[NS],
+                                                int M, int node, int plane, const double* truth_uv,
+                                                double* out, bool here, int r) {
+    double u[NS], v[NS];
+    double su = 0.0, sv = 0.0, bad = 0.0, rmin = INFINITY, rmax = -INFINITY;
+#pragma unroll
+    for (int h = 0; h < NS; ++h) {
+        u[h] = v[h] = 0.0;
+        if (mem[h]) {
+            double rho = 0.0, jx = 0.0, jy = 0.0;
+#pragma unroll
+            for (int a = 0; a < 9; ++a) {
+                rho += f[h][a];
+                jx += cx_of(a) * f[h][a];
+                jy += cy_of(a) * f[h][a];
+            }
+            const double ri = 1.0 / rho;
+            u[h] = jx * ri;
+            v[h] = jy * ri;
+            if (!isfinite(rho) || !isfinite(u[h]) || !isfinite(v[h])) bad += 1.0;
+            rmin = fmin(rmin, rho);
+            rmax = fmax(rmax, rho);
+        }
+        su += u[h];
+        sv += v[h];
+    }
+    const double ub = group_sum16(su) / M, vb = group_sum16(sv) / M;
+    double s2 = 0.0;
+#pragma unroll
+    for (int h = 0; h < NS; ++h) {
+        const double du = mem[h] ? u[h] - ub : 0.0, dv = mem[h] ? v[h] - vb : 0.0;
+        s2 += du * du + dv * dv;
+    }
+    s2 = group_sum16(s2);
+    bad = group_sum16(bad);
+    rmin = group_reduce<16>(rmin, OpMin());
+    rmax = group_reduce<16>(rmax, OpMax());
+    if (here && r == 0) {
+        double err2 = 0.0;
+        if (truth_uv) {
+            const double du = ub - truth_uv[node], dv = vb - truth_uv[plane + node];
+            err2 = du * du + dv * dv;
+        }
+        out[0] = err2;
+        out[1] = M > 1 ? s2 / (M - 1) : 0.0;
+        out[2] = bad;
+        out[3] = rmin;
+        out[4] = rmax;
+    }
 }
 
 // Work-queue form of the batched kernels: a persistent grid whose blocks take

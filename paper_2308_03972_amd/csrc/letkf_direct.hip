@@ -30,9 +30,9 @@ constexpr bool kRows16 = N <= 32;  // four nodes per wavefront
 // ---------------------------------------------------------------------------
 // observation route
 // ---------------------------------------------------------------------------
-// An observation of weight 0 (or a missing one) takes the index of one that counts, so
-// that the products with K meet no other node's values; a node without any reads
-// (finite) localization weights in place of K.
+// (An observation without weight takes the index of one that counts, so that the products
+// with K meet no other node's values; a node without any reads finite localization
+// weights in place of K.)
 
 // Four nodes nodes[item0 + 0 .. 3] (item < end) of one problem.
 template <int N>
@@ -53,16 +53,10 @@ __device__ __forceinline__ void direct_body(const AnalysisParams p, const int* n
         w[h] = b[h] = 0.0;
         if (valid && r + 16 * h < N) local_obs(p, node, r + 16 * h, &q[h], &w[h], &b[h]);
     }
-    const unsigned long long on = __ballot(w[0] != 0.0);
-    const int mask = (int)(on >> (lane & 48)) & 0xffff;
-    const int first = mask ? __ffs(mask) - 1 : 0;
-    const int qf = __builtin_amdgcn_ds_bpermute(((lane & 48) + first) * 4, q[0]);
+    const bool any = weighted_indices<NS>(q, w, lane);
     const double* krow[NS];
 #pragma unroll
-    for (int h = 0; h < NS; ++h) {
-        if (w[h] == 0.0) q[h] = mask ? qf : 0;
-        krow[h] = mask ? p.K + (size_t)q[h] * p.nobs : p.loc_g;
-    }
+    for (int h = 0; h < NS; ++h) krow[h] = any ? p.K + (size_t)q[h] * p.nobs : p.loc_g;
     // S = diag(w) K diag(w): all loads in flight together, then the weights
     double A[NS][N];
     auto load = [&](auto self, auto J) -> void {
@@ -217,58 +211,6 @@ void analysis_direct_queue_kernel(const AnalysisParams* P, const int4* waves, in
 // ---------------------------------------------------------------------------
 // ensemble route
 // ---------------------------------------------------------------------------
-// node_diag_record for a node held by a row of 16 lanes, members r + 16 h.
-template <int NS>
-__device__ __forceinline__ void row_diag_record(const double (&f)[NS][9], const bool (&mem)[NS],
-                                                int M, int node, int plane, const double* truth_uv,
-                                                double* out, bool here, int r) {
-    double u[NS], v[NS];
-    double su = 0.0, sv = 0.0, bad = 0.0, rmin = INFINITY, rmax = -INFINITY;
-#pragma unroll
-    for (int h = 0; h < NS; ++h) {
-        u[h] = v[h] = 0.0;
-        if (mem[h]) {
-            double rho = 0.0, jx = 0.0, jy = 0.0;
-#pragma unroll
-            for (int a = 0; a < 9; ++a) {
-                rho += f[h][a];
-                jx += cx_of(a) * f[h][a];
-                jy += cy_of(a) * f[h][a];
-            }
-            u[h] = jx / rho;
-            v[h] = jy / rho;
-            if (!isfinite(rho) || !isfinite(u[h]) || !isfinite(v[h])) bad += 1.0;
-            rmin = fmin(rmin, rho);
-            rmax = fmax(rmax, rho);
-        }
-        su += u[h];
-        sv += v[h];
-    }
-    const double ub = row_sum(su) / M, vb = row_sum(sv) / M;
-    double s2 = 0.0;
-#pragma unroll
-    for (int h = 0; h < NS; ++h) {
-        const double du = mem[h] ? u[h] - ub : 0.0, dv = mem[h] ? v[h] - vb : 0.0;
-        s2 += du * du + dv * dv;
-    }
-    s2 = row_sum(s2);
-    bad = row_sum(bad);
-    rmin = group_reduce<16>(rmin, OpMin());
-    rmax = group_reduce<16>(rmax, OpMax());
-    if (here && r == 0) {
-        double err2 = 0.0;
-        if (truth_uv) {
-            const double du = ub - truth_uv[node], dv = vb - truth_uv[plane + node];
-            err2 = du * du + dv * dv;
-        }
-        out[0] = err2;
-        out[1] = M > 1 ? s2 / (M - 1) : 0.0;
-        out[2] = bad;
-        out[3] = rmin;
-        out[4] = rmax;
-    }
-}
-
 // Nodes node0 .. node0 + 3 (those < nx * ny), M <= N <= 32 members, lane r of a row =
 // members r and r + 16.
 template <int N, typename T>

@@ -17,8 +17,8 @@
 //     buffer: without iterating (letkf_direct.hip), or, when the caller lowered the
 //     Jacobi sweep cap, analysis_eig_kernel<N> here, 64/N nodes per wavefront (a segment
 //     of N lanes per node): local observations, S, the Jacobi eigensolver, G and h;
-//   analysis_apply_kernel   one node per wavefront, lane = member: x_bar, dX,
-//     B, B G, B h and the update of the nine populations.
+//   the update of the nine populations (letkf_apply.hip; with the matrix-core transform
+//     of the precision form analysis_apply_mfma_kernel here).
 // Splitting keeps the register- and LDS-heavy solver apart from the
 // memory-bound state pass, so each runs at its own occupancy.
 #include "common.h"
@@ -454,174 +454,10 @@ hipError_t allow_lds(K kernel, size_t bytes, bool* done) {
     return e;
 }
 
-// ---------------------------------------------------------------------------
-// apply part: one node per wavefront, lane = member
-// ---------------------------------------------------------------------------
 __host__ __device__ inline int apply_lds_doubles(int n) {
     // G and h, dX [9][64], B [9][n], C [n][10], sw [n], mean increment [9],
     // x_bar [9], q [n]
     return n * n + n + 9 * 64 + 9 * n + 10 * n + n + 9 + 9 + (n + 1) / 2;
-}
-
-// One wavefront: node nodes[item] of one problem, lane = member.
-template <int N, typename T>
-__device__ __forceinline__ void apply_body(const AnalysisParams& p, const int* nodes, int item,
-                                           const double* __restrict__ gin) {
-    constexpr int n = N;
-    constexpr int groups = kWave / N;                  // member groups in B
-    constexpr int kChunk = (kWave + groups - 1) / groups;
-    T* __restrict__ fs = reinterpret_cast<T*>(p.f);
-    extern __shared__ double lds[];
-    double* Gs = lds;                                  // [n][n] as stored: (k, j) = G_jk
-    double* hs = Gs + n * n;                           // [n]
-    double* dxs = hs + n;                              // [9][64]
-    double* Bs = dxs + 9 * 64;                         // [9][n]
-    double* Cs = Bs + 9 * n;                           // [n][10]
-    double* sw = Cs + 10 * n;                          // [n]
-    double* dmv = sw + n;                              // [9]
-    double* xbv = dmv + 9;                             // [9]
-    int* qx = reinterpret_cast<int*>(xbv + 9);         // [n]
-
-    const int lane = threadIdx.x;
-    const int node = nodes[item];
-    const int nx = p.nx, ny = p.ny, M = p.members;
-    const bool mem = lane < M;
-    const int x = node % nx, y = node / nx;
-
-    // independent loads first, in one block so that they are all in flight
-    // before the first use: the nine populations, G and h (the last pass
-    // clamps its index), this lane's local observation
-    constexpr int kGn = n * n + n;
-    constexpr int kGp = (kGn + kWave - 1) / kWave;
-    double dx[9];
-    const int ml = mem ? lane : 0;  // a lane past the ensemble reads member 0 and discards it
-#pragma unroll
-    for (int a = 0; a < 9; ++a)
-        dx[a] = PopIO<T>::load(fs + slot(src_node(x, y, a, nx, ny), a, ml, M), a);
-#pragma unroll
-    for (int a = 0; a < 9; ++a) dx[a] = mem ? dx[a] : 0.0;
-    const double* g = gin + (size_t)item * kGn;
-    double gv[kGp];
-#pragma unroll
-    for (int u = 0; u < kGp; ++u) gv[u] = g[min(lane + u * kWave, kGn - 1)];
-    int qj = 0;
-    double wj = 0.0;
-    if (lane < n) local_obs(p, node, lane, &qj, &wj, nullptr);
-    if (p.diag_node)
-        node_diag_record(dx, mem, M, node, nx * ny, p.truth_uv,
-                         p.diag_node + (size_t)node * kDiagFieldCount);
-#pragma unroll
-    for (int u = 0; u < kGp; ++u)
-        if (lane + u * kWave < kGn) Gs[lane + u * kWave] = gv[u];
-    if (lane < n) {
-        qx[lane] = qj;
-        sw[lane] = wj;
-    }
-    wave_lds_sync();
-    // x_bar and dX of the nine populations
-#pragma unroll
-    for (int a = 0; a < 9; ++a) {
-        const double xbar = wave_sum(dx[a]) / M;
-        dx[a] = mem ? dx[a] - xbar : 0.0;
-        dxs[a * 64 + lane] = dx[a];
-        if (lane == 0) xbv[a] = xbar;
-    }
-    wave_lds_sync();
-    // B[a][j] = w_j sum_m dX_a(m) dY[q_j][m]: lane (group, j) sums a member
-    // range (its dY values loaded together first), the groups are combined in a
-    // fixed order
-    const int gi = lane / n, j = lane - gi * n;
-    const bool gact = gi < groups;
-    double b[9];
-#pragma unroll
-    for (int a = 0; a < 9; ++a) b[a] = 0.0;
-    if (gact && sw[j] != 0.0) {
-        const int mchunk = (M + groups - 1) / groups;
-        const int m0 = gi * mchunk;
-        const int m1 = min(M, m0 + mchunk);
-        const double* yrow = p.dY + (size_t)qx[j] * M;
-        double yv[kChunk];
-#pragma unroll
-        for (int t = 0; t < kChunk; ++t) yv[t] = m0 + t < m1 ? yrow[m0 + t] : 0.0;
-#pragma unroll
-        for (int t = 0; t < kChunk; ++t) {
-            const int m = m0 + t < m1 ? m0 + t : m0;
-#pragma unroll
-            for (int a = 0; a < 9; ++a) b[a] += dxs[a * 64 + m] * yv[t];
-        }
-    }
-    for (int gg = 1; gg < groups; ++gg) {
-        const int src = gact ? j + gg * n : lane;
-#pragma unroll
-        for (int a = 0; a < 9; ++a) {
-            const double v = __shfl(b[a], src, kWave);
-            b[a] += (gi == 0) ? v : 0.0;
-        }
-    }
-    if (lane < n) {
-        const double wj = sw[lane];
-#pragma unroll
-        for (int a = 0; a < 9; ++a) Bs[a * n + lane] = b[a] * wj;
-    }
-    wave_lds_sync();
-    // C = B G ([j][a]) and the mean increment B h
-    for (int jj = lane; jj < n; jj += kWave) {
-        double c[9];
-#pragma unroll
-        for (int a = 0; a < 9; ++a) c[a] = 0.0;
-        for (int k = 0; k < n; ++k) {
-            const double gkj = Gs[k * n + jj];
-#pragma unroll
-            for (int a = 0; a < 9; ++a) c[a] += Bs[a * n + k] * gkj;
-        }
-#pragma unroll
-        for (int a = 0; a < 9; ++a) Cs[jj * 10 + a] = c[a];
-        Cs[jj * 10 + 9] = 0.0;
-    }
-    if (lane < 9) {
-        double d = 0.0;
-        for (int k = 0; k < n; ++k) d += Bs[lane * n + k] * hs[k];
-        dmv[lane] = d;
-    }
-    wave_lds_sync();
-    double xa[9];  // the analysis as stored (diagnostics)
-#pragma unroll
-    for (int a = 0; a < 9; ++a) xa[a] = 0.0;
-    if (mem) {
-        // this member's l observation perturbations: unconditional loads (an
-        // unused entry has index 0) so that all N are in flight together
-        double z[N];
-#pragma unroll
-        for (int jj = 0; jj < N; ++jj) z[jj] = p.dY[(size_t)qx[jj] * M + lane];
-#pragma unroll
-        for (int jj = 0; jj < N; ++jj) {
-            const double wj = sw[jj];
-            z[jj] = wj != 0.0 ? wj * z[jj] : 0.0;
-        }
-        double acc[9];
-#pragma unroll
-        for (int a = 0; a < 9; ++a) acc[a] = 0.0;
-#pragma unroll
-        for (int jj = 0; jj < N; ++jj) {
-            const double2* c2 = reinterpret_cast<const double2*>(Cs + jj * 10);
-#pragma unroll
-            for (int hh = 0; hh < 5; ++hh) {
-                const double2 cv = c2[hh];
-                acc[2 * hh] += cv.x * z[jj];
-                if (2 * hh + 1 < 9) acc[2 * hh + 1] += cv.y * z[jj];
-            }
-            if (jj % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int a = 0; a < 9; ++a) {
-            const double v = xbv[a] + p.sqrt_beta * dx[a] + dmv[a] + acc[a];
-            PopIO<T>::store(fs + slot(src_node(x, y, a, nx, ny), a, lane, M), a, v);
-            xa[a] = PopIO<T>::round(v, a);
-        }
-    }
-    if (p.diag_node)
-        node_diag_record(xa, mem, M, node, nx * ny, p.truth_uv,
-                         p.diag_node + ((size_t)nx * ny + node) * kDiagFieldCount);
 }
 
 // ---------------------------------------------------------------------------
@@ -635,7 +471,8 @@ __device__ __forceinline__ void apply_body(const AnalysisParams& p, const int* n
 // wavefront, lane l, element t < 8): A[l % 16][8 (l / 16) + t],
 // B[8 (l / 16) + t][l % 16]; result register r of lane l holds
 // D[4 (l / 16) + r][l % 16] (measured on gfx950).  Rows of A are the nine
-// populations (padded to 16); everything else is as in apply_body.
+// populations (padded to 16); one node per wavefront, lane = member, the rest on FP64
+// vector units.
 // ---------------------------------------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -829,38 +666,25 @@ __device__ __forceinline__ void apply_body_mfma(const AnalysisParams& p, const i
                          p.diag_node + ((size_t)nx * ny + node) * kDiagFieldCount);
 }
 
-// The apply body of a node: with MF (FP32 storage, n <= 32) the matrix-core
-// contractions, else the FP64 vector path.
 template <int N>
-constexpr bool kMfmaApply = N <= 32;
-
-template <int N, typename T, bool MF>
-__device__ __forceinline__ void apply_node(const AnalysisParams& p, const int* nodes, int item,
-                                           const double* __restrict__ gin) {
-    if constexpr (MF && sizeof(T) == 4 && kMfmaApply<N>) apply_body_mfma<N>(p, nodes, item, gin);
-    else apply_body<N, T>(p, nodes, item, gin);
-}
-
-template <int N, typename T, bool MF>
-__global__ __launch_bounds__(64) void analysis_apply_kernel(AnalysisParams p, const int* nodes,
-                                                            int count,
-                                                            const double* __restrict__ gin) {
+__global__ __launch_bounds__(64) void analysis_apply_mfma_kernel(AnalysisParams p, const int* nodes,
+                                                                 int count,
+                                                                 const double* __restrict__ gin) {
     const int item = xcd_remap(blockIdx.x, gridDim.x);
     if (item >= count) return;  // uniform over the wavefront
-    apply_node<N, T, MF>(p, nodes, item, gin);
+    apply_body_mfma<N>(p, nodes, item, gin);
 }
 
-// Batched form: wavefront w takes waves[w] = (problem, item).
-template <int N, typename T, bool MF>
-__global__ __launch_bounds__(64) void analysis_apply_batch_kernel(const AnalysisParams* P,
-                                                                  const int2* waves, int nwaves,
-                                                                  const int* nodes,
-                                                                  const double* __restrict__ gin) {
+// Batched form: wavefront w takes waves[w] = (4 problem, item).
+template <int N>
+__global__ __launch_bounds__(64) void analysis_apply_mfma_batch_kernel(
+    const AnalysisParams* P, const int2* waves, int nwaves, const int* nodes,
+    const double* __restrict__ gin) {
     const int w = xcd_remap(blockIdx.x, gridDim.x);
     if (w >= nwaves) return;
     const int2 d = waves[w];
-    const AnalysisParams p = P[d.x];
-    apply_node<N, T, MF>(p, nodes, d.y, gin);
+    const AnalysisParams p = P[d.x >> 2];
+    apply_body_mfma<N>(p, nodes, d.y, gin);
 }
 
 template <int N>
@@ -885,12 +709,10 @@ void analysis_eig_queue_kernel(const AnalysisParams* P, const int4* waves, int n
     }
 }
 
-template <int N, typename T, bool MF>
-__global__ __launch_bounds__(64) void analysis_apply_queue_kernel(const AnalysisParams* P,
-                                                                  const int2* waves, int nwaves,
-                                                                  const int* nodes,
-                                                                  const double* __restrict__ gin,
-                                                                  int* counters) {
+template <int N>
+__global__ __launch_bounds__(64) void analysis_apply_mfma_queue_kernel(
+    const AnalysisParams* P, const int2* waves, int nwaves, const int* nodes,
+    const double* __restrict__ gin, int* counters) {
     __shared__ int next;
     const int per = (nwaves + 7) / 8;
     const int lo = (int)(blockIdx.x % 8) * per;
@@ -902,8 +724,8 @@ __global__ __launch_bounds__(64) void analysis_apply_queue_kernel(const Analysis
         for (int w = w0; w < w1; ++w) {
             if (w > w0) __syncthreads();
             const int2 d = waves[w];
-            const AnalysisParams p = P[d.x];
-            apply_node<N, T, MF>(p, nodes, d.y, gin);
+            const AnalysisParams p = P[d.x >> 2];
+            apply_body_mfma<N>(p, nodes, d.y, gin);
         }
     }
 }
@@ -922,21 +744,23 @@ hipError_t launch_jacobi_n(const AnalysisParams& p, const int* nodes, int count,
     return hipGetLastError();
 }
 
+// The matrix-core apply of one size (FP32 storage, n <= 32), plain or batched.
 template <int N>
-hipError_t launch_n(const AnalysisParams& p, const int* nodes, int count, double* gbuf,
-                    hipStream_t s) {
-    if (count == 0) return hipSuccess;
-    hipError_t e = direct_solver(p.max_sweeps) ? launch_eig_direct(p, nodes, count, N, gbuf, s)
-                                               : launch_jacobi_n<N>(p, nodes, count, gbuf, s);
-    if (e != hipSuccess) return e;
-    const size_t app_bytes = (size_t)apply_lds_doubles(N) * sizeof(double);
-    if (p.storage == kStoreF32Dev && p.mfma_transform && kMfmaApply<N>)
-        analysis_apply_kernel<N, float, true><<<count, 64, app_bytes, s>>>(p, nodes, count, gbuf);
-    else if (p.storage == kStoreF32Dev)
-        analysis_apply_kernel<N, float, false><<<count, 64, app_bytes, s>>>(p, nodes, count, gbuf);
-    else
-        analysis_apply_kernel<N, double, false><<<count, 64, app_bytes, s>>>(p, nodes, count, gbuf);
-    return hipGetLastError();
+hipError_t launch_apply_mfma_n(const ApplyLaunch& l, hipStream_t s) {
+    if constexpr (N <= 32) {
+        const size_t bytes = (size_t)apply_lds_doubles(N) * sizeof(double);
+        if (!l.waves)
+            analysis_apply_mfma_kernel<N><<<l.count, 64, bytes, s>>>(*l.p, l.nodes, l.count, l.gbuf);
+        else if (!l.counters)
+            analysis_apply_mfma_batch_kernel<N><<<l.count, 64, bytes, s>>>(
+                l.d_params, l.waves, l.count, l.nodes, l.gbuf);
+        else
+            analysis_apply_mfma_queue_kernel<N><<<persistent_blocks(64, l.count), 64, bytes, s>>>(
+                l.d_params, l.waves, l.count, l.nodes, l.gbuf, l.counters);
+        return hipGetLastError();
+    } else {
+        return hipErrorInvalidValue;
+    }
 }
 
 // The batched eigen launch with the Jacobi solver, per wave or (counters) as a queue.
@@ -962,54 +786,6 @@ hipError_t launch_jacobi_batch_n(const AnalysisParams* d_params, const int4* d_e
     return hipGetLastError();
 }
 
-template <int N>
-hipError_t launch_batch_n(const AnalysisParams* d_params, const int4* d_eig_waves, int n_eig,
-                          const int2* d_apply_waves, int n_apply, const int* d_nodes,
-                          double* gbuf, int storage, bool mfma_transform, bool direct,
-                          hipStream_t s) {
-    if (n_eig == 0) return hipSuccess;
-    hipError_t e = direct ? launch_eig_direct_batch(d_params, d_eig_waves, n_eig, d_nodes, N, gbuf,
-                                                    nullptr, s)
-                          : launch_jacobi_batch_n<N>(d_params, d_eig_waves, n_eig, d_nodes, gbuf,
-                                                     nullptr, s);
-    if (e != hipSuccess) return e;
-    const size_t app_bytes = (size_t)apply_lds_doubles(N) * sizeof(double);
-    if (storage == kStoreF32Dev && mfma_transform && kMfmaApply<N>)
-        analysis_apply_batch_kernel<N, float, true><<<n_apply, 64, app_bytes, s>>>(
-            d_params, d_apply_waves, n_apply, d_nodes, gbuf);
-    else if (storage == kStoreF32Dev)
-        analysis_apply_batch_kernel<N, float, false><<<n_apply, 64, app_bytes, s>>>(
-            d_params, d_apply_waves, n_apply, d_nodes, gbuf);
-    else
-        analysis_apply_batch_kernel<N, double, false><<<n_apply, 64, app_bytes, s>>>(
-            d_params, d_apply_waves, n_apply, d_nodes, gbuf);
-    return hipGetLastError();
-}
-
-template <int N>
-hipError_t launch_batch_queue_n(const AnalysisParams* d_params, const int4* d_eig_waves, int n_eig,
-                                const int2* d_apply_waves, int n_apply, const int* d_nodes,
-                                double* gbuf, int storage, bool mfma_transform, bool direct,
-                                int* counters, hipStream_t s) {
-    if (n_eig == 0) return hipSuccess;
-    hipError_t e = direct ? launch_eig_direct_batch(d_params, d_eig_waves, n_eig, d_nodes, N, gbuf,
-                                                    counters, s)
-                          : launch_jacobi_batch_n<N>(d_params, d_eig_waves, n_eig, d_nodes, gbuf,
-                                                     counters, s);
-    if (e != hipSuccess) return e;
-    const size_t app_bytes = (size_t)apply_lds_doubles(N) * sizeof(double);
-    auto go = [&](auto kernel) {
-        const int ga = persistent_blocks(64, n_apply);
-        kernel<<<ga, 64, app_bytes, s>>>(d_params, d_apply_waves, n_apply, d_nodes, gbuf,
-                                         counters + 8);
-        return hipGetLastError();
-    };
-    if (storage == kStoreF32Dev && mfma_transform && kMfmaApply<N>)
-        return go(analysis_apply_queue_kernel<N, float, true>);
-    if (storage == kStoreF32Dev) return go(analysis_apply_queue_kernel<N, float, false>);
-    return go(analysis_apply_queue_kernel<N, double, false>);
-}
-
 }  // namespace
 
 #define LBMLETKF_OBS_SIZES(X) X(8) X(10) X(12) X(14) X(16) X(18) X(20) X(22) X(24) X(26) \
@@ -1028,9 +804,7 @@ int obs_size_for(int n) {
 
 int obs_lds_bytes(int n) {
     switch (n) {
-#define X(v) case v: return (eig_lds_doubles<v>() > apply_lds_doubles(v) ? eig_lds_doubles<v>() \
-                                                                        : apply_lds_doubles(v)) * \
-                            (int)sizeof(double);
+#define X(v) case v: return eig_lds_doubles<v>() * (int)sizeof(double);
         LBMLETKF_OBS_SIZES(X)
 #undef X
         default: return 1 << 30;
@@ -1039,14 +813,58 @@ int obs_lds_bytes(int n) {
 
 size_t obs_gbuf_doubles(int n, int count) { return (size_t)count * ((size_t)n * n + n); }
 
-hipError_t launch_analysis_obs(const AnalysisParams& p, const int* nodes, int count, int n,
-                               double* gbuf, hipStream_t s) {
-    switch (n) {
-#define X(v) case v: return launch_n<v>(p, nodes, count, gbuf, s);
+namespace {
+hipError_t launch_apply_mfma(const ApplyLaunch& l, hipStream_t s) {
+    switch (l.n) {
+#define X(v) case v: return launch_apply_mfma_n<v>(l, s);
         LBMLETKF_OBS_SIZES(X)
 #undef X
         default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_jacobi(const AnalysisParams& p, const int* nodes, int count, int n, double* gbuf,
+                         hipStream_t s) {
+    switch (n) {
+#define X(v) case v: return launch_jacobi_n<v>(p, nodes, count, gbuf, s);
+        LBMLETKF_OBS_SIZES(X)
+#undef X
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_jacobi_batch(const AnalysisParams* P, const int4* waves, int n_eig,
+                               const int* nodes, int n, double* gbuf, int* counters,
+                               hipStream_t s) {
+    switch (n) {
+#define X(v) case v: return launch_jacobi_batch_n<v>(P, waves, n_eig, nodes, gbuf, counters, s);
+        LBMLETKF_OBS_SIZES(X)
+#undef X
+        default: return hipErrorInvalidValue;
+    }
+}
+}  // namespace
+
+bool apply_on_matrix_cores(int storage, bool mfma_transform, int n) {
+    return storage == kStoreF32Dev && mfma_transform && n <= 32;
+}
+
+hipError_t launch_analysis_obs(const AnalysisParams& p, const int* nodes, int count, int n,
+                               double* gbuf, hipStream_t s) {
+    if (count == 0) return hipSuccess;
+    hipError_t e = direct_solver(p.max_sweeps) ? launch_eig_direct(p, nodes, count, n, gbuf, s)
+                                               : launch_jacobi(p, nodes, count, n, gbuf, s);
+    if (e != hipSuccess) return e;
+    ApplyLaunch l{};
+    l.p = &p;
+    l.nodes = nodes;
+    l.count = count;
+    l.n = n;
+    l.members = p.members;
+    l.storage = p.storage;
+    l.gbuf = gbuf;
+    return apply_on_matrix_cores(p.storage, p.mfma_transform != 0, n) ? launch_apply_mfma(l, s)
+                                                                      : launch_apply_rows(l, s);
 }
 
 namespace {
@@ -1065,36 +883,30 @@ int obs_segments(int n, bool direct) {
     return direct ? direct_segments(n) : (n > 0 ? 64 / n : 0);
 }
 
-hipError_t launch_analysis_obs_batch_queue(const AnalysisParams* d_params, const int4* d_eig_waves,
-                                           int n_eig, const int2* d_apply_waves, int n_apply,
-                                           const int* d_nodes, int n, double* gbuf, int storage,
-                                           bool mfma_transform, bool direct, int* counters,
-                                           hipStream_t s) {
-    switch (n) {
-#define X(v)                                                                                \
-    case v:                                                                                 \
-        return launch_batch_queue_n<v>(d_params, d_eig_waves, n_eig, d_apply_waves, n_apply, \
-                                       d_nodes, gbuf, storage, mfma_transform, direct,      \
-                                       counters, s);
-        LBMLETKF_OBS_SIZES(X)
-#undef X
-        default: return hipErrorInvalidValue;
+hipError_t launch_analysis_obs_batch(const ObsBatchLaunch& b, hipStream_t s) {
+    if (b.n_eig == 0) return hipSuccess;
+    hipError_t e = b.direct ? launch_eig_direct_batch(b.d_params, b.eig_waves, b.n_eig, b.nodes, b.n,
+                                                      b.gbuf, b.counters, s)
+                            : launch_jacobi_batch(b.d_params, b.eig_waves, b.n_eig, b.nodes, b.n,
+                                                  b.gbuf, b.counters, s);
+    ApplyLaunch l{};
+    l.d_params = b.d_params;
+    l.nodes = b.nodes;
+    l.n = b.n;
+    l.storage = b.storage;
+    l.gbuf = b.gbuf;
+    l.waves = b.apply_waves;
+    // one launch per class of member counts (a queue's counters: one set per class)
+    for (int k = 0; k < 4 && e == hipSuccess; ++k) {
+        l.count = b.n_apply[k];
+        l.members = 16 * (k + 1);
+        l.counters = b.counters ? b.counters + 8 * (k + 1) : nullptr;
+        if (l.count > 0)
+            e = apply_on_matrix_cores(b.storage, b.mfma_transform, b.n) ? launch_apply_mfma(l, s)
+                                                                        : launch_apply_rows(l, s);
+        l.waves += b.n_apply[k];
     }
-}
-
-hipError_t launch_analysis_obs_batch(const AnalysisParams* d_params, const int4* d_eig_waves,
-                                     int n_eig, const int2* d_apply_waves, int n_apply,
-                                     const int* d_nodes, int n, double* gbuf, int storage,
-                                     bool mfma_transform, bool direct, hipStream_t s) {
-    switch (n) {
-#define X(v)                                                                                   \
-    case v:                                                                                    \
-        return launch_batch_n<v>(d_params, d_eig_waves, n_eig, d_apply_waves, n_apply, d_nodes, \
-                                 gbuf, storage, mfma_transform, direct, s);
-        LBMLETKF_OBS_SIZES(X)
-#undef X
-        default: return hipErrorInvalidValue;
-    }
+    return e;
 }
 
 }  // namespace lbmletkf

@@ -140,7 +140,7 @@ __device__ __forceinline__ void fmac_chain(double* ua, double* ub, const double*
 }
 #undef LBM_FMAC_DPP
 
-__device__ __forceinline__ double row_sum(double v) { return group_reduce<16>(v, OpAdd()); }
+__device__ __forceinline__ double row_sum(double v) { return group_sum16(v); }
 
 // x^{-1/2} and 1 / x of normal positive x: the hardware estimate and one cubic
 // correction step (y (1 + e/2 + 3 e^2/8), e = 1 - x y^2; y (1 + e + e^2), e = 1 - x y).
