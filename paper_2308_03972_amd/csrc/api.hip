@@ -1028,7 +1028,12 @@ lbmletkf_status lbmletkf_misfit_backward(lbmletkf_ctx* ctx, const void* d_f0, do
     double* cur = reinterpret_cast<double*>(sw.w + L.lam0);
     double* oth = reinterpret_cast<double*>(sw.w + L.lam1);
     double* kpart = reinterpret_cast<double*>(sw.w + L.kpart);
-    const int nparts = adjoint_partials(c->dims);
+    // (the misfit's terms are summed by now: several steps per launch may put their partial
+    // sums of dJ/dK there too)
+    const int capacity = (int)std::min<size_t>((L.total - L.jbuf) / sizeof(double), 1 << 20);
+    const StepPlan plan = adjoint_plan(c->dims, steps_per_obs, capacity);
+    const int nparts = plan.steps > 1 ? tile_blocks(c->dims, plan) : adjoint_partials(c->dims);
+    if (plan.steps > 1) kpart = reinterpret_cast<double*>(sw.w + L.jbuf);
     hipError_t e = launch_fill(cur, nlam, 0.0, s);
     if (e == hipSuccess) e = launch_fill(kpart, (size_t)nparts, 0.0, s);
     if (e != hipSuccess) return hip_fail(e, "fill");
@@ -1077,13 +1082,22 @@ lbmletkf_status lbmletkf_misfit_backward(lbmletkf_ctx* ctx, const void* d_f0, do
         // the states between checkpoints t - 1 and t
         e = hipStreamWaitEvent(s, c->rready[t % 2], 0);
         if (e != hipSuccess) return hip_fail(e, "recompute join");
-        for (int j = steps_per_obs - 1; j >= 0; --j) {
-            const void* state = j == 0 ? sw.ckpt(t - 1) : cw.seg(j);
-            StageTimer tm(c, kStageAdjoint, s);
-            e = launch_adjoint_step(state, cur, oth, c->force(), c->dims, c->lbm.tau0, cs,
-                                    c->lbm.mu, c->storage(), kpart, s);
+        const int most = std::max(1, plan.steps);
+        int launches = (steps_per_obs + most - 1) / most;
+        for (int j = steps_per_obs - 1; j >= 0; --launches) {
+            auto state = [&](int k) { return k == 0 ? sw.ckpt(t - 1) : cw.seg(k); };
+            const int n = (j + launches) / launches;  // states j, .., j - n + 1
+            StageTimer tm(c, kStageAdjoint, s, kPerLaunch, n);
+            if (plan.steps > 1)
+                e = launch_adjoint_tile(state(j), state(j - n + 1), sw.sb, cur, oth, c->force(),
+                                        c->dims, c->lbm.tau0, cs, c->lbm.mu, c->storage(), kpart,
+                                        nparts, plan, n, s);
+            else
+                e = launch_adjoint_step(state(j), cur, oth, c->force(), c->dims, c->lbm.tau0, cs,
+                                        c->lbm.mu, c->storage(), kpart, s);
             if (e != hipSuccess) return hip_fail(e, "adjoint_step");
             std::swap(cur, oth);
+            j -= n;
         }
         e = hipEventRecord(c->rfree[t % 2], s);
         if (e != hipSuccess) return hip_fail(e, "recompute release");

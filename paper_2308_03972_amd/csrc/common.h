@@ -347,6 +347,19 @@ hipError_t launch_adjoint_step(const void* fstate, const double* lam_in, double*
 // nodes (the points must be distinct).
 hipError_t launch_misfit(const void* f, const int* pts, int npts, int nvar, const double* yo,
                          double* lam, double* jbuf, LbmDims d, int storage, hipStream_t s);
+// Several reverse steps per launch: the plan for intervals of `interval` steps (steps = 0: one
+// step per launch), at most `capacity` blocks; pl.steps >= steps > 1, states fhi,
+// fhi - stride_bytes, .., flast.  k_partial: tile_blocks() partial sums.
+StepPlan adjoint_plan(LbmDims d, int interval, int capacity);
+inline int tile_blocks(LbmDims d, const StepPlan& pl) {
+    const int tile = pl.region - 2 * (pl.steps - 1);
+    return ((d.nx + tile - 1) / tile) * ((d.ny + tile - 1) / tile) *
+           ((d.members + pl.members - 1) / pl.members);
+}
+hipError_t launch_adjoint_tile(const void* fhi, const void* flast, size_t stride_bytes,
+                               const double* lam_in, double* lam_out, const double* force, LbmDims d,
+                               double tau0, double cs, double mu, int storage, double* k_partial,
+                               int capacity, const StepPlan& pl, int steps, hipStream_t s);
 // Adjoint state [node][a][member] -> canonical [member][a][y][x].
 hipError_t launch_lam_to_canonical(const double* lam, double* out, LbmDims d, hipStream_t s);
 hipError_t launch_sum(const double* v, size_t n, double scale, double* out, hipStream_t s);
