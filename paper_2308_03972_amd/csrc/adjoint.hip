@@ -273,7 +273,7 @@ __global__ __launch_bounds__(1024) void adjoint_tile_kernel(
 template <typename T>
 __global__ void misfit_kernel(const T* __restrict__ f, const int* __restrict__ pts, int npts,
                               int nvar, const double* __restrict__ yo, double* __restrict__ lam,
-                              double* __restrict__ jbuf, int nx, int ny, int members) {
+                              double* __restrict__ jbuf, int first, int nx, int ny, int members) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= npts * members) return;
     const int k = t / members, m = t - k * members;
@@ -298,7 +298,10 @@ __global__ void misfit_kernel(const T* __restrict__ f, const int* __restrict__ p
         ru = u - y0[0];
         rv = v - y0[1];
     }
-    if (jbuf) jbuf[(size_t)m * npts + k] += rr * rr + ru * ru + rv * rv;
+    if (jbuf) {
+        double& j = jbuf[(size_t)m * npts + k];
+        j = (first ? 0.0 : j) + (rr * rr + ru * ru + rv * rv);
+    }
     if (lam) {
         // dJ/df_a = 2 rr + 2 ru (c_ax - u)/rho + 2 rv (c_ay - v)/rho
         const size_t node = (size_t)y * nx + x;
@@ -338,10 +341,11 @@ __global__ __launch_bounds__(256) void sum_kernel(const double* __restrict__ v, 
     if (threadIdx.x == 0) out[0] = scale * red[0];
 }
 
-__global__ void fill_kernel(double* __restrict__ v, size_t n, double value) {
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n;
+__global__ void zero2_kernel(double* __restrict__ v0, size_t n0, double* __restrict__ v1,
+                             size_t n1) {
+    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n0 + n1;
          i += (size_t)gridDim.x * blockDim.x)
-        v[i] = value;
+        *(i < n0 ? v0 + i : v1 + (i - n0)) = 0.0;
 }
 
 }  // namespace
@@ -444,16 +448,17 @@ hipError_t launch_lam_to_canonical(const double* lam, double* out, LbmDims d, hi
 }
 
 hipError_t launch_misfit(const void* f, const int* pts, int npts, int nvar, const double* yo,
-                         double* lam, double* jbuf, LbmDims d, int storage, hipStream_t s) {
+                         double* lam, double* jbuf, bool first, LbmDims d, int storage,
+                         hipStream_t s) {
     const int total = npts * d.members;
     if (storage == kStoreF32Dev)
         misfit_kernel<float><<<(total + 127) / 128, 128, 0, s>>>((const float*)f, pts, npts, nvar,
-                                                                 yo, lam, jbuf, d.nx, d.ny,
-                                                                 d.members);
+                                                                 yo, lam, jbuf, first, d.nx,
+                                                                 d.ny, d.members);
     else
         misfit_kernel<double><<<(total + 127) / 128, 128, 0, s>>>((const double*)f, pts, npts,
-                                                                  nvar, yo, lam, jbuf, d.nx, d.ny,
-                                                                  d.members);
+                                                                  nvar, yo, lam, jbuf, first, d.nx,
+                                                                  d.ny, d.members);
     return hipGetLastError();
 }
 
@@ -462,9 +467,9 @@ hipError_t launch_sum(const double* v, size_t n, double scale, double* out, hipS
     return hipGetLastError();
 }
 
-hipError_t launch_fill(double* v, size_t n, double value, hipStream_t s) {
-    size_t g = (n + 255) / 256;
-    fill_kernel<<<(int)(g > 65536 ? 65536 : (g == 0 ? 1 : g)), 256, 0, s>>>(v, n, value);
+hipError_t launch_zero2(double* v0, size_t n0, double* v1, size_t n1, hipStream_t s) {
+    const size_t g = (n0 + n1 + 255) / 256;
+    zero2_kernel<<<(int)(g > 65536 ? 65536 : (g == 0 ? 1 : g)), 256, 0, s>>>(v0, n0, v1, n1);
     return hipGetLastError();
 }
 

@@ -80,6 +80,7 @@ struct Ctx {
         double cs = 0.0;
         int steps = 0, times = 0;
         const void* work = nullptr;
+        bool kept = false;  // the last two intervals' states are still in the work's two sets
     } fwd;
     // the reverse sweep recomputes the next interval's states on this stream
     // while the caller's stream runs the current interval's adjoint steps
@@ -981,19 +982,23 @@ lbmletkf_status lbmletkf_misfit_forward(lbmletkf_ctx* ctx, const void* d_f0, dou
     Sweep sw{d_f0, reinterpret_cast<char*>(d_work), L, align_up(c->state_bytes())};
     double* jbuf = reinterpret_cast<double*>(sw.w + L.jbuf);
     const size_t nj = (size_t)c->dims.members * c->obs.n_points;
-    hipError_t e = launch_fill(jbuf, nj, 0.0, s);
-    if (e != hipSuccess) return hip_fail(e, "fill");
+    hipError_t e = hipSuccess;
     for (int t = 1; t <= n_times; ++t) {
-        if ((st = segment_advance(c, sw, t, steps_per_obs, cs, s))) return st;
+        // the last two intervals' states stay for the reverse sweep, which starts there
+        // (40 x 24 x 5, three intervals: two of three recomputations and their launches saved)
+        st = t + 2 > n_times
+                 ? segment_steps(c, sw.with_set(t % 2), t, steps_per_obs, steps_per_obs, cs, s)
+                 : segment_advance(c, sw, t, steps_per_obs, cs, s);
+        if (st) return st;
         StageTimer tm(c, kStageMisfit, s);
         e = launch_misfit(sw.ckpt(t), c->pts(), c->obs.n_points, c->obs.nvar,
-                          d_yo + (size_t)(t - 1) * c->nobs, nullptr, jbuf, c->dims, c->storage(),
-                          s);
+                          d_yo + (size_t)(t - 1) * c->nobs, nullptr, jbuf, t == 1, c->dims,
+                          c->storage(), s);
         if (e != hipSuccess) return hip_fail(e, "misfit");
     }
     e = launch_sum(jbuf, nj, 1.0, d_J, s);
     if (e != hipSuccess) return hip_fail(e, "sum");
-    c->fwd = {true, d_f0, cs, steps_per_obs, n_times, d_work};
+    c->fwd = {true, d_f0, cs, steps_per_obs, n_times, d_work, true};
     return LBMLETKF_OK;
 }
 
@@ -1034,9 +1039,16 @@ lbmletkf_status lbmletkf_misfit_backward(lbmletkf_ctx* ctx, const void* d_f0, do
     const StepPlan plan = adjoint_plan(c->dims, steps_per_obs, capacity);
     const int nparts = plan.steps > 1 ? tile_blocks(c->dims, plan) : adjoint_partials(c->dims);
     if (plan.steps > 1) kpart = reinterpret_cast<double*>(sw.w + L.jbuf);
-    hipError_t e = launch_fill(cur, nlam, 0.0, s);
-    if (e == hipSuccess) e = launch_fill(kpart, (size_t)nparts, 0.0, s);
+    hipError_t e = launch_zero2(cur, nlam, kpart, (size_t)nparts, s);
     if (e != hipSuccess) return hip_fail(e, "fill");
+    // the forward sweep left the last two intervals' states; earlier intervals overwrite them
+    // (not relied on in a captured sweep, which may be replayed without the forward one)
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    e = hipStreamIsCapturing(s, &capturing);
+    if (e != hipSuccess) return hip_fail(e, "capture status");
+    const bool use = fw.kept && capturing == hipStreamCaptureStatusNone;
+    const int kept = use ? n_times - 1 : n_times + 1;  // intervals kept .. n_times
+    if (n_times > 2) c->fwd.kept = false;
     // The states between checkpoints t - 1 and t are recomputed on the
     // recompute stream into set t % 2, one interval ahead of the adjoint steps
     // on the caller's stream: interval t - 1 is recomputed while interval t is
@@ -1056,6 +1068,7 @@ lbmletkf_status lbmletkf_misfit_backward(lbmletkf_ctx* ctx, const void* d_f0, do
     if (e == hipSuccess) e = hipStreamWaitEvent(rs, c->rstart, 0);
     if (e != hipSuccess) return hip_fail(e, "recompute fork");
     auto recompute = [&](int t) -> lbmletkf_status {
+        if (t >= kept) return LBMLETKF_OK;
         if (t + 2 <= n_times) {
             // set t % 2 was last read by interval t + 2's adjoint steps
             hipError_t ee = hipStreamWaitEvent(rs, c->rfree[t % 2], 0);
@@ -1075,12 +1088,12 @@ lbmletkf_status lbmletkf_misfit_backward(lbmletkf_ctx* ctx, const void* d_f0, do
             // lam^(t s) += dJ_t/df at the observation nodes
             StageTimer tm(c, kStageMisfit, s);
             e = launch_misfit(sw.ckpt(t), c->pts(), c->obs.n_points, c->obs.nvar,
-                              d_yo + (size_t)(t - 1) * c->nobs, cur, nullptr, c->dims,
+                              d_yo + (size_t)(t - 1) * c->nobs, cur, nullptr, false, c->dims,
                               c->storage(), s);
             if (e != hipSuccess) return hip_fail(e, "misfit");
         }
         // the states between checkpoints t - 1 and t
-        e = hipStreamWaitEvent(s, c->rready[t % 2], 0);
+        if (t < kept) e = hipStreamWaitEvent(s, c->rready[t % 2], 0);
         if (e != hipSuccess) return hip_fail(e, "recompute join");
         const int most = std::max(1, plan.steps);
         int launches = (steps_per_obs + most - 1) / most;

@@ -345,8 +345,10 @@ hipError_t launch_adjoint_step(const void* fstate, const double* lam_in, double*
 // Misfit terms at one observation time: jbuf[m * npts + k] += sum_var (H - y^o)^2
 // (jbuf may be NULL); if lam is not NULL, lam += dJ/df at the observation
 // nodes (the points must be distinct).
+// jbuf is added to, or with `first` written.
 hipError_t launch_misfit(const void* f, const int* pts, int npts, int nvar, const double* yo,
-                         double* lam, double* jbuf, LbmDims d, int storage, hipStream_t s);
+                         double* lam, double* jbuf, bool first, LbmDims d, int storage,
+                         hipStream_t s);
 // Several reverse steps per launch: the plan for intervals of `interval` steps (steps = 0: one
 // step per launch), at most `capacity` blocks; pl.steps >= steps > 1, states fhi,
 // fhi - stride_bytes, .., flast.  k_partial: tile_blocks() partial sums.
@@ -363,6 +365,7 @@ hipError_t launch_adjoint_tile(const void* fhi, const void* flast, size_t stride
 // Adjoint state [node][a][member] -> canonical [member][a][y][x].
 hipError_t launch_lam_to_canonical(const double* lam, double* out, LbmDims d, hipStream_t s);
 hipError_t launch_sum(const double* v, size_t n, double scale, double* out, hipStream_t s);
-hipError_t launch_fill(double* v, size_t n, double value, hipStream_t s);
+// Zeros for two buffers.
+hipError_t launch_zero2(double* v0, size_t n0, double* v1, size_t n1, hipStream_t s);
 
 }  // namespace lbmletkf
