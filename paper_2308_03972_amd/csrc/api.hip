@@ -701,11 +701,27 @@ lbmletkf_status observe(lbmletkf_ctx* ctx, const void* d_f, double* d_yf, void* 
 
 namespace {
 
-// The analysis of letkf_analyze; with diag_node, the analysis kernels also
+ObsTask obs_task(const Ctx* c, const void* d_f, const double* d_yo) {
+    return {d_f,      c->pts(),  d_yo,        c->ybar(),    c->dY(),    c->dvec(),
+            c->K(),   c->obs.n_points, c->obs.nvar, c->dims.nx, c->dims.ny, c->dims.members};
+}
+
+// The analysis of letkf_analyze (d_yf = NULL: of d_f's own observations); with diag_node, the analysis kernels also
 // write every node's diagnostics record of the forecast and of the analysis.
 lbmletkf_status analyze_impl(Ctx* c, void* d_f, const double* d_yf, const double* d_yo,
                              const double* d_truth_uv, double* diag_node, hipStream_t s) {
-    {
+    if (!d_yf) {
+        const ObsTask task = obs_task(c, d_f, d_yo);
+        hipError_t e;
+        {
+            StageTimer t(c, kStageObserve, s);
+            e = launch_observe_stats(&task, 1, c->storage(), s);
+        }
+        if (e != hipSuccess) return hip_fail(e, "observe");
+        StageTimer t(c, kStageStats, s);
+        e = launch_obs_grams(&task, 1, c->storage(), s);
+        if (e != hipSuccess) return hip_fail(e, "obs_stats");
+    } else {
         StageTimer t(c, kStageStats, s);
         hipError_t e = launch_obs_stats(d_yf, d_yo, c->nobs, c->dims.members, c->ybar(), c->dY(),
                                         c->dvec(), c->K(), c->storage(), s);
@@ -796,12 +812,11 @@ lbmletkf_status run_cycle(lbmletkf_ctx* ctx, void* d_f, int32_t nsteps, const do
     if (c->dims.members < 2) return fail(LBMLETKF_EINVAL, "analysis needs >= 2 members");
     lbmletkf_status st = lbm_ensemble_step(ctx, d_f, nsteps, stream);
     if (st) return st;
-    if ((st = observe(ctx, d_f, c->yf(), stream))) return st;
     hipStream_t s = as_stream(stream);
-    if (!d_diag) return analyze_impl(c, d_f, c->yf(), d_yo, nullptr, nullptr, s);
+    if (!d_diag) return analyze_impl(c, d_f, nullptr, d_yo, nullptr, nullptr, s);
     // diagnostics of the forecast and of the analysis from the analysis kernels'
     // per-node records (they hold each node's forecast and analysis anyway)
-    if ((st = analyze_impl(c, d_f, c->yf(), d_yo, d_truth_uv, c->diag_node(), s))) return st;
+    if ((st = analyze_impl(c, d_f, nullptr, d_yo, d_truth_uv, c->diag_node(), s))) return st;
     {
         StageTimer t(c, kStageDiag, s);
         hipError_t e = launch_diag_nodes_final(c->diag_node(), c->dims.nx * c->dims.ny,
@@ -1526,16 +1541,12 @@ hipError_t batch_analysis(Batch* b, const AnalysisParams* params, hipStream_t s)
 // Observation operator and statistics of every problem (inputs: the bound states
 // or, for tuning, their partners).
 hipError_t batch_observe(Batch* b, bool partners, hipStream_t s) {
-    hipError_t e = hipSuccess;
-    for (size_t k = 0; k < b->ctx.size() && e == hipSuccess; ++k) {
-        Ctx* c = b->ctx[k];
-        const void* f = partners ? c->fbuf() : b->f[k];
-        e = launch_observe(f, c->pts(), c->obs.n_points, c->obs.nvar, c->yf(), c->dims,
-                           b->storage, s);
-        if (e == hipSuccess)
-            e = launch_obs_stats(c->yf(), b->d_yo + b->yo_off[k], c->nobs, c->dims.members,
-                                 c->ybar(), c->dY(), c->dvec(), c->K(), b->storage, s);
-    }
+    std::vector<ObsTask> tasks;
+    for (size_t k = 0; k < b->ctx.size(); ++k)
+        tasks.push_back(obs_task(b->ctx[k], partners ? b->ctx[k]->fbuf() : b->f[k],
+                                 b->d_yo + b->yo_off[k]));
+    hipError_t e = launch_observe_stats(tasks.data(), (int)tasks.size(), b->storage, s);
+    if (e == hipSuccess) e = launch_obs_grams(tasks.data(), (int)tasks.size(), b->storage, s);
     return e;
 }
 

@@ -188,6 +188,18 @@ hipError_t launch_observe(const void* f, const int* pts, int npts, int nvar, dou
 hipError_t launch_obs_stats(const double* yf, const double* yo, int nobs, int members,
                             double* ybar, double* dY, double* dvec, double* K, int storage,
                             hipStream_t s);
+// Observation operator and statistics of n problems straight from their states, and the
+// Gram matrices of those with K != NULL (after launch_observe_stats): as launch_observe and
+// launch_obs_stats, in one launch each.
+struct ObsTask {
+    const void* f;
+    const int* pts;
+    const double* yo;
+    double *ybar, *dY, *dvec, *K;
+    int npts, nvar, nx, ny, members;
+};
+hipError_t launch_observe_stats(const ObsTask* tasks, int n, int storage, hipStream_t s);
+hipError_t launch_obs_grams(const ObsTask* tasks, int n, int storage, hipStream_t s);
 hipError_t launch_local_table(const int* pts, int npts, double d_cut, int lmax, int nx, int ny,
                               int* loc_pt, double* loc_g, int* overflow, hipStream_t s);
 

@@ -84,6 +84,48 @@ __global__ __launch_bounds__(256) void obs_stats_kernel(
     }
 }
 
+// Observation operator and statistics in one launch, for the problems of a cycle (up to
+// kObsTasks): one wavefront per observation point, lane = member, block row = problem; the
+// same values as the two kernels above, without y^f and a launch per problem and step
+// (32^2 x 8: 5.5 -> 3 us; four problems of a batch: 50 -> 10 us of a replayed graph).
+constexpr int kObsTasks = 32;
+struct ObsTasks {
+    ObsTask t[kObsTasks];
+};
+
+template <typename T>
+__global__ __launch_bounds__(256) void observe_stats_kernel(const ObsTasks tasks) {
+    const ObsTask& p = tasks.t[blockIdx.y];
+    const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int m = threadIdx.x & 63;
+    const int M = p.members;
+    if (k >= p.npts) return;
+    const int x = p.pts[2 * k], y = p.pts[2 * k + 1];
+    double rho = 0.0, jx = 0.0, jy = 0.0;
+    if (m < M) {
+#pragma unroll
+        for (int a = 0; a < 9; ++a) {
+            const double fa = PopIO<T>::load(
+                static_cast<const T*>(p.f) + slot(src_node(x, y, a, p.nx, p.ny), a, m, M), a);
+            rho += fa;
+            jx += cx_of(a) * fa;
+            jy += cy_of(a) * fa;
+        }
+    }
+    const double val[3] = {rho, jx / rho, jy / rho};
+    for (int v = 0; v < p.nvar; ++v) {
+        const double o = v + 3 - p.nvar == 0 ? val[0] : (v + 3 - p.nvar == 1 ? val[1] : val[2]);
+        const double yf = m < M ? o : 0.0;
+        const double mean = wave_sum(yf) / M;
+        const int q = k * p.nvar + v;
+        if (m < M) p.dY[(size_t)q * M + m] = yf - mean;
+        if (m == 0) {
+            p.ybar[q] = mean;
+            p.dvec[q] = p.yo[q] - mean;
+        }
+    }
+}
+
 // K = dY dY^T (unweighted observation-space Gram matrix, nobs x nobs, inner
 // dimension the members): the dense contraction under every node's
 // Z Z^T = diag(sqrt r) K_L diag(sqrt r), on the matrix cores.  One wavefront
@@ -114,8 +156,8 @@ __device__ __forceinline__ int mfma16_row(int lane, int j) {
 }
 
 template <typename T>
-__global__ __launch_bounds__(64) void obs_gram_kernel(const double* __restrict__ dY, int nobs,
-                                                      int members, double* __restrict__ K) {
+__device__ __forceinline__ void obs_gram(const double* __restrict__ dY, int nobs, int members,
+                                         double* __restrict__ K) {
     const int tx = blockIdx.x, ty = blockIdx.y;
     if (ty > tx) return;  // uniform over the wavefront
     const int lane = threadIdx.x;
@@ -153,6 +195,20 @@ __global__ __launch_bounds__(64) void obs_gram_kernel(const double* __restrict__
         K[(size_t)row * nobs + col] = out[j];
         K[(size_t)col * nobs + row] = out[j];
     }
+}
+
+template <typename T>
+__global__ __launch_bounds__(64) void obs_gram_kernel(const double* __restrict__ dY, int nobs,
+                                                      int members, double* __restrict__ K) {
+    obs_gram<T>(dY, nobs, members, K);
+}
+
+template <typename T>
+__global__ __launch_bounds__(64) void obs_gram_tasks_kernel(const ObsTasks tasks) {
+    const ObsTask& p = tasks.t[blockIdx.z];
+    const int nobs = p.npts * p.nvar;
+    if (!p.K || (int)blockIdx.x * 16 >= nobs) return;  // uniform over the wavefront
+    obs_gram<T>(p.dY, nobs, p.members, p.K);
 }
 
 // ---------------------------------------------------------------------------
@@ -584,11 +640,16 @@ __global__ __launch_bounds__(kDiagBlock) void diag_fold_kernel(const double* __r
     }
 }
 
-__global__ __launch_bounds__(kDiagBlock) void diag_final_kernel(const double* __restrict__ partial,
+// The last reduction: block s takes the nblocks records of state s to out0 or out1.
+__global__ __launch_bounds__(kDiagBlock) void diag_final_kernel(const double* __restrict__ records,
                                                                 int nblocks, int plane,
-                                                                double* __restrict__ out) {
+                                                                double* __restrict__ out0,
+                                                                double* __restrict__ out1) {
+    const double* partial = records + (size_t)blockIdx.x * nblocks * kDiagFields;
+    double* out = blockIdx.x == 0 ? out0 : out1;
     __shared__ double red[kDiagFields][kDiagBlock];
     double err2 = 0.0, spr2 = 0.0, bad = 0.0, rmin = INFINITY, rmax = -INFINITY;
+#pragma unroll 4
     for (int b = threadIdx.x; b < nblocks; b += kDiagBlock) {
         err2 += partial[b * kDiagFields + 0];
         spr2 += partial[b * kDiagFields + 1];
@@ -738,6 +799,48 @@ hipError_t launch_obs_stats(const double* yf, const double* yo, int nobs, int me
     return hipGetLastError();
 }
 
+hipError_t launch_observe_stats(const ObsTask* tasks, int n, int storage, hipStream_t s) {
+    for (int k0 = 0; k0 < n; k0 += kObsTasks) {
+        ObsTasks l{};
+        const int count = n - k0 < kObsTasks ? n - k0 : kObsTasks;
+        int npts = 0;
+        for (int k = 0; k < count; ++k) {
+            l.t[k] = tasks[k0 + k];
+            npts = l.t[k].npts > npts ? l.t[k].npts : npts;
+        }
+        const dim3 grid((npts + 3) / 4, count);
+        if (storage == kStoreF32Dev)
+            observe_stats_kernel<float><<<grid, 256, 0, s>>>(l);
+        else
+            observe_stats_kernel<double><<<grid, 256, 0, s>>>(l);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t launch_obs_grams(const ObsTask* tasks, int n, int storage, hipStream_t s) {
+    for (int k0 = 0; k0 < n; k0 += kObsTasks) {
+        ObsTasks l{};
+        int count = 0, nobs = 0;
+        for (int k = k0; k < n && k < k0 + kObsTasks; ++k) {
+            if (!tasks[k].K) continue;
+            l.t[count++] = tasks[k];
+            const int q = tasks[k].npts * tasks[k].nvar;
+            nobs = q > nobs ? q : nobs;
+        }
+        if (count == 0) continue;
+        const dim3 grid((nobs + 15) / 16, (nobs + 15) / 16, count);
+        if (storage == kStoreF32Dev)
+            obs_gram_tasks_kernel<float><<<grid, 64, 0, s>>>(l);
+        else
+            obs_gram_tasks_kernel<double><<<grid, 64, 0, s>>>(l);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 hipError_t launch_local_table(const int* pts, int npts, double d_cut, int lmax, int nx, int ny,
                               int* loc_pt, double* loc_g, int* overflow, hipStream_t s) {
     const int plane = nx * ny;
@@ -792,7 +895,7 @@ hipError_t launch_diag(const void* f, const double* truth_uv, LbmDims d, int sto
                                                                 d.ny, d.members, partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    diag_final_kernel<<<1, kDiagBlock, 0, s>>>(partial, need, d.nx * d.ny, out);
+    diag_final_kernel<<<1, kDiagBlock, 0, s>>>(partial, need, d.nx * d.ny, out, nullptr);
     return hipGetLastError();
 }
 
@@ -801,15 +904,18 @@ int diag_fold_blocks(int plane) { return (plane + kDiagBlock - 1) / kDiagBlock; 
 hipError_t launch_diag_nodes_final(const double* diag_node, int plane, double* partial,
                                    double* out_forecast, double* out_analysis, hipStream_t s) {
     static_assert(kDiagFields == kDiagFieldCount, "one diagnostics record layout");
+    // (up to 16 records per thread the last reduction takes the nodes' own records:
+    // 32^2 3.8 + 2.7 -> 3 us, one launch less)
+    if (plane <= 16 * kDiagBlock) {
+        diag_final_kernel<<<2, kDiagBlock, 0, s>>>(diag_node, plane, plane, out_forecast,
+                                                   out_analysis);
+        return hipGetLastError();
+    }
     const int nb = diag_fold_blocks(plane);
     diag_fold_kernel<<<dim3(nb, 2), kDiagBlock, 0, s>>>(diag_node, plane, partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    diag_final_kernel<<<1, kDiagBlock, 0, s>>>(partial, nb, plane, out_forecast);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    diag_final_kernel<<<1, kDiagBlock, 0, s>>>(partial + (size_t)nb * kDiagFields, nb, plane,
-                                               out_analysis);
+    diag_final_kernel<<<2, kDiagBlock, 0, s>>>(partial, nb, plane, out_forecast, out_analysis);
     return hipGetLastError();
 }
 
