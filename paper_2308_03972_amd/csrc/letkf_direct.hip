@@ -8,12 +8,13 @@
 // and the update x_m = x_bar + dX (w_bar + dW[:, m]) of the nine populations follows in the
 // same wavefront, the rows of dW still in registers.
 //
-// Sizes up to 32 take four nodes per wavefront (a row of 16 lanes each), larger ones one.
+// Sizes up to 32 take four nodes per wavefront (a row of 16 lanes each), the observation
+// route's 40 and 48 two, larger ones (and the ensemble route's 48) one.
 // What bounds it: FP64 issue and the latency of the reflector chain (two reductions and
 // two reciprocal square roots per step); LDS and memory traffic are minor.  Measured
 // per node (S resident, 39,232 nodes at N <= 32, 16,384 beyond; before: the Jacobi
 // solver): N = 8 1.0 ns (6), 16 2.4 (19), 18 3.8 (15), 24 7.3 (65), 32 11.5 (109),
-// 40 62 (404), 48 75 (687), 64 178 (1466).
+// 40 32 (404; one node per wavefront: 62), 48 43 (687; 75), 64 178 (1466).
 #include <type_traits>
 
 #include "common.h"
@@ -26,6 +27,8 @@ using namespace dev;
 
 template <int N>
 constexpr bool kRows16 = N <= 32;  // four nodes per wavefront
+template <int N>
+constexpr bool kPairs = N > 32 && N <= 48;  // two (observation route)
 
 // ---------------------------------------------------------------------------
 // observation route
@@ -92,7 +95,69 @@ __device__ __forceinline__ void direct_body(const AnalysisParams p, const int* n
     }
 }
 
-// One node nodes[item] (item < end), 32 < N <= 64.
+// Two nodes nodes[item0], nodes[item0 + 1] (item < end), N = 40 or 48.
+template <int N>
+__device__ __forceinline__ void direct_body_pair(const AnalysisParams p, const int* nodes, int item0,
+                                                 int end, double* gout) {
+    using D = DirectP<N>;
+    extern __shared__ double lds[];
+    const int lane = threadIdx.x;
+    const int r = lane & 15, half = lane >> 4 & 1;
+    const int item = item0 + (lane >> 5);
+    const bool valid = item < end;
+    const int node = valid ? nodes[item] : 0;
+    int q[3];
+    double w[3], b[3];
+#pragma unroll
+    for (int h = 0; h < 3; ++h) {
+        q[h] = 0;
+        w[h] = b[h] = 0.0;
+        if (valid && r + 16 * h < N) local_obs(p, node, r + 16 * h, &q[h], &w[h], &b[h]);
+    }
+    const bool any = weighted_indices<3>(q, w, lane);
+    const double* krow[3];
+#pragma unroll
+    for (int h = 0; h < 3; ++h) krow[h] = any ? p.K + (size_t)q[h] * p.nobs : p.loc_g;
+    // S = diag(w) K diag(w): all loads in flight together, then the weights
+    double A[3][D::COLS];
+    auto load = [&](auto self, auto C) -> void {
+        constexpr int c = decltype(C)::value, j0 = D::elem(c, 0), j1 = D::elem(c, 1);
+        const int q0 = __builtin_amdgcn_mov_dpp(q[j0 / 16], 0x150 + j0 % 16, 0xF, 0xF, true);
+        const int q1 = __builtin_amdgcn_mov_dpp(q[j1 / 16], 0x150 + j1 % 16, 0xF, 0xF, true);
+        const int qj = half ? q1 : q0;
+#pragma unroll
+        for (int h = 0; h < 3; ++h) A[h][c] = krow[h][qj];
+        if constexpr (c + 1 < D::COLS) self(self, std::integral_constant<int, c + 1>());
+    };
+    load(load, std::integral_constant<int, 0>());
+    auto weigh = [&](auto self, auto C) -> void {
+        constexpr int c = decltype(C)::value, j0 = D::elem(c, 0), j1 = D::elem(c, 1);
+        const double w0 = row_bcast<j0 % 16>(w[j0 / 16]), w1 = row_bcast<j1 % 16>(w[j1 / 16]);
+        const double wj = half ? w1 : w0;
+#pragma unroll
+        for (int h = 0; h < 3; ++h) A[h][c] *= w[h] * wj;
+        if constexpr (c + 1 < D::COLS) self(self, std::integral_constant<int, c + 1>());
+    };
+    weigh(weigh, std::integral_constant<int, 0>());
+    const double ia = 1.0 / p.a;
+    double* out = gout + (size_t)(valid ? item : item0) * (N * N + N);
+    const ReflGlobal vs{out, N, valid};
+    const bool finite = sym_direct_pair<N, false>(A, b, ia, -p.sqrt_beta * ia, lds, vs, lane);
+    if (__any(valid && !finite) && lane == 0) atomicAdd(p.eig_fail, 1);
+    if (valid) {
+#pragma unroll
+        for (int h = 0; h < 3; ++h) {
+            const int i = r + 16 * h;
+            if (i >= N) continue;
+#pragma unroll
+            for (int c = 0; c < D::COLS; ++c)
+                out[(size_t)(half ? D::elem(c, 1) : D::elem(c, 0)) * N + i] = A[h][c];
+            if (half == 0) out[(size_t)N * N + i] = b[h] * ia;
+        }
+    }
+}
+
+// One node nodes[item] (item < end), 48 < N <= 64.
 template <int N>
 __device__ __forceinline__ void direct_body_wave(const AnalysisParams p, const int* nodes, int item,
                                                  int end, double* gout) {
@@ -152,11 +217,12 @@ template <int N>
 __device__ __forceinline__ void direct_node(const AnalysisParams p, const int* nodes, int item0,
                                             int end, double* gout) {
     if constexpr (kRows16<N>) direct_body<N>(p, nodes, item0, end, gout);
+    else if constexpr (kPairs<N>) direct_body_pair<N>(p, nodes, item0, end, gout);
     else direct_body_wave<N>(p, nodes, item0, end, gout);
 }
 
 template <int N>
-constexpr int direct_segs() { return kRows16<N> ? 4 : 1; }
+constexpr int direct_segs() { return kRows16<N> ? 4 : (kPairs<N> ? 2 : 1); }
 
 // Wavefronts per SIMD the registers allow without spilling.
 template <int N>
@@ -165,6 +231,7 @@ constexpr int direct_waves() { return N <= 16 ? 4 : (N <= 20 ? 3 : 2); }
 template <int N>
 constexpr size_t direct_lds_bytes() {
     if constexpr (kRows16<N>) return 4 * Direct<N>::kNodeDoubles * sizeof(double);
+    else if constexpr (kPairs<N>) return 2 * DirectP<N>::kNodeDoubles * sizeof(double);
     else return DirectW<N>::kDoubles * sizeof(double);
 }
 
@@ -406,6 +473,9 @@ __device__ __forceinline__ void ens_direct_node(const AnalysisParams& p, int nod
 }
 
 template <int N>
+constexpr int ens_direct_segs() { return kRows16<N> ? 4 : 1; }
+
+template <int N>
 constexpr size_t ens_direct_lds_bytes() {
     if constexpr (kRows16<N>)
         return 4 * (Direct<N>::kNodeDoubles + ReflLds::doubles(N)) * sizeof(double);
@@ -416,7 +486,7 @@ constexpr size_t ens_direct_lds_bytes() {
 template <int N, typename T>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(direct_waves<N>())))
 void analysis_ens_direct_kernel(AnalysisParams p) {
-    ens_direct_node<N, T>(p, xcd_remap(blockIdx.x, gridDim.x) * direct_segs<N>());
+    ens_direct_node<N, T>(p, xcd_remap(blockIdx.x, gridDim.x) * ens_direct_segs<N>());
 }
 
 template <int N, typename T>
@@ -454,7 +524,7 @@ hipError_t launch_direct_batch_n(const AnalysisParams* P, const int4* waves, int
 
 template <int N, typename T>
 hipError_t launch_ens_direct_t(const AnalysisParams& p, hipStream_t s) {
-    constexpr int segs = direct_segs<N>();
+    constexpr int segs = ens_direct_segs<N>();
     analysis_ens_direct_kernel<N, T><<<(p.nx * p.ny + segs - 1) / segs, 64,
                                        ens_direct_lds_bytes<N>(), s>>>(p);
     return hipGetLastError();
@@ -473,7 +543,7 @@ hipError_t launch_ens_direct_batch_t(const AnalysisParams* P, const int2* waves,
     X(28) X(30) X(32) X(40) X(48) X(56) X(64)
 #define LBMLETKF_ENS_SIZES(X) X(8) X(16) X(24) X(32) X(48) X(64)
 
-int direct_segments(int n) { return n <= 32 ? 4 : 1; }
+int direct_segments(int n) { return n <= 32 ? 4 : (n <= 48 ? 2 : 1); }
 
 hipError_t launch_eig_direct(const AnalysisParams& p, const int* nodes, int count, int n,
                              double* gbuf, hipStream_t s) {

@@ -1,6 +1,7 @@
 // Direct (iteration-free) functions of small symmetric matrices for the analysis:
 // Householder tridiagonalisation, a sum of shifted tridiagonal inverses
-// (sqrt_poles.h) and the back transformation, four nodes per wavefront.
+// (sqrt_poles.h) and the back transformation: four nodes per wavefront up to N = 32
+// (described here), two up to 48, one up to 64.
 //
 // Layout: a node owns a row of 16 lanes; lane r holds rows r and r + 16 (N > 16) of
 // its N x N matrix in registers.  Everything one lane needs of another's comes
@@ -519,6 +520,441 @@ __device__ __forceinline__ bool sym_direct(double (&A)[Direct<N>::NS][N],
 #pragma unroll
     for (int h = 0; h < NS; ++h) b[h] = hv[h];
     back_all<N, D::kTop>(A, b, vs, lane);
+    return finite;
+}
+
+// ---------------------------------------------------------------------------
+// two nodes per wavefront, 32 < N <= 48
+// ---------------------------------------------------------------------------
+// A node owns two rows of 16 lanes.  Lane (q, r) of it (q = 0, 1) holds rows r, r + 16 and
+// r + 32 and of them half the columns: of each 16 columns the 8 of index 8 q .. 8 q + 7 (of
+// the last 8, N = 40, four), in all N / 2 a row: 120 or 144 registers where whole rows would
+// need 240 or 288.  A vector is kept by rows in both lane rows; as broadcast operand the second
+// lane row takes it rotated by those 8 (or 4) lanes, so that one row_newbcast serves both.  Only
+// the products' partial sums cross the lane rows (v_permlane16_swap).  Against one node per
+// wavefront (below) this leaves 2.4 times fewer instructions a node: no vector goes through
+// LDS, and a step's reductions and square roots serve two nodes.
+template <int N>
+struct DirectP {
+    static_assert(N == 40 || N == 48, "the last rows' 8 or 16 columns split evenly");
+    static constexpr int NS = 3;
+    static constexpr int COLS = N / 2;
+    static constexpr int ZS = N + 1;
+    static constexpr int kPoles = 11;             // a pass; lane 11: the solution
+    static constexpr int kNodeDoubles = 24 * ZS;  // tables z, e of 12 lanes; then the transposes
+    static constexpr int width(int h) { return h < 2 ? 8 : N / 2 - 16; }
+    // the element of column c (0 .. COLS - 1) in lane row q
+    static constexpr int elem(int c, int q) {
+        return 16 * (c / 8) + width(c / 8) * q + c % 8;
+    }
+};
+
+// The sum over a node's two lane rows, in both.
+__device__ __forceinline__ double pair_sum(double x) {
+    const unsigned lo = __double2loint(x), hi = __double2hiint(x);
+    const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __hiloint2double(b[0], a[0]) + __hiloint2double(b[1], a[1]);
+}
+
+// A vector by rows as broadcast operand, slots 0 .. S.
+template <int N, int S>
+__device__ __forceinline__ void pair_operand(const double* x, double (&out)[3], int q) {
+#pragma unroll
+    for (int h = 0; h <= S; ++h) {
+        int lo, hi;
+        if (DirectP<N>::width(h) == 8) {
+            lo = __builtin_amdgcn_mov_dpp(__double2loint(x[h]), 0x128, 0xF, 0xF, true);
+            hi = __builtin_amdgcn_mov_dpp(__double2hiint(x[h]), 0x128, 0xF, 0xF, true);
+        } else {
+            lo = __builtin_amdgcn_mov_dpp(__double2loint(x[h]), 0x12C, 0xF, 0xF, true);
+            hi = __builtin_amdgcn_mov_dpp(__double2hiint(x[h]), 0x12C, 0xF, 0xF, true);
+        }
+        out[h] = q ? __hiloint2double(hi, lo) : x[h];
+    }
+}
+
+// a += x y and a . x over the columns of slots 0 .. S.
+template <int N, int S>
+__device__ __forceinline__ void pair_axpy(double* a, const double (&x)[3], double y) {
+    fmac_axpy<0, 8>(a, x[0], y);
+    if constexpr (S > 0) fmac_axpy<0, 8>(a + 8, x[1], y);
+    if constexpr (S > 1) fmac_axpy<0, DirectP<N>::width(2)>(a + 16, x[2], y);
+}
+template <int N, int S>
+__device__ __forceinline__ double pair_dot(const double* a, const double (&x)[3]) {
+    double s0 = 0.0, s1 = 0.0;
+    fmac_dot<0, 8>(a, x[0], s0, s1);
+    if constexpr (S > 0) fmac_dot<0, 8>(a + 8, x[1], s0, s1);
+    if constexpr (S > 1) fmac_dot<0, DirectP<N>::width(2)>(a + 16, x[2], s0, s1);
+    return pair_sum(s0 + s1);
+}
+
+// tri_phase for the pivot columns n - 1 of slot S that lane row Q holds.
+template <int N, int S, int Q, typename R>
+__device__ __forceinline__ void pair_tri_phase(double (&A)[3][DirectP<N>::COLS], double (&d)[3],
+                                               double (&e)[3], double (&b)[3], const R& vs,
+                                               int lane) {
+    constexpr int W = DirectP<N>::width(S);
+    constexpr int BASE = 16 * S + W * Q;
+    const int r = lane & 15, q = lane >> 4 & 1;
+#pragma unroll 1
+    for (int n = BASE + W; n > (BASE > 2 ? BASE : 2); --n) {
+        double x[3] = {0.0, 0.0, 0.0}, v[3] = {0.0, 0.0, 0.0}, p[3] = {0.0, 0.0, 0.0};
+        double xr[3] = {0.0, 0.0, 0.0};
+        // column n - 1 (weights 1 and 0, as in tri_phase), from its lane row to both
+#pragma unroll
+        for (int c = 0; c < W; ++c) {
+            const double w = q == Q && n - 1 == BASE + c ? 1.0 : 0.0;
+#pragma unroll
+            for (int h = 0; h <= S; ++h) xr[h] = fma(A[h][8 * S + c], w, xr[h]);
+        }
+        double s2 = 0.0;
+#pragma unroll
+        for (int h = 0; h <= S; ++h) {
+            const double t = pair_sum(xr[h]);
+            d[h] = r + 16 * h == n - 1 ? t : d[h];
+            x[h] = r + 16 * h < n - 1 ? t : 0.0;
+            s2 = fma(x[h], x[h], s2);
+        }
+        const double xp = S > 0 && n - 2 < 16 * S ? x[S > 0 ? S - 1 : 0] : x[S];
+        const double x1 = row_bcast_dyn(xp, (n - 2) & 15, lane);
+        s2 = row_sum(s2);
+        const bool some = s2 > 1e-290;
+        const double norm = s2 * fast_rsqrt(s2);
+        const double rb = some ? fast_rsqrt(fma(fabs(x1), norm, s2)) : 0.0;
+        const double alpha = some ? -copysign(norm, x1) : x1;
+        const double shift = some ? copysign(norm, x1) : 0.0;
+#pragma unroll
+        for (int h = 0; h <= S; ++h) {
+            const bool piv = r + 16 * h == n - 2;
+            e[h] = piv ? alpha : e[h];
+            v[h] = (x[h] + (piv ? shift : 0.0)) * rb;
+            vs.put(n, r + 16 * h, v[h]);
+        }
+        double vq[3], pq[3];
+        pair_operand<N, S>(v, vq, q);
+        double c = 0.0, cb = 0.0;
+#pragma unroll
+        for (int h = 0; h <= S; ++h) {
+            p[h] = pair_dot<N, S>(A[h], vq);
+            c = fma(v[h], p[h], c);
+            cb = fma(v[h], b[h], cb);
+        }
+        c = row_sum(c);
+        cb = row_sum(cb);
+        pair_operand<N, S>(p, pq, q);
+#pragma unroll
+        for (int h = 0; h <= S; ++h) {
+            const double w = fma(-c, v[h], p[h]);
+            b[h] = fma(-cb, v[h], b[h]);
+            pair_axpy<N, S>(A[h], pq, -v[h]);
+            pair_axpy<N, S>(A[h], vq, -w);
+        }
+    }
+}
+
+// back_phase for the reflectors of the pivot columns in slot S.
+template <int N, int S, typename R>
+__device__ __forceinline__ void pair_back_phase(double (&G)[3][DirectP<N>::COLS], double (&hv)[3],
+                                                const R& vs, int lane) {
+    const int r = lane & 15, q = lane >> 4 & 1;
+    constexpr int HI = 16 * S + 16 < N ? 16 * S + 16 : N;
+#pragma unroll 1
+    for (int n = S > 0 ? 16 * S + 1 : 3; n <= HI; ++n) {
+        double v[3] = {0.0, 0.0, 0.0}, p[3], vq[3], pq[3];
+#pragma unroll
+        for (int h = 0; h <= S; ++h) v[h] = vs.get(n, r + 16 * h);
+        pair_operand<N, S>(v, vq, q);
+        double c = 0.0, ch = 0.0;
+#pragma unroll
+        for (int h = 0; h < 3; ++h) {
+            p[h] = pair_dot<N, S>(G[h], vq);
+            if (h <= S) {
+                c = fma(v[h], p[h], c);
+                ch = fma(v[h], hv[h], ch);
+            }
+        }
+        c = row_sum(c);
+        ch = row_sum(ch);
+        pair_operand<N, 2>(p, pq, q);
+#pragma unroll
+        for (int h = 0; h < 3; ++h) {
+            if (h <= S) {
+                hv[h] = fma(-ch, v[h], hv[h]);
+                pair_axpy<N, 2>(G[h], pq, -v[h]);
+                pair_axpy<N, S>(G[h], vq, -fma(-c, v[h], p[h]));
+            } else {
+                pair_axpy<N, S>(G[h], vq, -p[h]);
+            }
+        }
+    }
+}
+
+// Two poles' entries of the columns of slot HC for a row of slot H: sa, sb the row's values at
+// the column before them, own: this lane's diagonal column in the slot, if any.
+template <int W, int K>
+__device__ __forceinline__ void pair_chain(double* a, const double* g, double wa, double wb,
+                                           double& pa, double& pb, int pr, int own) {
+    double ua[4], ub[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const bool o = own == K + k;
+        ua[k] = o ? wa : 0.0;
+        ub[k] = o ? wb : 0.0;
+    }
+    if (pr == 0) fmac_chain<0, 4>(ua, ub, g + K, pa, pb);
+    else fmac_chain<2, 4>(ua, ub, g + K, pa, pb);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        a[K + k] += ua[k] + ub[k];
+        // summed here (see wave_chain)
+        asm volatile("" : "+v"(a[K + k]));
+    }
+    pa = ua[3];
+    pb = ub[3];
+    if constexpr (K + 4 < W) pair_chain<W, K + 4>(a, g, wa, wb, pa, pb, pr, own);
+}
+
+// The same in the slots after the row's own.
+template <int W, int K>
+__device__ __forceinline__ void pair_chain_on(double* a, const double* g, double& pa, double& pb,
+                                              int pr) {
+    double ua[4] = {0.0, 0.0, 0.0, 0.0}, ub[4] = {0.0, 0.0, 0.0, 0.0};
+    if (pr == 0) fmac_chain<0, 4>(ua, ub, g + K, pa, pb);
+    else fmac_chain<2, 4>(ua, ub, g + K, pa, pb);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        a[K + k] += ua[k] + ub[k];
+        asm volatile("" : "+v"(a[K + k]));
+    }
+    pa = ua[3];
+    pb = ub[3];
+    if constexpr (K + 4 < W) pair_chain_on<W, K + 4>(a, g, pa, pb, pr);
+}
+
+// ta += bcast(P, pr) sa, tb += bcast(P, pr + 1) sb
+__device__ __forceinline__ void pair_scale(double& ta, double& tb, double P, double sa, double sb,
+                                           int pr) {
+    if (pr == 0) {
+        fmac_axpy<0, 1>(&ta, P, sa);
+        fmac_axpy<1, 1>(&tb, P, sb);
+    } else {
+        fmac_axpy<2, 1>(&ta, P, sa);
+        fmac_axpy<3, 1>(&tb, P, sb);
+    }
+}
+
+// sym_direct for the two nodes of a wavefront (A: half rows as above; b by rows, in both
+// lane rows).  lds: 2 * DirectP<N>::kNodeDoubles doubles.
+template <int N, bool ROOT, typename R>
+__device__ __forceinline__ bool sym_direct_pair(double (&A)[3][DirectP<N>::COLS], double (&b)[3],
+                                                double ia, double scale, double* lds, const R& vs,
+                                                int lane) {
+    using D = DirectP<N>;
+    constexpr int ZS = D::ZS;
+    const int r = lane & 15, q = lane >> 4 & 1;
+    double* zt = lds + (size_t)(lane >> 5) * D::kNodeDoubles;  // [12][ZS]
+    double* et = zt + 12 * ZS;
+    double d[3] = {0.0, 0.0, 0.0}, e[3] = {0.0, 0.0, 0.0};
+    pair_tri_phase<N, 2, 1>(A, d, e, b, vs, lane);
+    pair_tri_phase<N, 2, 0>(A, d, e, b, vs, lane);
+    pair_tri_phase<N, 1, 1>(A, d, e, b, vs, lane);
+    pair_tri_phase<N, 1, 0>(A, d, e, b, vs, lane);
+    pair_tri_phase<N, 0, 1>(A, d, e, b, vs, lane);
+    pair_tri_phase<N, 0, 0>(A, d, e, b, vs, lane);
+    {
+        // rows 0 and 1 are left: d_0, d_1, e_0
+        const double t0 = pair_sum(q == 0 ? (r == 0 ? A[0][0] : A[0][1]) : 0.0);
+        const double t1 = pair_sum(q == 0 ? A[0][1] : 0.0);
+        d[0] = r < 2 ? t0 : d[0];
+        e[0] = r == 0 ? t1 : e[0];
+    }
+    bool finite = true;
+    float f2 = 0.0f;
+#pragma unroll
+    for (int h = 0; h < 3; ++h) {
+        d[h] *= ia;
+        e[h] *= ia;
+        finite = finite && fabs(d[h]) + fabs(e[h]) < 1e300;
+        const float df = (float)d[h], ef = (float)e[h];
+        f2 += df * df + 2.0f * ef * ef;
+    }
+    const int cls = pole_class<false>(f2);
+    const int p0 = kPoleOffset[cls], np = kPoleOffset[cls + 1] - p0;
+#pragma unroll
+    for (int h = 0; h < 3; ++h)
+#pragma unroll
+        for (int c = 0; c < D::COLS; ++c) A[h][c] = 0.0;
+    double hv[3] = {0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int pb = 0; pb < np; pb += D::kPoles) {
+        const int pi = pb + r < np && r < D::kPoles ? p0 + pb + r : -1;
+        const double t2 = pi >= 0 ? kSqrtPoles[pi < 0 ? 0 : pi].t2 : 0.0;
+        double cw = pi >= 0 ? kSqrtPoles[pi < 0 ? 0 : pi].c * scale : 0.0;
+        if constexpr (ROOT) cw *= 1.0 + t2;
+        const double base = 1.0 + t2;
+        const bool inv = r == D::kPoles;
+        const bool keep = q == 0 && r <= D::kPoles;  // (both lane rows compute the same)
+        double rg = 0.0, y = 0.0;
+        // as in sym_direct: val_j = 1 / gamma_j (z table), g_j (e table), downwards
+        auto down = [&](auto self, auto J) -> void {
+            constexpr int j = decltype(J)::value;
+            const double dj = row_bcast<j % 16>(d[j / 16]), bj = row_bcast<j % 16>(b[j / 16]);
+            double gam = base + dj, gj = 0.0;
+            if constexpr (j == N - 1) {
+                y = bj;
+            } else {
+                const double ej = row_bcast<j % 16>(e[j / 16]);
+                gj = -ej * rg;
+                gam = fma(gj, ej, gam);
+                y = fma(gj, y, bj);
+            }
+            rg = fast_rcp(gam);
+            if (keep) {
+                zt[r * ZS + j] = inv ? y * rg : rg;
+                et[r * ZS + j] = gj;
+            }
+            if constexpr (j % 8 == 0) __builtin_amdgcn_sched_barrier(0);
+            if constexpr (j > 0) self(self, std::integral_constant<int, j - 1>());
+        };
+        down(down, std::integral_constant<int, N - 1>());
+        wave_lds_sync();
+        const int row = (r <= D::kPoles ? r : 0) * ZS;
+        {
+            const double cx = inv ? 1.0 : cw;
+            double z = 0.0, m = 0.0;
+#pragma unroll 8
+            for (int j = 0; j < N; ++j) {
+                const double gj = et[row + j];
+                z = fma(m, z, zt[row + j]);
+                if (keep) zt[row + j] = z * cx;
+                m = inv ? gj : gj * gj;
+            }
+        }
+        wave_lds_sync();
+        // upwards again: the factors into this lane row's columns, the value of each row at
+        // the end of its own block of columns (e table), the products over the blocks between
+        // two of this lane row's
+        double gc[D::COLS], P[2] = {0.0, 0.0};
+        {
+            double sp = 1.0;  // product of the factors from column j to its block's end
+            auto up = [&](auto self, auto J) -> void {
+                constexpr int j = decltype(J)::value;
+                constexpr int w = D::width(j / 16);
+                constexpr bool last = j % 16 % w == w - 1;
+                const double gj = et[row + j];  // the factor into column j + 1
+                if constexpr (j + 1 < N) {
+                    constexpr int h1 = (j + 1) / 16, w1 = D::width(h1), q1 = (j + 1) % 16 / w1;
+                    constexpr int c1 = 8 * h1 + (j + 1) % 16 % w1;
+                    if constexpr (q1 == 1) gc[c1] = gj;
+                    else gc[c1] = q ? gc[c1] : gj;
+                }
+                // the block after this one ends its product at j = its first column - 1
+                if constexpr (last && j + 1 < N) {
+                    constexpr int blk = 2 * ((j + 1) / 16) + (j + 1) % 16 / D::width((j + 1) / 16);
+                    const double prod = gj * sp;
+                    if constexpr (blk == 1) P[0] = q ? P[0] : prod;
+                    if constexpr (blk == 2) P[0] = q ? prod : P[0];
+                    if constexpr (blk == 3) P[1] = q ? P[1] : prod;
+                    if constexpr (blk == 4) P[1] = q ? prod : P[1];
+                }
+                sp = last ? 1.0 : gj * sp;
+                if (keep) et[row + j] = zt[row + j] * sp;
+                if constexpr (j == 0) gc[0] = q ? gc[0] : 0.0;
+                if constexpr (j % 8 == 0) __builtin_amdgcn_sched_barrier(0);
+                if constexpr (j > 0) self(self, std::integral_constant<int, j - 1>());
+            };
+            up(up, std::integral_constant<int, N - 1>());
+        }
+        wave_lds_sync();
+#pragma unroll
+        for (int h = 0; h < 3; ++h)
+            hv[h] = r + 16 * h < N ? zt[D::kPoles * ZS + r + 16 * h] : 0.0;
+        const int left = np - pb < D::kPoles ? np - pb : D::kPoles;
+#pragma unroll 1
+        for (int k = 0; k < left; k += 4) {
+#pragma unroll
+            for (int pr = 0; pr < 4; pr += 2) {
+                const int pa = k + pr, pq = k + pr + 1;
+                const bool on = pq != D::kPoles;  // (the solution's lane is no pole)
+                auto rows = [&](auto self, auto H) -> void {
+                    constexpr int h = decltype(H)::value, w = D::width(h);
+                    const int i = r + 16 * h;
+                    const int at = i < N ? i : 0;
+                    const bool in = i < N;
+                    double wa = zt[pa * ZS + at], wb = zt[pq * ZS + at];
+                    double ea = et[pa * ZS + at], eb = et[pq * ZS + at];
+                    wa = in ? wa : 0.0;
+                    wb = in && on ? wb : 0.0;
+                    eb = on ? eb : 0.0;
+                    // the lane row's block in the rows' own slot
+                    const bool enter = q == 1 && r < w;
+                    double sa = enter ? ea : 0.0, sb = enter ? eb : 0.0;
+                    int own = r - w * q;
+                    asm volatile("" : "+v"(own));
+                    pair_chain<w, 0>(A[h] + 8 * h, gc + 8 * h, wa, wb, sa, sb, pr, own);
+                    if constexpr (h < 2) {
+                        double ta = 0.0, tb = 0.0;
+                        pair_scale(ta, tb, P[h], sa, sb, pr);
+                        const bool late = q == 0 && r >= w;
+                        sa = late ? ea : ta;
+                        sb = late ? eb : tb;
+                        pair_chain_on<D::width(h + 1), 0>(A[h] + 8 * (h + 1), gc + 8 * (h + 1), sa,
+                                                          sb, pr);
+                    }
+                    if constexpr (h == 0) {
+                        double ta = 0.0, tb = 0.0;
+                        pair_scale(ta, tb, P[1], sa, sb, pr);
+                        sa = ta;
+                        sb = tb;
+                        pair_chain_on<D::width(2), 0>(A[0] + 16, gc + 16, sa, sb, pr);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (h < 2) self(self, std::integral_constant<int, h + 1>());
+                };
+                rows(rows, std::integral_constant<int, 0>());
+            }
+            auto turn = [](double& v) {
+                const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x12C, 0xF, 0xF, true);
+                const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x12C, 0xF, 0xF, true);
+                v = __hiloint2double(hi, lo);
+            };
+#pragma unroll
+            for (int c = 0; c < D::COLS; ++c) turn(gc[c]);
+            turn(P[0]);
+            turn(P[1]);
+        }
+        wave_lds_sync();
+    }
+    // lower triangle, one slot of rows at a time through LDS
+    auto mirror = [&](auto self, auto SS) -> void {
+        constexpr int s = decltype(SS)::value, w = D::width(s);
+#pragma unroll
+        for (int c = 8 * s; c < D::COLS; ++c)
+            if (16 * s + r < N) zt[r * ZS + (q ? D::elem(c, 1) : D::elem(c, 0))] = A[s][c];
+        wave_lds_sync();
+        if (16 * s + r < N) zt[r * ZS + 16 * s + r] = 0.0;
+        wave_lds_sync();
+#pragma unroll
+        for (int h = s; h < 3; ++h) {
+            const int i = 16 * h + r;
+#pragma unroll
+            for (int k = 0; k < w; ++k) {
+                const double t = zt[(w * q + k) * ZS + (i < N ? i : 0)];
+                A[h][8 * s + k] += i < N ? t : 0.0;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        wave_lds_sync();
+        if constexpr (s < 2) self(self, std::integral_constant<int, s + 1>());
+    };
+    mirror(mirror, std::integral_constant<int, 0>());
+#pragma unroll
+    for (int h = 0; h < 3; ++h) b[h] = hv[h];
+    pair_back_phase<N, 0>(A, b, vs, lane);
+    pair_back_phase<N, 1>(A, b, vs, lane);
+    pair_back_phase<N, 2>(A, b, vs, lane);
     return finite;
 }
 
