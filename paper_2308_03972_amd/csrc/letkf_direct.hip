@@ -468,7 +468,11 @@ __device__ __forceinline__ void ens_direct_wave(const AnalysisParams& p, int nod
 template <int N, typename T>
 __device__ __forceinline__ void ens_direct_node(const AnalysisParams& p, int node0) {
     if (node0 >= p.nx * p.ny) return;  // uniform over the wavefront
-    if constexpr (kRows16<N>) ens_direct_body<N, T>(p, node0);
+    if constexpr (N == 8) {
+        // (half the size for ensembles of up to four members)
+        if (p.members <= 4) ens_direct_body<4, T>(p, node0);
+        else ens_direct_body<8, T>(p, node0);
+    } else if constexpr (kRows16<N>) ens_direct_body<N, T>(p, node0);
     else ens_direct_wave<N, T>(p, node0);
 }
 

@@ -158,7 +158,7 @@ __device__ __forceinline__ double fast_rcp(double x) {
 
 template <int N>
 struct Direct {
-    static_assert(N >= 8 && N <= 32 && N % 2 == 0, "one or two matrix rows per lane");
+    static_assert(N >= 4 && N <= 32 && N % 2 == 0, "one or two matrix rows per lane");
     static constexpr int NS = (N + 15) / 16;      // matrix rows per lane
     static constexpr int ZS = N + 1;              // stride of the LDS tables (odd)
     static constexpr int kNodeDoubles = 16 * ZS;  // per node: pole table, then the transposes
