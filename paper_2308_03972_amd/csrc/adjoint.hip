@@ -380,14 +380,14 @@ hipError_t launch_adjoint_step(const void* fstate, const double* lam_in, double*
 // shapes with one block per CU at most, the best by a fit of those sweeps: a launch 2.5 us, a
 // step 1.5 us and 2.5 us more per 1024 threads of the block.
 StepPlan adjoint_plan(LbmDims d, int interval, int capacity) {
-    StepPlan best{0, 0, 0, 0};
+    StepPlan best{};
     if (interval < 2 || (double)d.nx * d.ny * d.members > 7e4) return best;
     double least = 1e30;
     for (int mg = 1; mg <= 4 && mg <= d.members; mg *= 2)
         for (int k = 2; k <= 6 && k <= interval; ++k)
             for (int tile = 4; tile <= 24; tile += 2) {
-                const StepPlan pl{k, tile + 2 * (k - 1), mg, 1};
-                const int threads = pl.region * pl.region * mg;
+                const StepPlan pl{k, tile + 2 * (k - 1), tile + 2 * (k - 1), mg, 1};
+                const int threads = pl.rx * pl.ry * mg;
                 if (threads > 1024 || tile_blocks(d, pl) > std::min(256, capacity)) continue;
                 const double t = 2.5 / k + 1.5 + 2.5 * threads / 1024;
                 if (t < least) {
@@ -404,7 +404,7 @@ hipError_t launch_adjoint_tile_t(const void* fhi, const void* flast, size_t stri
                                  const double* lam_in, double* lam_out, const double* force,
                                  LbmDims d, double tau0, double K, double mu, double* k_partial,
                                  int capacity, const StepPlan& pl, int steps, hipStream_t s) {
-    const int R = pl.region - 2 * (pl.steps - steps);
+    const int R = pl.rx - 2 * (pl.steps - steps);
     const int tile = R - 2 * (steps - 1);
     const int blocks = tile_blocks(d, pl);
     const int threads = (R * R * pl.members + kWave - 1) / kWave * kWave;

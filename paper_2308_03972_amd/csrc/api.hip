@@ -70,6 +70,7 @@ struct Ctx {
     bool check_every_cycle = false;
     // precision form: the apply kernels' contractions on BF16 matrix cores
     bool mfma_transform = false;
+    StepPlans plans{};  // the tiled multi-step launches, laid out once
     char* ws;
     Layout L;
     // arguments of the last misfit forward sweep (its checkpoints feed the
@@ -516,6 +517,7 @@ lbmletkf_status lbmletkf_create(const lbmletkf_lbm_params* lbm, const lbmletkf_o
     c->obs = *obs;
     c->obs.points = nullptr;
     c->dims = {lbm->nx, lbm->ny, lbm->members};
+    c->plans = step_plans(c->dims, lbm->storage);
     c->nobs = obs->n_points * obs->nvar;
     c->lmax = lmax;
     c->route = route;
@@ -657,10 +659,9 @@ lbmletkf_status lbm_ensemble_step(lbmletkf_ctx* ctx, void* d_f, int32_t nsteps, 
     // several steps per launch where the plan gives them, spread evenly over an even
     // number of launches (the result then lies in d_f and needs no copy); else pairs of
     // steps where the ensemble allows it, a single step for an odd remainder
-    const StepPlan plan = step_plan(c->dims, c->storage());
+    const StepPlans& plans = c->plans;
     const bool two = two_step_supported(c->dims, c->storage());
-    int launches = plan.steps > 1 && nsteps > 1 ? (nsteps + plan.steps - 1) / plan.steps : 0;
-    if (launches & 1) ++launches;
+    int launches = plans.most > 1 && nsteps > 1 ? plan_launches(plans, nsteps, true) : 0;
     for (int k = 0; k < nsteps;) {
         int n = (two && nsteps - k >= 2) ? 2 : 1;
         hipError_t e;
@@ -669,7 +670,7 @@ lbmletkf_status lbm_ensemble_step(lbmletkf_ctx* ctx, void* d_f, int32_t nsteps, 
             --launches;
             StageTimer t(c, kStageCollide, s, kPerLaunch, n);
             e = launch_stream_collide_tile(a, b, c->force(), c->dims, c->lbm.tau0, c->lbm.cs,
-                                           c->lbm.mu, c->storage(), s, plan, n);
+                                           c->lbm.mu, c->storage(), s, plans.p[n], n);
         } else {
             StageTimer t(c, kStageCollide, s, kPerLaunch, n);
             e = n == 2 ? launch_stream_collide2(a, b, c->force(), c->dims, c->lbm.tau0, c->lbm.cs,
@@ -926,18 +927,19 @@ struct Sweep {
 // ensemble allows it (the same bits as single steps).
 lbmletkf_status segment_steps(Ctx* c, const Sweep& sw, int t, int steps, int last, double cs,
                               hipStream_t s) {
-    const StepPlan plan = step_plan(c->dims, c->storage());
-    const int most = plan.steps > 1 ? plan.steps : (two_step_supported(c->dims, c->storage()) ? 2 : 1);
-    int launches = (last + most - 1) / most;
+    const StepPlans& plans = c->plans;
+    const bool tiles = plans.most > 1;
+    const int most = two_step_supported(c->dims, c->storage()) ? 2 : 1;
+    int launches = tiles && last > 0 ? plan_launches(plans, last, false) : 0;
     for (int j = 1; j <= last; --launches) {
         const void* in = j == 1 ? sw.ckpt(t - 1) : sw.seg(j - 1);
-        const int n = plan.steps > 1 ? (last - j + launches) / launches : std::min(most, last - j + 1);
+        const int n = tiles ? (last - j + launches) / launches : std::min(most, last - j + 1);
         void* out = j + n - 1 == steps ? sw.ckpt_mut(t) : sw.seg(j + n - 1);
         StageTimer tm(c, kStageCollide, s, kPerLaunch, n);
         hipError_t e;
-        if (plan.steps > 1 && n > 1)
+        if (tiles && n > 1)
             e = launch_stream_collide_tile(in, out, c->force(), c->dims, c->lbm.tau0, cs, c->lbm.mu,
-                                           c->storage(), s, plan, n, sw.seg(j), sw.sb);
+                                           c->storage(), s, plans.p[n], n, sw.seg(j), sw.sb);
         else if (n == 2)
             e = launch_stream_collide2(in, out, c->force(), c->dims, c->lbm.tau0, cs, c->lbm.mu,
                                        c->storage(), s, sw.seg(j));
@@ -955,18 +957,19 @@ lbmletkf_status segment_steps(Ctx* c, const Sweep& sw, int t, int steps, int las
 // same bits as single steps); states in between pass through the segment buffers.
 lbmletkf_status segment_advance(Ctx* c, const Sweep& sw, int t, int steps, double cs,
                                 hipStream_t s) {
-    const StepPlan plan = step_plan(c->dims, c->storage());
-    const int most = plan.steps > 1 ? plan.steps : (two_step_supported(c->dims, c->storage()) ? 2 : 1);
-    int launches = (steps + most - 1) / most;
+    const StepPlans& plans = c->plans;
+    const bool tiles = plans.most > 1;
+    const int most = two_step_supported(c->dims, c->storage()) ? 2 : 1;
+    int launches = tiles ? plan_launches(plans, steps, false) : 0;
     const void* in = sw.ckpt(t - 1);
     for (int j = 0; j < steps; --launches) {
-        const int n = plan.steps > 1 ? (steps - j + launches - 1) / launches : std::min(most, steps - j);
+        const int n = tiles ? (steps - j + launches - 1) / launches : std::min(most, steps - j);
         void* out = j + n == steps ? sw.ckpt_mut(t) : sw.seg(j + n);
         StageTimer tm(c, kStageCollide, s, kPerLaunch, n);
         hipError_t e;
-        if (plan.steps > 1 && n > 1)
+        if (tiles && n > 1)
             e = launch_stream_collide_tile(in, out, c->force(), c->dims, c->lbm.tau0, cs, c->lbm.mu,
-                                           c->storage(), s, plan, n);
+                                           c->storage(), s, plans.p[n], n);
         else if (n == 2)
             e = launch_stream_collide2(in, out, c->force(), c->dims, c->lbm.tau0, cs, c->lbm.mu,
                                        c->storage(), s);

@@ -139,12 +139,21 @@ bool two_step_supported(LbmDims d, int storage);
 hipError_t launch_stream_collide2(const void* fin, void* fout, const double* force, LbmDims d,
                                   double tau0, double cs, double mu, int storage, hipStream_t s,
                                   void* fmid = nullptr);
-// Up to `steps` steps in one launch on regions of `region`^2 nodes and `members` members
-// per block, `items` per thread (any ensemble size); steps = 0: not the faster way.
+// Up to `steps` steps in one launch on regions of rx x ry nodes and `members` members
+// per block, `items` per thread (any ensemble size).
 struct StepPlan {
-    int steps, region, members, items;
+    int steps, rx, ry, members, items;
 };
-StepPlan step_plan(LbmDims d, int storage);
+// The plan of a launch of n <= most steps and its expected time (most = 0: none), and the
+// number of launches (even, if asked for) that takes `steps` steps fastest, spread evenly.
+constexpr int kMostSteps = 6;
+struct StepPlans {
+    int most;
+    StepPlan p[kMostSteps + 1];
+    double us[kMostSteps + 1];
+};
+StepPlans step_plans(LbmDims d, int storage);
+int plan_launches(const StepPlans& plans, int steps, bool even);
 // `steps` <= pl.steps steps; with fmid != NULL the states after steps 1 .. steps - 1 go to
 // fmid, fmid + mid_bytes, ...  Same arithmetic and rounding as single steps.
 hipError_t launch_stream_collide_tile(const void* fin, void* fout, const double* force, LbmDims d,
@@ -366,8 +375,8 @@ hipError_t launch_misfit(const void* f, const int* pts, int npts, int nvar, cons
 // fhi - stride_bytes, .., flast.  k_partial: tile_blocks() partial sums.
 StepPlan adjoint_plan(LbmDims d, int interval, int capacity);
 inline int tile_blocks(LbmDims d, const StepPlan& pl) {
-    const int tile = pl.region - 2 * (pl.steps - 1);
-    return ((d.nx + tile - 1) / tile) * ((d.ny + tile - 1) / tile) *
+    const int tx = pl.rx - 2 * (pl.steps - 1), ty = pl.ry - 2 * (pl.steps - 1);
+    return ((d.nx + tx - 1) / tx) * ((d.ny + ty - 1) / ty) *
            ((d.members + pl.members - 1) / pl.members);
 }
 hipError_t launch_adjoint_tile(const void* fhi, const void* flast, size_t stride_bytes,

@@ -19,6 +19,8 @@
 //     tau^2 - tau0 tau - 9 sqrt(2) C_s^2 |Pi| / (2 rho) = 0,
 // |Pi| = sqrt(Pi_xx^2 + Pi_yy^2 + 2 Pi_xy^2), whose positive root is used.
 // The momentum flux of f^eq is rho/3 I + rho u u, so Pi needs no f^eq.
+#include <algorithm>
+
 #include "common.h"
 #include "device_util.h"
 
@@ -439,8 +441,8 @@ stream_collide2_batch_kernel(const LbmTask* __restrict__ tasks, int ntasks) {
 }
 
 // ---------------------------------------------------------------------------
-// Several steps per launch on square regions of any size and any member count: a block
-// takes MG members of a region of R x R nodes, pulls the first step from HBM and keeps
+// Several steps per launch on regions of any size and any member count: a block
+// takes MG members of a region of RX x RY nodes, pulls the first step from HBM and keeps
 // the results in LDS; each further step loses the region's outer ring, and after k steps
 // the inner T x T nodes (T = R - 2 (k - 1)) are written.  For ensembles that the 128-byte
 // member blocks above do not fit, and for problems so small that a step's launch costs
@@ -450,24 +452,25 @@ stream_collide2_batch_kernel(const LbmTask* __restrict__ tasks, int ntasks) {
 // between two barriers.  Same arithmetic and rounding as single steps, bit for bit.
 // Bound by latency (a launch, one round of loads, k barriers) on small problems and by
 // L2 requests of 32-byte pieces and FP64 issue on large ones (4.0 TB/s of the kernel's own
-// bytes at 400^2 x 24).  Shapes: step_plan below.
+// bytes at 400^2 x 24).  Shapes: step_plans below.
 // ---------------------------------------------------------------------------
 template <typename T, int V, int I>
 __global__ __launch_bounds__(1024) void stream_collide_tile_kernel(
     const T* __restrict__ fin, T* __restrict__ fout, const double* __restrict__ force, int nx,
-    int ny, int members, double tau0, double smag, double mu, int R, int MG, int steps,
+    int ny, int members, double tau0, double smag, double mu, int RX, int RY, int MG,
+    int steps,
     T* __restrict__ fmid, size_t mid_stride) {
     extern __shared__ char lds_raw[];
-    T* const mid = reinterpret_cast<T*>(lds_raw);  // [9][R * R][MG]
+    T* const mid = reinterpret_cast<T*>(lds_raw);  // [9][RX * RY][MG]
     typedef T vec __attribute__((ext_vector_type(V)));
-    const int halo = steps - 1, tile = R - 2 * halo;
+    const int halo = steps - 1, tile_x = RX - 2 * halo, tile_y = RY - 2 * halo;
     const int groups = (members + MG - 1) / MG;
-    const int tiles_x = (nx + tile - 1) / tile;
+    const int tiles_x = (nx + tile_x - 1) / tile_x;
     const int b = dev::xcd_remap(blockIdx.x, gridDim.x);  // the groups of a tile share lines
     const int t = b / groups, m0 = (b - t * groups) * MG;
-    const int x0 = (t % tiles_x) * tile, y0 = (t / tiles_x) * tile;
+    const int x0 = (t % tiles_x) * tile_x, y0 = (t / tiles_x) * tile_y;
     const int per = MG / V;  // items per node
-    const int plane = nx * ny, rr = R * R;
+    const int plane = nx * ny, rr = RX * RY;
     int rx[I], ry[I], m[I];
     bool on[I];
     size_t own[I];
@@ -478,8 +481,8 @@ __global__ __launch_bounds__(1024) void stream_collide_tile_kernel(
         const int it = threadIdx.x + i * blockDim.x;
         const int node_r = it / per;
         m[i] = (it - node_r * per) * V;
-        ry[i] = node_r / R;
-        rx[i] = node_r - ry[i] * R;
+        ry[i] = node_r / RX;
+        rx[i] = node_r - ry[i] * RX;
         on[i] = node_r < rr && m0 + m[i] < members;
         int gx = (x0 - halo + rx[i]) % nx, gy = (y0 - halo + ry[i]) % ny;
         gx = gx < 0 ? gx + nx : gx;
@@ -502,10 +505,10 @@ __global__ __launch_bounds__(1024) void stream_collide_tile_kernel(
         }
     }
     for (int s = 1;; ++s) {
-        const int lo = s - 1, hi = R - lo;  // this step's nodes
+        const int lo = s - 1, hx = RX - lo, hy = RY - lo;  // this step's nodes
 #pragma unroll
         for (int i = 0; i < I; ++i) {
-            on[i] = on[i] && rx[i] >= lo && rx[i] < hi && ry[i] >= lo && ry[i] < hi;
+            on[i] = on[i] && rx[i] >= lo && rx[i] < hx && ry[i] >= lo && ry[i] < hy;
             if (!on[i]) continue;
 #pragma unroll
             for (int k = 0; k < V; ++k) {
@@ -515,8 +518,8 @@ __global__ __launch_bounds__(1024) void stream_collide_tile_kernel(
                     collide_node_dev(f[i][k], (float)tau0, (float)smag, (float)fx[i], (float)fy[i],
                                      (float)mu);
             }
-            const bool inner = rx[i] >= halo && rx[i] < halo + tile && ry[i] >= halo &&
-                               ry[i] < halo + tile && x0 + rx[i] - halo < nx &&
+            const bool inner = rx[i] >= halo && rx[i] < halo + tile_x && ry[i] >= halo &&
+                               ry[i] < halo + tile_y && x0 + rx[i] - halo < nx &&
                                y0 + ry[i] - halo < ny;
             T* const dst = s == steps ? fout : (fmid ? fmid + (size_t)(s - 1) * mid_stride : nullptr);
             if (inner && dst) {
@@ -539,19 +542,20 @@ __global__ __launch_bounds__(1024) void stream_collide_tile_kernel(
                 vec v;
 #pragma unroll
                 for (int k = 0; k < V; ++k) v[k] = f[i][k][a];
-                *reinterpret_cast<vec*>(mid + ((size_t)a * rr + ry[i] * R + rx[i]) * MG + m[i]) = v;
+                *reinterpret_cast<vec*>(mid + ((size_t)a * rr + ry[i] * RX + rx[i]) * MG + m[i]) = v;
             }
         }
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < I; ++i) {
             // the next step's nodes: their neighbours are this step's
-            const bool next = on[i] && rx[i] > lo && rx[i] < hi - 1 && ry[i] > lo && ry[i] < hi - 1;
+            const bool next = on[i] && rx[i] > lo && rx[i] < hx - 1 && ry[i] > lo &&
+                              ry[i] < hy - 1;
             if (!next) continue;
 #pragma unroll
             for (int a = 0; a < 9; ++a) {
                 const vec v = *reinterpret_cast<const vec*>(
-                    mid + ((size_t)a * rr + (ry[i] - cy_of(a)) * R + rx[i] - cx_of(a)) * MG + m[i]);
+                    mid + ((size_t)a * rr + (ry[i] - cy_of(a)) * RX + rx[i] - cx_of(a)) * MG + m[i]);
 #pragma unroll
                 for (int k = 0; k < V; ++k) f[i][k][a] = v[k];
             }
@@ -750,40 +754,176 @@ bool two_step_supported(LbmDims d, int storage) {
     return d.members % kTwoMG == 0;
 }
 
-// The tiled multi-step launch of an ensemble, or k = 0 where pairs of steps on 128-byte
-// member blocks are as fast or faster.  Chosen from a sweep of every (members per block,
-// region, steps, items per thread) at grids 24^2 .. 400^2 and 1 .. 64 members; P =
-// node-members.  us per step, FP64 unless noted (single step / pair / this):
-//   256^2 x 1 11.2 / - / 2.6, 48^2 x 8 5.2 / - / 1.8, 150 x 97 x 20 10.6 / - / 7.3,
-//   256^2 x 24 44 / - / 28, 400^2 x 24 FP32 76 / - / 36;
-//   16 | M: 24^2 x 16 3.9 / 3.0 / 1.6, 48^2 x 32 4.8 / 3.5 / 2.9, but 96^2 x 16 5.8 / 3.7 / 3.7
-//   and 160^2 x 32 20.4 / 15.3 / 16: pairs from P = 1e5 on.  FP32 with 16 members (64-byte
-//   member blocks as pairs) stays here at any size: 256^2 x 16 17.8 / 14.2 / 10.6.
-// Small problems take few members and long chains (more blocks, fewer launches); large
-// ones four members (32 bytes, eight in FP32) and k = 3, where a longer chain's halo costs
-// more than it saves.
-StepPlan step_plan(LbmDims d, int storage) {
+namespace {
+// Time (us) of a multi-step launch, fitted to 6,700 timed shapes on problems of 24^2 .. 512 x 400
+// nodes and 1 .. 64 members (median error 8%): a launch, a step of a round of blocks (two
+// per CU where LDS and the 16 wavefronts of 128 registers allow), the wavefronts a CU runs in
+// all rounds once and per step, in thousands the 64-byte and 128-byte lines a CU touches
+// and the bytes it moves, and in MB all blocks' bytes and 128-byte lines.
+struct TileFit {
+    double launch, round_step, wave, wave_step, lines64, lines128, bytes, all_bytes, all_lines;
+};
+constexpr TileFit kTileFit[3][2] = {  // FP64, FP32, FP32 pairs of members; items per thread
+    {{3.15, 0.436, 0.0, 0.0688, 0.207, 0.0676, 0.00418, 0.0565, 0.0062},
+     {4.38, 0.602, 0.0, 0.0558, 0.279, 0.0, 0.0, 0.0546, 0.0112}},
+    {{4.48, 0.322, 0.0, 0.0240, 0.0307, 0.0, 0.0296, 0.0135, 0.00352},
+     {2.86, 0.940, 0.0, 0.0240, 0.136, 0.0, 0.0288, 0.0346, 0.00241}},
+    {{4.73, 0.252, 0.0, 0.0690, 0.202, 0.0, 0.0, 0.0485, 0.00822},
+     {3.78, 1.19, 0.0339, 0.0396, 0.245, 0.0, 0.0, 0.0399, 0.0126}}};
+constexpr int kMostTileLds = 80 * 1024;  // two blocks per CU
+
+// Lines of `line` bytes that a block's members of one population touch, mean over the
+// rows' alignments and the member groups.
+double lines_touched(int members, int mg, int elem, int line) {
+    int total = 0, n = 0;
+    for (int row = 0; row < 32; ++row)
+        for (int m0 = 0; m0 < members; m0 += mg, ++n) {
+            const int first = (row * members + m0) * elem;
+            const int last = first + (members - m0 < mg ? members - m0 : mg) * elem - 1;
+            total += last / line - first / line + 1;
+        }
+    return (double)total / n;
+}
+
+struct TileCost {
+    int members, elem, V, mg, groups;
+    const TileFit* fit;  // [items per thread - 1]
+    double l64, l128;
+    TileCost(LbmDims d, int storage, int V_, int mg_)
+        : members(d.members), elem((int)state_elem_bytes(storage)), V(V_), mg(mg_),
+          groups((d.members + mg_ - 1) / mg_),
+          fit(kTileFit[V_ == 2 ? 2 : (storage == kStoreF32Dev ? 1 : 0)]),
+          l64(lines_touched(d.members, mg_, elem, 64)),
+          l128(lines_touched(d.members, mg_, elem, 128)) {}
+    // us per step of a launch of pl.steps, or a large number where it does not fit
+    double operator()(LbmDims d, const StepPlan& pl) const {
+        const int tx = pl.rx - 2 * (pl.steps - 1), ty = pl.ry - 2 * (pl.steps - 1);
+        const int lds = 9 * pl.rx * pl.ry * mg * elem;
+        const int items = pl.rx * pl.ry * mg / V;
+        const int threads = ((items + pl.items - 1) / pl.items + kWave - 1) / kWave * kWave;
+        if (lds > kMostTileLds || threads > 1024) return 1e30;
+        const int blocks = ((d.nx + tx - 1) / tx) * ((d.ny + ty - 1) / ty) * groups;
+        const int per_cu = std::min(160 * 1024 / lds, 1024 / threads);
+        const int round = 256 * per_cu;
+        const int rounds = (blocks + round - 1) / round;
+        const int mine = blocks / round * per_cu + (blocks % round + 255) / 256;
+        const double waves = (double)mine * threads / kWave * pl.items;
+        const double rows = (double)(pl.rx * pl.ry + tx * ty) * 9;  // of one block
+        const double kb = rows * mine / 1e3, mb = rows * blocks / 1e6;
+        const TileFit& f = fit[pl.items - 1];
+        return (f.launch + f.round_step * rounds * pl.steps + waves * (f.wave + f.wave_step * pl.steps) +
+                kb * (f.lines64 * l64 + f.lines128 * l128 + f.bytes * mg * elem) +
+                mb * (f.all_bytes * mg * elem + f.all_lines * l128 * 128)) / pl.steps;
+    }
+};
+
+// A plan by size alone, from a sweep of every (members per block, square region, steps,
+// items per thread): small problems take few members and long chains, large ones four
+// members (32 bytes, eight in FP32) and k = 3, where a longer chain's halo costs more than
+// it saves.
+StepPlan square_plan(int M, double P, bool pairs) {
+    auto balanced = [&](int most) { return (M + (M + most - 1) / most - 1) / ((M + most - 1) / most); };
+    auto square = [](int k, int r, int mg, int items) { return StepPlan{k, r, r, mg, items}; };
+    if (pairs) {
+        if (M == 2) return P <= 1e5 ? square(6, 16, 2, 1) : square(4, 22, 2, 1);
+        if (P <= 2e4) return square(6, 16, 2, 1);
+        if (P <= 6.4e4) return square(5, 16, 4, 1);
+        if (P <= 1e5) return square(4, 16, 4, 1);
+        if (M % 8 == 0 && P <= 9e5) return square(P <= 2e5 ? 4 : 3, 16, 8, 1);
+        return square(4, 22, 4, 1);
+    }
+    if (P <= 1e4 || (M == 1 && P <= 2e4)) return square(6, 16, 1, 1);
+    if (M == 1) return P <= 1e5 ? square(5, 24, 1, 1) : square(4, 22, 1, 1);
+    if (P <= 3.2e4 || (M <= 3 && P <= 6.4e4)) return square(5, 16, M == 3 ? 3 : 2, 1);
+    if (M <= 3) return square(4, M == 2 ? 22 : 16, M, 1);
+    const int mg = balanced(4);
+    if (P <= 6.4e4) return square(5, 16, mg, 1);
+    if (P <= 1e5) return square(4, 16, mg, 1);
+    return square(3, 16, mg, P <= 2.2e5 ? 1 : 2);
+}
+}  // namespace
+
+// The tiled multi-step launches of an ensemble, or none where pairs of steps on 128-byte
+// member blocks are as fast or faster: 16 | M from P = 1e5 node-members on, except FP32
+// with 16 members (us per step, single / pair / tiles: 96^2 x 16 5.8 / 3.7 / 3.7, 160^2 x 32
+// 20.4 / 15.3 / 16, but 24^2 x 16 3.9 / 3.0 / 1.6 and FP32 256^2 x 16 17.8 / 14.2 / 10.6).
+// Square regions leave to chance how full the last round of blocks is, so a launch of n
+// steps takes the shape of the least fitted time, if that is 8% (the fit's error) below the
+// square one's.  Searched at the square plan's members and, but for FP32 pairs, among the
+// member counts and steps that were ever best: one member and long chains for ensembles of up
+// to three and small problems (not the smallest, one block on every other CU at most); four
+// members (or five, or half the ensemble) and up to three steps else; two in between.  us per
+// step, square / this: 32^2 x 8 1.8 / 1.5, 149 x 143 x 1 1.7 / 1.3, 150 x 97 x 20 9.0 / 8.5,
+// 170 x 110 x 6 5.0 / 3.5, 333 x 300 x 5 16 / 10.5; FP32 101 x 122 x 20 5.3 / 4.1, 201 x 249 x 3
+// 4.1 / 2.9.
+StepPlans step_plans(LbmDims d, int storage) {
     const double P = (double)d.nx * d.ny * d.members;
     const int M = d.members;
     const bool pairs = members_per_thread((int)state_elem_bytes(storage), M) == 2;
-    if (M % kTwoMG == 0 && P > 1e5 && !(pairs && M == 16)) return {0, 0, 0, 0};
-    auto balanced = [&](int most) { return (M + (M + most - 1) / most - 1) / ((M + most - 1) / most); };
-    if (pairs) {
-        if (M == 2) return P <= 1e5 ? StepPlan{6, 16, 2, 1} : StepPlan{4, 22, 2, 1};
-        if (P <= 2e4) return {6, 16, 2, 1};
-        if (P <= 6.4e4) return {5, 16, 4, 1};
-        if (P <= 1e5) return {4, 16, 4, 1};
-        if (M % 8 == 0 && P <= 9e5) return {P <= 2e5 ? 4 : 3, 16, 8, 1};
-        return {4, 22, 4, 1};
+    StepPlans out{};
+    if (M % kTwoMG == 0 && P > 1e5 && !(pairs && M == 16)) return out;
+    const int V = pairs ? 2 : 1;
+    StepPlan base = square_plan(M, P, pairs);
+    double guard[kMostSteps + 1];
+    {
+        const TileCost cost(d, storage, V, base.members);
+        for (int n = 1; n <= kMostSteps; ++n) {
+            out.us[n] = guard[n] = 1e30;
+            if (n > base.steps) continue;
+            out.p[n] = base;
+            out.p[n].steps = n;
+            out.us[n] = n * cost(d, out.p[n]);
+            guard[n] = 0.92 * out.us[n];
+        }
     }
-    if (P <= 1e4 || (M == 1 && P <= 2e4)) return {6, 16, 1, 1};
-    if (M == 1) return P <= 1e5 ? StepPlan{5, 24, 1, 1} : StepPlan{4, 22, 1, 1};
-    if (P <= 3.2e4 || (M <= 3 && P <= 6.4e4)) return {5, 16, M == 3 ? 3 : 2, 1};
-    if (M <= 3) return {4, M == 2 ? 22 : 16, M, 1};
-    const int mg = balanced(4);
-    if (P <= 6.4e4) return {5, 16, mg, 1};
-    if (P <= 1e5) return {4, 16, mg, 1};
-    return {3, 16, mg, P <= 2.2e5 ? 1 : 2};
+    auto search = [&](int mg, int k0, int k1) {
+        if (mg > M || mg % V) return;
+        const TileCost cost(d, storage, V, mg);
+        for (int k = k0; k <= k1; ++k)
+            for (int tx = 4; tx <= 32; ++tx)
+                for (int ty = 4; ty <= 32; ++ty)
+                    for (int i = 1; i <= 2; ++i) {
+                        const StepPlan pl{k, tx + 2 * (k - 1), ty + 2 * (k - 1), mg, i};
+                        const double t = k * cost(d, pl);
+                        if (t < guard[k]) {
+                            guard[k] = out.us[k] = t;
+                            out.p[k] = pl;
+                        }
+                    }
+    };
+    if (P > 5e3) search(base.members, 2, base.steps);
+    if (pairs) {
+        if (M % 10 == 0 && P > 1e6) search(10, 3, 3);
+    } else if (P > 5e3) {
+        if (M <= 3 || P < 2e4) search(1, 5, 6);
+        if (P < 2e5) search(2, 3, 5);
+        if (M == 3) search(3, 2, 3);
+        search(4, 2, 3);
+        search(5, 2, 3);
+        if (M >= 12 && M <= 24) search((M + 1) / 2, 2, 2);
+    }
+    for (int n = 1; n <= kMostSteps; ++n)
+        if (out.us[n] < 1e29) out.most = n;
+    return out;
+}
+
+int plan_launches(const StepPlans& plans, int steps, bool even) {
+    int best = 0;
+    double least = 1e30;
+    const int first = (steps + plans.most - 1) / plans.most;
+    for (int launches = first; launches <= first + 3 + first / 2; ++launches) {
+        if (even && (launches & 1)) continue;
+        if (launches > steps && best) break;
+        const int n = steps / launches, longer = steps - n * launches;  // of n + 1 steps
+        double t = 0.0;
+        if (longer) t += longer * plans.us[n + 1];
+        if (n) t += (launches - longer) * plans.us[n];
+        if (t < least) {
+            least = t;
+            best = launches;
+        }
+    }
+    return best;
 }
 
 namespace {
@@ -791,14 +931,15 @@ template <typename T, int V, int I>
 hipError_t launch_tile_t(const void* fin, void* fout, const double* force, LbmDims d, double tau0,
                          double smag, double mu, hipStream_t s, const StepPlan& pl, int steps,
                          void* fmid, size_t mid_bytes) {
-    const int tile = pl.region - 2 * (steps - 1);
-    const int blocks = ((d.nx + tile - 1) / tile) * ((d.ny + tile - 1) / tile) *
+    const int tx = pl.rx - 2 * (steps - 1), ty = pl.ry - 2 * (steps - 1);
+    if (tx < 1 || ty < 1) return hipErrorInvalidValue;
+    const int blocks = ((d.nx + tx - 1) / tx) * ((d.ny + ty - 1) / ty) *
                        ((d.members + pl.members - 1) / pl.members);
-    const int items = pl.region * pl.region * (pl.members / V);
+    const int items = pl.rx * pl.ry * (pl.members / V);
     const int threads = ((items + I - 1) / I + kWave - 1) / kWave * kWave;
-    const size_t lds = (size_t)9 * pl.region * pl.region * pl.members * sizeof(T);
-    constexpr size_t kMostLds = 80 * 1024;  // every plan's region: two blocks per CU
-    if (tile < 1 || threads > 1024 || lds > kMostLds || pl.members % V) return hipErrorInvalidValue;
+    const size_t lds = (size_t)9 * pl.rx * pl.ry * pl.members * sizeof(T);
+    constexpr size_t kMostLds = kMostTileLds;
+    if (threads > 1024 || lds > kMostLds || pl.members % V) return hipErrorInvalidValue;
     static bool attr = false;
     if (!attr) {
         hipError_t e = hipFuncSetAttribute(
@@ -808,8 +949,8 @@ hipError_t launch_tile_t(const void* fin, void* fout, const double* force, LbmDi
         attr = true;
     }
     stream_collide_tile_kernel<T, V, I><<<blocks, threads, lds, s>>>(
-        (const T*)fin, (T*)fout, force, d.nx, d.ny, d.members, tau0, smag, mu, pl.region, pl.members,
-        steps, (T*)fmid, mid_bytes / sizeof(T));
+        (const T*)fin, (T*)fout, force, d.nx, d.ny, d.members, tau0, smag, mu, pl.rx, pl.ry,
+        pl.members, steps, (T*)fmid, mid_bytes / sizeof(T));
     return hipGetLastError();
 }
 }  // namespace
@@ -826,8 +967,10 @@ hipError_t launch_stream_collide_tile(const void* fin, void* fout, const double*
                              : launch_tile_t<double, 1, 2>(fin, fout, force, d, tau0, smag, mu, s,
                                                            pl, steps, fmid, mid_bytes);
     if (members_per_thread(4, d.members) == 2)
-        return launch_tile_t<float, 2, 1>(fin, fout, force, d, tau0, smag, mu, s, pl, steps, fmid,
-                                          mid_bytes);
+        return pl.items == 1 ? launch_tile_t<float, 2, 1>(fin, fout, force, d, tau0, smag, mu, s,
+                                                          pl, steps, fmid, mid_bytes)
+                             : launch_tile_t<float, 2, 2>(fin, fout, force, d, tau0, smag, mu, s,
+                                                          pl, steps, fmid, mid_bytes);
     return pl.items == 1 ? launch_tile_t<float, 1, 1>(fin, fout, force, d, tau0, smag, mu, s, pl,
                                                       steps, fmid, mid_bytes)
                          : launch_tile_t<float, 1, 2>(fin, fout, force, d, tau0, smag, mu, s, pl,
