@@ -149,9 +149,10 @@ lbmletkf_status lbmletkf_export(lbmletkf_ctx* ctx, const void* d_f, double* d_ca
 
 /* Forecast (Sec. 2 LBE): advance every member nsteps >= 0 steps of
  * fused pull-stream + collide, in place on d_f (storage layout; the
- * workspace holds the ping-pong partner).  With FP64 storage and 16 | M,
- * pairs of steps run in one launch (spatial tiles, the intermediate state on
- * chip); the result is bit-identical to nsteps single-step calls. */
+ * workspace holds the ping-pong partner).  Several steps run in one launch
+ * (spatial tiles, the intermediate states on chip): pairs with 16 | M on large
+ * problems, up to six otherwise; the result is bit-identical to nsteps
+ * single-step calls. */
 lbmletkf_status lbm_ensemble_step(lbmletkf_ctx* ctx, void* d_f, int32_t nsteps, void* stream);
 
 /* Observation operator y = H x (Sec. 3): d_yf[M][nvar * n_points]. */

@@ -175,8 +175,8 @@ __global__ __launch_bounds__(kBlock) void adjoint_step_kernel(
 // over the values it has read, and step s finds population a of node y + c_a at y + s c_a: one
 // barrier per step, no second buffer.  fhi: the state of the first reversed step, the next
 // ones `stride` elements below; flast: that of the last one.
-// Bound by FP64 issue (about 500 instructions per node and member) and, on small problems,
-// by the latency of a step.  Same arithmetic as single steps; only the order of the partial
+// Bound by FP64 issue (about 240 FP64 instructions per node, member and step) and, on small
+// problems, by the latency of a step.  Same arithmetic as single steps; only the order of the partial
 // sums of dJ/dK differs.  Shapes: adjoint_plan.
 template <typename T>
 __global__ __launch_bounds__(1024) void adjoint_tile_kernel(

@@ -550,8 +550,8 @@ lbmletkf_status lbmletkf_create(const lbmletkf_lbm_params* lbm, const lbmletkf_o
         }
         c->n_eig = maxn;
         // Spread the groups over the caller's stream and the side streams by
-        // longest-processing-time-first on an estimated cost (the Jacobi sweeps
-        // grow as N^3 per node, plus a per-node share for the state passes), so
+        // longest-processing-time-first on an estimated cost (the solvers' work
+        // grows as N^3 per node, plus a per-node share for the state passes), so
         // no group waits behind another on one stream while the GPU idles.
         auto cost = [](const Bucket& b) { return (double)b.count * ((double)b.n * b.n * b.n + 3000.0); };
         std::stable_sort(c->buckets.begin(), c->buckets.end(),

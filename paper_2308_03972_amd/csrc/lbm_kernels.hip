@@ -444,10 +444,10 @@ stream_collide2_batch_kernel(const LbmTask* __restrict__ tasks, int ntasks) {
 // Several steps per launch on regions of any size and any member count: a block
 // takes MG members of a region of RX x RY nodes, pulls the first step from HBM and keeps
 // the results in LDS; each further step loses the region's outer ring, and after k steps
-// the inner T x T nodes (T = R - 2 (k - 1)) are written.  For ensembles that the 128-byte
+// the inner nodes (RX - 2 (k - 1) by RY - 2 (k - 1)) are written.  For ensembles that the 128-byte
 // member blocks above do not fit, and for problems so small that a step's launch costs
 // more than its work: 72 M bytes per node leave room for regions of 12-24 nodes, so that
-// k = 3-6 steps cost one read of R^2 and one write of T^2 nodes, one launch and k barriers.
+// k = 3-6 steps cost one read of the region and one write of its inner nodes, one launch and k barriers.
 // One thread holds I items (a node, V members) through all steps, LDS is updated in place
 // between two barriers.  Same arithmetic and rounding as single steps, bit for bit.
 // Bound by latency (a launch, one round of loads, k barriers) on small problems and by

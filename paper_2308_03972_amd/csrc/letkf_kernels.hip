@@ -16,8 +16,9 @@
 //            = -sqrt(beta) / (a s (1 + s)),  s = sqrt(1 + l/a)
 //     (the second form has no cancellation and is finite at l = 0);
 //   x_m^a = x_bar + dX (w_bar + dW[:, m]) for the nine populations.
-// The n x n symmetric eigenproblem is solved by parallel cyclic Jacobi
-// (Golub & Van Loan, Sec. 8.5) with the Brent-Luk ordering: lane i holds row
+// At the default sweep cap both routes use the solvers of letkf_direct.hip; the ensemble
+// route's kernels here serve a lowered cap: the n x n symmetric eigenproblem is solved by
+// parallel cyclic Jacobi (Golub & Van Loan, Sec. 8.5) with the Brent-Luk ordering: lane i holds row
 // i of the matrix and of the eigenvector matrix in registers; each round
 // rotates the neighbour pairs (2k+p, 2k+p+1) and swaps them, so two fixed
 // pairings alternate and every pair meets once per n rounds.
@@ -86,8 +87,10 @@ __global__ __launch_bounds__(256) void obs_stats_kernel(
 
 // Observation operator and statistics in one launch, for the problems of a cycle (up to
 // kObsTasks): one wavefront per observation point, lane = member, block row = problem; the
-// same values as the two kernels above, without y^f and a launch per problem and step
-// (32^2 x 8: 5.5 -> 3 us; four problems of a batch: 50 -> 10 us of a replayed graph).
+// same values as the two kernels above, without y^f and a launch per problem and kernel.
+// Latency-bound (a launch, two rounds of loads, the reductions): with the Gram launches merged
+// as well a batch of four FP32 problems went from 1403 to 1382 us, and with the diagnostics'
+// reduction below the 32^2 x 8 cycle from 44.3 to 37.9 us.
 constexpr int kObsTasks = 32;
 struct ObsTasks {
     ObsTask t[kObsTasks];
@@ -904,8 +907,8 @@ int diag_fold_blocks(int plane) { return (plane + kDiagBlock - 1) / kDiagBlock; 
 hipError_t launch_diag_nodes_final(const double* diag_node, int plane, double* partial,
                                    double* out_forecast, double* out_analysis, hipStream_t s) {
     static_assert(kDiagFields == kDiagFieldCount, "one diagnostics record layout");
-    // (up to 16 records per thread the last reduction takes the nodes' own records:
-    // 32^2 3.8 + 2.7 -> 3 us, one launch less)
+    // (up to 16 records per thread the last reduction takes the nodes' own records: a
+    // launch of 3.8 us less at 32^2; beyond that one block would read too much)
     if (plane <= 16 * kDiagBlock) {
         diag_final_kernel<<<2, kDiagBlock, 0, s>>>(diag_node, plane, plane, out_forecast,
                                                    out_analysis);
