@@ -328,10 +328,11 @@ __global__ __launch_bounds__(kTwoMG * kTwoR * kTwoR) void stream_collide2_kernel
 // members each (8-byte accesses, as in the single step), the intermediate
 // deviations kept in LDS as FP32 -- exactly the values a single step would
 // store -- so that a launch equals two single-step launches bit for bit.
-// Block b of a two-step launch over one problem (FP32 storage): member group
-// b % (members / gsize) of tile b / (members / gsize), gsize <= MG members per
-// group (threads with 2 threadIdx.x >= gsize idle: a batch runs 16-member
-// problems in 32-member blocks).
+// Block b of a two-step launch over one problem (FP32 storage) holds MG / gsize units of
+// gsize members; unit u is member group u % (members / gsize) of tile u / (members / gsize).
+// (A batch runs ensembles that 32 does not divide as two units of 16 per block; with one,
+// half of each block's threads idled: batch of 128^2 x 16, 128^2 x 32, 192^2 x 16, 192^2 x 64,
+// us per launch 87 -> 82.)
 template <int MG>
 __device__ __forceinline__ void two_step_dev_body(const float* __restrict__ fin,
                                                   float* __restrict__ fout,
@@ -342,11 +343,13 @@ __device__ __forceinline__ void two_step_dev_body(const float* __restrict__ fin,
     typedef float f2 __attribute__((ext_vector_type(2)));
     const int groups = members / gsize;
     const int tiles_x = (nx + kTwoT - 1) / kTwoT;
-    const int mg = b % groups, tile = b / groups;
+    const int units = tiles_x * ((ny + kTwoT - 1) / kTwoT) * groups;
+    const int mp = 2 * threadIdx.x;          // first member of the pair within the block
+    const int u = b * (MG / gsize) + mp / gsize;
+    const bool on = gsize == MG || u < units;  // (the last block may hold one unit)
+    const int mg = on ? u % groups : 0, tile = on ? u / groups : 0;
     const int x0 = (tile % tiles_x) * kTwoT, y0 = (tile / tiles_x) * kTwoT;
-    const int mp = 2 * threadIdx.x;          // first member of the pair within the group
-    const bool on = mp < gsize;
-    const int m = mg * gsize + (on ? mp : 0);
+    const int m = mg * gsize + mp % gsize;
     const int r = threadIdx.y, rx = r % kTwoR, ry = r / kTwoR;
     const int gx = (x0 - 1 + rx + nx) % nx, gy = (y0 - 1 + ry + ny) % ny;
     const int plane = nx * ny;
@@ -418,7 +421,7 @@ __global__ __launch_bounds__(MG / 2 * kTwoR * kTwoR) void stream_collide2_dev_ke
 
 // Two steps of many problems in one launch: block b belongs to the task k
 // with block0_k <= b < block0_{k+1} (a problem's blocks are its tiles x member
-// groups: 16 members for FP64 storage, 32 -- or 16 for a 16-member problem --
+// groups: 16 members for FP64 storage, 32 -- or two units of 16 where 32 does not divide M --
 // for FP32 storage), and runs that problem's two-step block b - block0_k.
 constexpr int kTwoMG32 = 32;  // members per block of the FP32 batched launch
 
@@ -1036,7 +1039,9 @@ hipError_t launch_stream_collide_batch(const LbmTask* d_tasks, int ntasks, int n
 
 int two_step_blocks(LbmDims d, int storage) {
     const int g = (storage == kStoreF32Dev && d.members % kTwoMG32 == 0) ? kTwoMG32 : kTwoMG;
-    return ((d.nx + kTwoT - 1) / kTwoT) * ((d.ny + kTwoT - 1) / kTwoT) * (d.members / g);
+    const int per = storage == kStoreF32Dev ? kTwoMG32 / g : 1;  // units per block
+    const int units = ((d.nx + kTwoT - 1) / kTwoT) * ((d.ny + kTwoT - 1) / kTwoT) * (d.members / g);
+    return (units + per - 1) / per;
 }
 
 hipError_t launch_stream_collide2_batch(const LbmTask* d_tasks, int ntasks, int nblocks,

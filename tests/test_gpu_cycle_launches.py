@@ -80,3 +80,33 @@ def test_cycle_diagnostics_equal_a_plain_reduction(nx, ny):
         spread = np.sqrt((((uv - mean[:, None]) ** 2).sum((0, 1)) / (M - 1)).mean())
         assert abs(got[0] - rmse) <= 1e-12 * rmse and abs(got[1] - spread) <= 1e-12 * spread
         assert got[2] == 0 and abs(got[3] - rho.min()) <= 1e-14 and abs(got[4] - rho.max()) <= 1e-14
+
+
+def test_two_step_batch_of_half_block_ensembles_equals_each_alone():
+    """FP32 ensembles that 32 does not divide run as two units of 16 members per block of the
+    two-step batch: odd and even numbers of units, one and three member groups, next to a
+    32-member problem; bit for bit each problem's own run_cycle."""
+    say("cycle launches: two units per block")
+    shapes = [(14, 13, 16), (20, 19, 48), (9, 8, 32), (13, 12, 16)]  # 9, 48, 2 x 2, 6 units
+
+    def contexts():
+        return [binding.Context(nx, ny, M, 0.55, 0.1, np.array([[3, 4], [7, 2]], np.int32), 2,
+                                (0.02, 0.02), 5.0, 1.05, storage=binding.STORAGE_F32_DEV)
+                for nx, ny, M in shapes]
+
+    rng = np.random.default_rng(14)
+    fe = [random_state(rng, M, ny, nx) for nx, ny, M in shapes]
+    yo = [cuda(0.03 * rng.standard_normal(4)) for _ in shapes]
+    alone = []
+    for c, f, y in zip(contexts(), fe, yo):
+        s = c.import_canonical(cuda(f))
+        c.run_cycle(s, 5, y)
+        alone.append(host(s))
+    ctxs = contexts()
+    states = [c.import_canonical(cuda(f)) for c, f in zip(ctxs, fe)]
+    batch = binding.Batch(ctxs, states, 5, dict(forecast_blocks=0, tile_rows=2, bucket_granularity=2,
+                                                use_graph=1, analysis_queue=0, steps_per_launch=2))
+    batch.run_cycle(yo)
+    torch.cuda.synchronize()
+    for a, s in zip(alone, states):
+        np.testing.assert_array_equal(a, host(s))
