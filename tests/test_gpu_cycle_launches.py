@@ -84,10 +84,9 @@ def test_cycle_diagnostics_equal_a_plain_reduction(nx, ny):
 
 def test_two_step_batch_of_half_block_ensembles_equals_each_alone():
     """FP32 ensembles that 32 does not divide run as two units of 16 members per block of the
-    two-step batch: odd and even numbers of units, one and three member groups, next to a
-    32-member problem; bit for bit each problem's own run_cycle."""
+    two-step batch: odd and even numbers of units, next to 32- and 64-member problems; bit for bit each problem's own run_cycle."""
     say("cycle launches: two units per block")
-    shapes = [(14, 13, 16), (20, 19, 48), (9, 8, 32), (13, 12, 16)]  # 9, 48, 2 x 2, 6 units
+    shapes = [(14, 13, 16), (20, 19, 64), (9, 8, 32), (19, 12, 16)]  # 9 and 8 units of 16
 
     def contexts():
         return [binding.Context(nx, ny, M, 0.55, 0.1, np.array([[3, 4], [7, 2]], np.int32), 2,
