@@ -13,9 +13,10 @@
 // n (n1 + n2) products instead of n^2; a prime n has n1 = 1, the direct sum.  The
 // row pass reads a row for a group of members (whole cache lines), the column pass
 // sums |Z|^2 over its group of members in member order, the groups are added in order,
-// and the shells sum in a fixed order (deterministic).  256^2 x 64 FP64: rows 637 -> 136 us, columns
-// 880 -> 116 us, shells 38 -> 14 us against direct sums with one member per block.
-// Bound by LDS reads (one 16-byte value per four multiply-adds) and latency.
+// and the shells sum in a fixed order (deterministic).  Passes of any n: 256^2 x 64 FP64 rows
+// 637 -> 136 us, columns 880 -> 116 us against direct sums with one member per block (shells
+// 38 -> 14), bound by LDS reads (one 16-byte value per four multiply-adds) and latency;
+// with factors of 8 and 16 in registers, see below.
 // Off the hot path: called at report times.  Scratch comes from the
 // context's ping-pong buffer.
 #include "common.h"
@@ -185,6 +186,173 @@ __global__ __launch_bounds__(kSpecBlock) void spectrum_cols_kernel(const double2
     }
 }
 
+// The same passes for n = n1 n2 with factors of 8 and 16 (64, 128, 256): a thread holds one
+// sub-transform of 8 or 16 values in registers, radix 4 x 4 or 2 x 4, so that a value crosses
+// LDS three times instead of 2 (n1 + n2) / 4 and the line buffer is used in place, which
+// leaves room for sixteen lines: whole 128-byte lines of members in the row pass, and of columns
+// in the column pass, whose sums over its members stay in registers.  256^2 x 64 FP64: rows
+// 136 -> 71 us, columns 116 -> 20 us.  Bound by HBM (the state once, the row transforms
+// written and read).
+__device__ __forceinline__ double2 cmul(double2 a, double c, double s) {  // a (c - i s)
+    return make_double2(fma(a.x, c, a.y * s), fma(a.y, c, -a.x * s));
+}
+__device__ __forceinline__ void dft4(double2& a, double2& b, double2& c, double2& d) {
+    const double2 p = make_double2(a.x + c.x, a.y + c.y), m = make_double2(a.x - c.x, a.y - c.y);
+    const double2 q = make_double2(b.x + d.x, b.y + d.y), r = make_double2(b.x - d.x, b.y - d.y);
+    a = make_double2(p.x + q.x, p.y + q.y);
+    b = make_double2(m.x + r.y, m.y - r.x);
+    c = make_double2(p.x - q.x, p.y - q.y);
+    d = make_double2(m.x - r.y, m.y + r.x);
+}
+// v <- its R-point transform, in order: index 4 a + b, a < R / 4, then c + (R / 4) d.
+template <int R>
+__device__ __forceinline__ void dft(double2 (&v)[R]) {
+    static_assert(R == 8 || R == 16, "radix 2 x 4 or 4 x 4");
+    constexpr int Q = R / 4;
+    constexpr double kCos[10] = {1.0, 0.92387953251128675613, 0.70710678118654752440,
+                                 0.38268343236508977173, 0.0, -0.38268343236508977173,
+                                 -0.70710678118654752440, -0.92387953251128675613, -1.0,
+                                 -0.92387953251128675613};  // cos(pi k / 8)
+    constexpr double kSin[10] = {0.0, 0.38268343236508977173, 0.70710678118654752440,
+                                 0.92387953251128675613, 1.0, 0.92387953251128675613,
+                                 0.70710678118654752440, 0.38268343236508977173, 0.0,
+                                 -0.38268343236508977173};
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        if constexpr (R == 16) {
+            dft4(v[b], v[4 + b], v[8 + b], v[12 + b]);
+        } else {
+            const double2 p = v[b], q = v[4 + b];
+            v[b] = make_double2(p.x + q.x, p.y + q.y);
+            v[4 + b] = make_double2(p.x - q.x, p.y - q.y);
+        }
+#pragma unroll
+        for (int c = 1; c < Q; ++c)
+            if (b > 0) v[4 * c + b] = cmul(v[4 * c + b], kCos[b * c * (16 / R)], kSin[b * c * (16 / R)]);
+    }
+    double2 u[R];
+#pragma unroll
+    for (int c = 0; c < Q; ++c) {
+        dft4(v[4 * c], v[4 * c + 1], v[4 * c + 2], v[4 * c + 3]);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) u[c + Q * d] = v[4 * c + d];
+    }
+#pragma unroll
+    for (int j = 0; j < R; ++j) v[j] = u[j];
+}
+
+constexpr int kRegLines = 16;
+
+template <int N1, int N2>
+constexpr size_t reg_lds() {
+    return ((size_t)kRegLines * (N1 * N2 + N1 + 1) + N1 * N2) * sizeof(double2);
+}
+
+// transform() in place on z[line][n], line < lines <= 16; emit(line, c, u) gets
+// Z(c + N1 d) = u[d], threads with consecutive line (LINE) or c together.
+template <int N1, int N2, bool LINE, typename Emit>
+__device__ __forceinline__ void transform_regs(double2* z, const double2* tw, int lines, Emit emit) {
+    constexpr int ls = N1 * N2 + N1 + 1;
+    const int t = threadIdx.x;
+    const int l = t / N2, b = t % N2;
+    const bool on = l < lines;
+    __syncthreads();
+    double2 v[N1];
+    if (on) {
+#pragma unroll
+        for (int a = 0; a < N1; ++a) v[a] = z[l * ls + N2 * a + b];
+        dft<N1>(v);
+#pragma unroll
+        for (int c = 1; c < N1; ++c) {
+            const double2 w = tw[b * c];
+            v[c] = cmul(v[c], w.x, -w.y);
+        }
+    }
+    __syncthreads();
+    if (on) {
+#pragma unroll
+        for (int c = 0; c < N1; ++c) z[l * ls + c * (N2 + 1) + b] = v[c];
+    }
+    __syncthreads();
+    const int l2 = LINE ? t % kRegLines : t / N1, c2 = LINE ? t / kRegLines : t % N1;
+    if (c2 < N1 && l2 < lines) {
+        double2 u[N2];
+#pragma unroll
+        for (int d = 0; d < N2; ++d) u[d] = z[l2 * ls + c2 * (N2 + 1) + d];
+        dft<N2>(u);
+        emit(l2, c2, u);
+    }
+    __syncthreads();
+}
+
+template <typename T, int N1, int N2>
+__global__ __launch_bounds__(kSpecBlock) void spectrum_rows_regs_kernel(const T* __restrict__ f,
+                                                                        int members,
+                                                                        double2* __restrict__ out) {
+    extern __shared__ double2 spec[];
+    constexpr int n = N1 * N2, ls = n + N1 + 1;
+    double2* z = spec;
+    double2* tw = z + kRegLines * ls;
+    const int groups = (members + kRegLines - 1) / kRegLines;
+    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    const int y = blk / groups, m0 = (blk - y * groups) * kRegLines;
+    const int nm = min(kRegLines, members - m0);
+    fill_twiddles(tw, n);
+    const int m = threadIdx.x % kRegLines;
+    if (m < nm) {
+#pragma unroll 2
+        for (int x = threadIdx.x / kRegLines; x < n; x += kSpecBlock / kRegLines) {
+            double rho = 0.0, jx = 0.0, jy = 0.0;
+#pragma unroll
+            for (int a = 0; a < 9; ++a) {
+                const double fa =
+                    PopIO<T>::load(f + slot(src_node(x, y, a, n, n), a, m0 + m, members), a);
+                rho += fa;
+                jx += cx_of(a) * fa;
+                jy += cy_of(a) * fa;
+            }
+            z[m * ls + x] = make_double2(jx / rho, jy / rho);
+        }
+    }
+    transform_regs<N1, N2, false>(z, tw, nm, [&](int l, int c, const double2 (&u)[N2]) {
+        double2* o = out + ((size_t)(m0 + l) * n + y) * n + c;
+#pragma unroll
+        for (int d = 0; d < N2; ++d) o[N1 * d] = u[d];
+    });
+}
+
+template <int N1, int N2>
+__global__ __launch_bounds__(kSpecBlock) void spectrum_cols_regs_kernel(
+    const double2* __restrict__ rows, int members, double* __restrict__ e) {
+    extern __shared__ double2 spec[];
+    constexpr int n = N1 * N2, ls = n + N1 + 1, tiles = n / kRegLines;
+    double2* z = spec;
+    double2* tw = z + kRegLines * ls;
+    const int group = blockIdx.x / tiles, kx0 = (blockIdx.x - group * tiles) * kRegLines;
+    fill_twiddles(tw, n);
+    double* const eg = e + (size_t)group * n * n;
+    const int mend = min(members, (group + 1) * kColMembers);
+    double acc[N2];
+#pragma unroll
+    for (int d = 0; d < N2; ++d) acc[d] = 0.0;
+    for (int m = group * kColMembers; m < mend; ++m) {
+        const int l = threadIdx.x % kRegLines;
+#pragma unroll 4
+        for (int y = threadIdx.x / kRegLines; y < n; y += kSpecBlock / kRegLines)
+            z[l * ls + y] = rows[((size_t)m * n + y) * n + kx0 + l];
+        transform_regs<N1, N2, true>(z, tw, kRegLines, [&](int, int, const double2 (&u)[N2]) {
+#pragma unroll
+            for (int d = 0; d < N2; ++d) acc[d] += 0.5 * (u[d].x * u[d].x + u[d].y * u[d].y);
+        });
+    }
+    // (the thread of line l and residue c, as transform_regs deals them out)
+    const int l = threadIdx.x % kRegLines, c = threadIdx.x / kRegLines;
+    if (c < N1) {
+#pragma unroll
+        for (int d = 0; d < N2; ++d) eg[(size_t)(c + N1 * d) * n + kx0 + l] = acc[d];
+    }
+}
+
 // The groups' sums added up, in group order, into the first.
 __global__ __launch_bounds__(kSpecBlock) void spectrum_fold_kernel(double* __restrict__ e, int modes,
                                                                    int groups) {
@@ -238,21 +406,9 @@ hipError_t allow_spec_lds(K kernel, size_t bytes) {
                                (int)bytes);
 }
 
-}  // namespace
-
-size_t spectrum_scratch_bytes(int n, int members) {
-    const size_t rows = (size_t)members * n * n * sizeof(double2);
-    const size_t need = rows + (size_t)col_groups(members) * n * n * sizeof(double);
-    // the documented requirement (half-plane transforms of u and v, one energy plane)
-    const size_t ncol = (size_t)n / 2 + 1;
-    const size_t stated = (size_t)members * n * ncol * 32 + n * ncol * sizeof(double) + 256;
-    return need > stated ? need : stated;
-}
-
-hipError_t launch_energy_spectrum(const void* f, int n, int members, int storage, int kmax,
-                                  void* scratch, double* E, hipStream_t s) {
-    double2* rows = reinterpret_cast<double2*>(scratch);
-    double* e = reinterpret_cast<double*>(rows + (size_t)members * n * n);
+// Row and column passes: e[group][ky][kx] from the state.
+hipError_t launch_passes_any(const void* f, int n, int members, int storage, double2* rows, double* e,
+                             hipStream_t s) {
     const int n1 = spec_factor(n);
     int most = 1;
     while (most < members && most < 16) most *= 2;
@@ -274,7 +430,55 @@ hipError_t launch_energy_spectrum(const void* f, int n, int members, int storage
     const int groups = col_groups(members);
     spectrum_cols_kernel<<<groups * ((n + cl - 1) / cl), kSpecBlock, col_lds, s>>>(rows, n, n1,
                                                                                    members, cl, e);
+    return hipGetLastError();
+}
+
+template <typename T, int N1, int N2>
+hipError_t launch_passes_t(const T* f, int members, double2* rows, double* e, hipStream_t s) {
+    constexpr int n = N1 * N2;
+    constexpr size_t lds = reg_lds<N1, N2>();
+    hipError_t err = allow_spec_lds(spectrum_rows_regs_kernel<T, N1, N2>, lds);
+    if (err == hipSuccess) err = allow_spec_lds(spectrum_cols_regs_kernel<N1, N2>, lds);
+    if (err != hipSuccess) return err;
+    spectrum_rows_regs_kernel<T, N1, N2>
+        <<<n * ((members + kRegLines - 1) / kRegLines), kSpecBlock, lds, s>>>(f, members, rows);
     if ((err = hipGetLastError()) != hipSuccess) return err;
+    spectrum_cols_regs_kernel<N1, N2>
+        <<<col_groups(members) * (n / kRegLines), kSpecBlock, lds, s>>>(rows, members, e);
+    return hipGetLastError();
+}
+
+template <int N1, int N2>
+hipError_t launch_passes(const void* f, int members, int storage, double2* rows, double* e,
+                         hipStream_t s) {
+    return storage == kStoreF32Dev
+               ? launch_passes_t<float, N1, N2>((const float*)f, members, rows, e, s)
+               : launch_passes_t<double, N1, N2>((const double*)f, members, rows, e, s);
+}
+
+}  // namespace
+
+size_t spectrum_scratch_bytes(int n, int members) {
+    const size_t rows = (size_t)members * n * n * sizeof(double2);
+    const size_t need = rows + (size_t)col_groups(members) * n * n * sizeof(double);
+    // the documented requirement (half-plane transforms of u and v, one energy plane)
+    const size_t ncol = (size_t)n / 2 + 1;
+    const size_t stated = (size_t)members * n * ncol * 32 + n * ncol * sizeof(double) + 256;
+    return need > stated ? need : stated;
+}
+
+hipError_t launch_energy_spectrum(const void* f, int n, int members, int storage, int kmax,
+                                  void* scratch, double* E, hipStream_t s) {
+    double2* rows = reinterpret_cast<double2*>(scratch);
+    double* e = reinterpret_cast<double*>(rows + (size_t)members * n * n);
+    const int groups = col_groups(members);
+    // (the sizes whose two factors are 8 or 16 transform in registers, 252 -> 91 us for both passes
+    // at 256^2 x 64; same results to rounding)
+    hipError_t err = n == 256   ? launch_passes<16, 16>(f, members, storage, rows, e, s)
+                     : n == 128 ? launch_passes<8, 16>(f, members, storage, rows, e, s)
+                     : n == 64  ? launch_passes<8, 8>(f, members, storage, rows, e, s)
+                                : launch_passes_any(f, n, members, storage, rows, e, s);
+    if (err != hipSuccess) return err;
     if (groups > 1) {
         spectrum_fold_kernel<<<(n * n + kSpecBlock - 1) / kSpecBlock, kSpecBlock, 0, s>>>(e, n * n,
                                                                                           groups);
