@@ -132,6 +132,7 @@ __device__ __forceinline__ void apply_rows(const AnalysisParams& p, const int* n
         row_diag_record<MS>(f, mem, M, node, nx * ny, p.truth_uv,
                             p.diag_node + (size_t)node * kDiagFieldCount, valid, r);
     // (the means wait in LDS: in registers they would cost B a wavefront per SIMD)
+    wave_lds_sync();  // (a queue's previous nodes are done with theirs)
     const double rm = 1.0 / M;
 #pragma unroll
     for (int a = 0; a < 9; ++a) {
@@ -182,7 +183,7 @@ __device__ __forceinline__ void apply_rows(const AnalysisParams& p, const int* n
             for (int a = 0; a < 9; ++a) B[h][a] *= w[h];
     }
     // the mean increment B h and x_bar go into the update, which replaces dX
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
 #pragma unroll
     for (int a = 0; a < 9; ++a) {
         double d = B[0][a] * hv[0];
