@@ -182,16 +182,19 @@ __device__ __forceinline__ void apply_rows(const AnalysisParams& p, const int* n
 #pragma unroll
             for (int a = 0; a < 9; ++a) B[h][a] *= w[h];
     }
-    // the mean increment B h and x_bar go into the update, which replaces dX
+    // x_bar plus the mean increment B h waits with the means; the members' part of the update
+    // replaces dX and stays at the size of dX until the end (summed into the populations
+    // themselves, each of its n terms would round at their size: 3 to 10 ulps against 1)
     wave_lds_sync();
 #pragma unroll
     for (int a = 0; a < 9; ++a) {
         double d = B[0][a] * hv[0];
 #pragma unroll
         for (int h = 1; h < NS; ++h) d = fma(B[h][a], hv[h], d);
-        const double c0 = mean[row][a] + row_sum(d);
+        d = row_sum(d);
+        if (r == a) mean[row][a] += d;
 #pragma unroll
-        for (int s = 0; s < MS; ++s) f[s][a] = fma(p.sqrt_beta, f[s][a], c0);
+        for (int s = 0; s < MS; ++s) f[s][a] *= p.sqrt_beta;
     }
     if (any) {
         // C = B G, column 16 h + r, then weighted for the unweighted dY below
@@ -247,6 +250,13 @@ __device__ __forceinline__ void apply_rows(const AnalysisParams& p, const int* n
             for (int s = 0; s < MS; ++s) fmac9<k + 3>(f[s], C[hb], z[3][s]);
         };
         chunks<4 * NS>(z_part);
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int a = 0; a < 9; ++a) {
+        const double c0 = mean[row][a];
+#pragma unroll
+        for (int s = 0; s < MS; ++s) f[s][a] += c0;
     }
     {
         // (the slots' addresses anew: kept from the loads they would hold 18 registers)
