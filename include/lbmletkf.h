@@ -217,9 +217,11 @@ lbmletkf_status run_cycle(lbmletkf_ctx* ctx, void* d_f, int32_t nsteps, const do
  *   max_sweeps         cap of the analysis eigensolvers' Jacobi sweeps, 1..100
  *                      (default 30; converged solves take 4-8); a node that
  *                      reaches it is counted and its weights are used as they are.
- *                      At 30 and above the analysis may solve without iterating
- *                      (the same weights to rounding; a node whose matrix is not
- *                      finite is counted as one at the cap);
+ *                      At 30 and above the analysis solves without iterating
+ *                      (the same weights to rounding); then the nodes counted
+ *                      are those whose matrix is not finite.  With a lower cap
+ *                      nodes that share a wavefront stop together and count as
+ *                      one;
  *   diverge_limit      run_cycle's divergence threshold on the analysis RMSE and
  *                      spread (same units as the velocity; <= 0 or inf: none,
  *                      the default);
@@ -235,9 +237,10 @@ lbmletkf_status lbmletkf_set_checks(lbmletkf_ctx* ctx, int32_t max_sweeps, doubl
  * check, in this order: LBMLETKF_ENONFINITE if d_diag (NULL, or a run_cycle
  * diagnostics record of 16 doubles) counts members with a non-finite density
  * or velocity or holds a non-finite RMSE/spread; LBMLETKF_EEIG if any node's
- * eigensolver reached the sweep cap; LBMLETKF_EDIVERGED if the record's
+ * eigenproblem was counted as failed (at the sweep cap, or not finite; see
+ * max_sweeps above); LBMLETKF_EDIVERGED if the record's
  * analysis RMSE or spread exceeds the divergence limit; else LBMLETKF_OK.  The
- * counts are in lbmletkf_last_error().  Clears the sweep-cap counter. */
+ * counts are in lbmletkf_last_error().  Clears the counter of failed nodes. */
 lbmletkf_status lbmletkf_check(lbmletkf_ctx* ctx, const double* d_diag, void* stream);
 
 /* Precision form (F32_DEV storage) only: enable = 1 runs the observation

@@ -227,7 +227,8 @@ struct AnalysisParams {
     double sqrt_beta;
     int max_sweeps;       // Jacobi sweep cap of the eigensolvers
     int mfma_transform;   // FP32 storage: B = dX Z^T and the transform on BF16 matrix cores
-    int* eig_fail;        // count of nodes whose eigensolver hit the sweep cap
+    int* eig_fail;        // count of failed solves: nodes with a matrix that is not finite, or
+                          // (iterative solver) wavefronts stopped by the sweep cap
     // cycle diagnostics folded into the analysis (NULL: none): per node the five
     // diagnostic fields (err2, spread2, non-finite, rho min, rho max) of the
     // forecast at diag_node[node * 5] and of the analysis at

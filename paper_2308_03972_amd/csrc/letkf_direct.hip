@@ -30,6 +30,17 @@ constexpr bool kRows16 = N <= 32;  // four nodes per wavefront
 template <int N>
 constexpr bool kPairs = N > 32 && N <= 48;  // two (observation route)
 
+// Adds the wavefront's failed nodes (SEG lanes each, any of them `bad`) to *count.
+template <int SEG>
+__device__ __forceinline__ void count_failed(bool bad, int* count, int lane) {
+    const unsigned long long lanes = __ballot(bad);
+    if (lanes == 0) return;  // uniform
+    int nodes = 0;
+#pragma unroll
+    for (int k = 0; k < kWave; k += SEG) nodes += (lanes >> k & ((1ull << SEG) - 1)) != 0;
+    if (lane == 0) atomicAdd(count, nodes);
+}
+
 // ---------------------------------------------------------------------------
 // observation route
 // ---------------------------------------------------------------------------
@@ -82,7 +93,7 @@ __device__ __forceinline__ void direct_body(const AnalysisParams p, const int* n
     double* out = gout + (size_t)(valid ? item : item0) * (N * N + N);
     const ReflGlobal vs{out, N, valid};
     const bool finite = sym_direct<N, false>(A, b, ia, -p.sqrt_beta * ia, lds, vs, lane);
-    if (__any(valid && !finite) && lane == 0) atomicAdd(p.eig_fail, 1);
+    count_failed<16>(valid && !finite, p.eig_fail, lane);
     if (valid) {
 #pragma unroll
         for (int h = 0; h < NS; ++h) {
@@ -143,7 +154,7 @@ __device__ __forceinline__ void direct_body_pair(const AnalysisParams p, const i
     double* out = gout + (size_t)(valid ? item : item0) * (N * N + N);
     const ReflGlobal vs{out, N, valid};
     const bool finite = sym_direct_pair<N, false>(A, b, ia, -p.sqrt_beta * ia, lds, vs, lane);
-    if (__any(valid && !finite) && lane == 0) atomicAdd(p.eig_fail, 1);
+    count_failed<32>(valid && !finite, p.eig_fail, lane);
     if (valid) {
 #pragma unroll
         for (int h = 0; h < 3; ++h) {
@@ -341,7 +352,7 @@ __device__ __forceinline__ void ens_direct_body(const AnalysisParams& p, int nod
     const double ia = 1.0 / p.a;
     const ReflLds vs{lds + 4 * Direct<N>::kNodeDoubles + seg * ReflLds::doubles(N)};
     const bool finite = sym_direct<N, true>(A, b, ia, p.sqrt_beta, lds, vs, lane);
-    if (__any(here && !finite) && lane == 0) atomicAdd(p.eig_fail, 1);
+    count_failed<16>(here && !finite, p.eig_fail, lane);
 
     // the populations, read only now: nothing above needs them, and they would hold
     // 18 registers per member slot through the solver
