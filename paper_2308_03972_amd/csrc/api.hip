@@ -83,6 +83,9 @@ struct Ctx {
         const void* work = nullptr;
         bool kept = false;  // the last two intervals' states are still in the work's two sets
     } fwd;
+    // a reverse sweep of this context has been captured: a replay of it overwrites both sets
+    // without a call here, so from then on no forward sweep keeps states
+    bool backward_captured = false;
     // the reverse sweep recomputes the next interval's states on this stream
     // while the caller's stream runs the current interval's adjoint steps
     // (created at the first backward call)
@@ -1001,10 +1004,11 @@ lbmletkf_status lbmletkf_misfit_forward(lbmletkf_ctx* ctx, const void* d_f0, dou
     double* jbuf = reinterpret_cast<double*>(sw.w + L.jbuf);
     const size_t nj = (size_t)c->dims.members * c->obs.n_points;
     hipError_t e = hipSuccess;
+    const bool keep = !c->backward_captured;
     for (int t = 1; t <= n_times; ++t) {
         // the last two intervals' states stay for the reverse sweep, which starts there
         // (40 x 24 x 5, three intervals: two of three recomputations and their launches saved)
-        st = t + 2 > n_times
+        st = keep && t + 2 > n_times
                  ? segment_steps(c, sw.with_set(t % 2), t, steps_per_obs, steps_per_obs, cs, s)
                  : segment_advance(c, sw, t, steps_per_obs, cs, s);
         if (st) return st;
@@ -1016,7 +1020,7 @@ lbmletkf_status lbmletkf_misfit_forward(lbmletkf_ctx* ctx, const void* d_f0, dou
     }
     e = launch_sum(jbuf, nj, 1.0, d_J, s);
     if (e != hipSuccess) return hip_fail(e, "sum");
-    c->fwd = {true, d_f0, cs, steps_per_obs, n_times, d_work, true};
+    c->fwd = {true, d_f0, cs, steps_per_obs, n_times, d_work, keep};
     return LBMLETKF_OK;
 }
 
@@ -1059,13 +1063,17 @@ lbmletkf_status lbmletkf_misfit_backward(lbmletkf_ctx* ctx, const void* d_f0, do
     if (plan.steps > 1) kpart = reinterpret_cast<double*>(sw.w + L.jbuf);
     hipError_t e = launch_zero2(cur, nlam, kpart, (size_t)nparts, s);
     if (e != hipSuccess) return hip_fail(e, "fill");
-    // the forward sweep left the last two intervals' states; earlier intervals overwrite them
-    // (not relied on in a captured sweep, which may be replayed without the forward one)
+    // the forward sweep left the last two intervals' states; earlier intervals overwrite them.
+    // A captured sweep recomputes them (it may be replayed without the forward one), and
+    // its replays overwrite what later forward sweeps would leave.
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     e = hipStreamIsCapturing(s, &capturing);
     if (e != hipSuccess) return hip_fail(e, "capture status");
-    const bool use = fw.kept && capturing == hipStreamCaptureStatusNone;
-    const int kept = use ? n_times - 1 : n_times + 1;  // intervals kept .. n_times
+    if (capturing != hipStreamCaptureStatusNone) {
+        c->backward_captured = true;
+        c->fwd.kept = false;
+    }
+    const int kept = fw.kept ? n_times - 1 : n_times + 1;  // intervals kept .. n_times
     if (n_times > 2) c->fwd.kept = false;
     // The states between checkpoints t - 1 and t are recomputed on the
     // recompute stream into set t % 2, one interval ahead of the adjoint steps
