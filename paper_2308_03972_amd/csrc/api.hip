@@ -82,10 +82,14 @@ struct Ctx {
         int steps = 0, times = 0;
         const void* work = nullptr;
         bool kept = false;  // the last two intervals' states are still in the work's two sets
+        bool used = false;  // a reverse sweep has followed
     } fwd;
     // a reverse sweep of this context has been captured: a replay of it overwrites both sets
     // without a call here, so from then on no forward sweep keeps states
     bool backward_captured = false;
+    // the states a forward sweep kept were not used before the next one: the caller evaluates
+    // J alone and nothing is kept until a reverse sweep follows again
+    bool forward_alone = false;
     // the reverse sweep recomputes the next interval's states on this stream
     // while the caller's stream runs the current interval's adjoint steps
     // (created at the first backward call)
@@ -1004,7 +1008,11 @@ lbmletkf_status lbmletkf_misfit_forward(lbmletkf_ctx* ctx, const void* d_f0, dou
     double* jbuf = reinterpret_cast<double*>(sw.w + L.jbuf);
     const size_t nj = (size_t)c->dims.members * c->obs.n_points;
     hipError_t e = hipSuccess;
-    const bool keep = !c->backward_captured;
+    if (c->fwd.kept && !c->fwd.used) c->forward_alone = true;
+    // writing every state of two intervals costs J alone up to half its time (us, kept / not:
+    // FP64 128^2 x 16, 20 steps, 1 interval 183 / 131, 256^2 x 64, 10 steps, 1 interval
+    // 1073 / 732) and saves a gradient more (463 / 600, 3491 / 4102)
+    const bool keep = !c->backward_captured && !c->forward_alone;
     for (int t = 1; t <= n_times; ++t) {
         // the last two intervals' states stay for the reverse sweep, which starts there
         // (40 x 24 x 5, three intervals: two of three recomputations and their launches saved)
@@ -1075,6 +1083,8 @@ lbmletkf_status lbmletkf_misfit_backward(lbmletkf_ctx* ctx, const void* d_f0, do
     }
     const int kept = fw.kept ? n_times - 1 : n_times + 1;  // intervals kept .. n_times
     if (n_times > 2) c->fwd.kept = false;
+    c->fwd.used = true;
+    c->forward_alone = false;
     // The states between checkpoints t - 1 and t are recomputed on the
     // recompute stream into set t % 2, one interval ahead of the adjoint steps
     // on the caller's stream: interval t - 1 is recomputed while interval t is
