@@ -935,7 +935,7 @@ struct Sweep {
 lbmletkf_status segment_steps(Ctx* c, const Sweep& sw, int t, int steps, int last, double cs,
                               hipStream_t s) {
     const StepPlans& plans = c->plans;
-    const bool tiles = plans.most > 1;
+    const bool tiles = plans.most > 1 && tiles_keep_states(c->dims);
     const int most = two_step_supported(c->dims, c->storage()) ? 2 : 1;
     int launches = tiles && last > 0 ? plan_launches(plans, last, false) : 0;
     for (int j = 1; j <= last; --launches) {

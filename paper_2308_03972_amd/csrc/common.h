@@ -154,6 +154,8 @@ struct StepPlans {
 };
 StepPlans step_plans(LbmDims d, int storage);
 int plan_launches(const StepPlans& plans, int steps, bool even);
+// Whether a tiled launch also pays where every state in between is written.
+bool tiles_keep_states(LbmDims d);
 // `steps` <= pl.steps steps; with fmid != NULL the states after steps 1 .. steps - 1 go to
 // fmid, fmid + mid_bytes, ...  Same arithmetic and rounding as single steps.
 hipError_t launch_stream_collide_tile(const void* fin, void* fout, const double* force, LbmDims d,

@@ -910,6 +910,15 @@ StepPlans step_plans(LbmDims d, int storage) {
     return out;
 }
 
+// With every state written a tiled launch saves only reads and launches, and writes each line in
+// the pieces of its member groups: beyond 12 members and 4e5 node-members single steps (pairs
+// for 16 FP32 members) take over.  Reverse sweep of 3 x 10 steps, time single / tiled: 8 members
+// 1.17, 1.11, 1.06 at P = 5e4, 4e5, 4e6; 24 members 1.08, 1.00, 0.84; 40 members 1.10, 0.97, 0.80;
+// FP32 16 members 1.15, 1.06, 0.92; 33 members 1.06, 1.02, 0.95.
+bool tiles_keep_states(LbmDims d) {
+    return d.members <= 12 || (double)d.nx * d.ny * d.members <= 4e5;
+}
+
 int plan_launches(const StepPlans& plans, int steps, bool even) {
     int best = 0;
     double least = 1e30;
