@@ -374,14 +374,16 @@ hipError_t launch_adjoint_step(const void* fstate, const double* lam_in, double*
 }
 
 // Small problems only, where a step's launch and latency cost more than its work: up to
-// P = 7e4 node-members (us per step, single / this: 24^2 x 1 4.7 / 1.9, 40 x 24 x 5
-// 4.9 / 2.2, 48^2 x 8 4.6 / 2.8, 100 x 80 x 4 4.5 / 3.2, 64^2 x 16 4.9 / 4.5; 80 x 60 x 20
-// 5.8 / 5.6 and 160 x 120 x 5 7.8 / 5.9 on the other side, 128^2 x 16 10.1 / 12.7).  Of the
-// shapes with one block per CU at most, the best by a fit of those sweeps: a launch 2.5 us, a
+// P = 7e4 node-members for at most five members and 2e4 for more, whose blocks take one or two
+// members and with them an eighth of each line they touch.  us of a reverse sweep of ten steps
+// (about 40 of them its other launches), single / this: 1 member 84 / 51 at P = 3e3, 154 / 81 at
+// 7e4; 5 members 82 / 53, 134 / 110; 8 members 82 / 56, 82 / 72 at 1.5e4; 24 members 82 / 53,
+// 83 / 69 at 1.5e4, but 90 / 125 at 6e4 (40 members 86 / 115 at 5e4).  Of the
+// shapes with one block per CU at most, the best by a fit of a sweep: a launch 2.5 us, a
 // step 1.5 us and 2.5 us more per 1024 threads of the block.
 StepPlan adjoint_plan(LbmDims d, int interval, int capacity) {
     StepPlan best{};
-    if (interval < 2 || (double)d.nx * d.ny * d.members > 7e4) return best;
+    if (interval < 2 || (double)d.nx * d.ny * d.members > (d.members <= 5 ? 7e4 : 2e4)) return best;
     double least = 1e30;
     for (int mg = 1; mg <= 4 && mg <= d.members; mg *= 2)
         for (int k = 2; k <= 6 && k <= interval; ++k)

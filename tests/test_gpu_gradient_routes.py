@@ -1,6 +1,8 @@
 """The launches a gradient takes on either side of the sizes where they change: states between
 observation times written by tiled launches or by single steps and pairs, whatever the route the
-same bits as single steps."""
+same bits as single steps; several reverse steps per launch or one (7e4 node-members for up to
+five members, 2e4 for more), against the oracle's gradient with the tolerances of
+test_gpu_adjoint.py (1e-11 of the gradient's scale, 1e-13 of J)."""
 import numpy as np
 import pytest
 import torch
@@ -8,6 +10,7 @@ import torch
 import oracle
 from paper_2308_03972_amd import binding
 from gpu_helpers import cuda, host, need_gpu, random_state, say
+from test_gpu_adjoint import _gpu_gradient, _oracle_gradient, _problem
 
 pytestmark = pytest.mark.gpu
 
@@ -55,3 +58,15 @@ def test_states_between_observations(nx, ny, M, storage):
     assert found == steps
     ref = float(((host(ctx.observe(st)) - host(yo[0])) ** 2).sum())
     assert abs(J1 - ref) <= 1e-13 * ref
+
+
+@pytest.mark.parametrize("m,ny,nx", [(5, 118, 118), (5, 119, 119), (6, 58, 57), (6, 58, 58)])
+def test_reverse_steps_per_launch(m, ny, nx):
+    say(f"gradient routes: reverse steps {nx} x {ny} x {m}")
+    p = _problem(600 + m + nx, m, ny, nx, npts=4, nvar=2, n_times=2, s=3)
+    J, (g, gcs), (g2, gcs2) = _gpu_gradient(p, repeat=2)
+    Jr, gr, gcsr = _oracle_gradient(p)
+    assert abs(J - Jr) <= 1e-13 * Jr
+    assert np.max(np.abs(g - gr)) <= 1e-11 * np.max(np.abs(gr))
+    assert abs(gcs - gcsr) <= 1e-11 * abs(gcsr)
+    assert np.array_equal(g, g2) and gcs == gcs2
