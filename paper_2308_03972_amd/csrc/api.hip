@@ -668,18 +668,18 @@ lbmletkf_status lbm_ensemble_step(lbmletkf_ctx* ctx, void* d_f, int32_t nsteps, 
     // steps where the ensemble allows it, a single step for an odd remainder
     const StepPlans& plans = c->plans;
     const bool two = two_step_supported(c->dims, c->storage());
-    int launches = plans.most > 1 && nsteps > 1 ? plan_launches(plans, nsteps, true) : 0;
+    int launches =
+        plans.most > 1 && nsteps > plans.fewest ? plan_launches(plans, nsteps, true) : 0;
+    const bool tiles = launches > 0;
     for (int k = 0; k < nsteps;) {
         int n = (two && nsteps - k >= 2) ? 2 : 1;
         hipError_t e;
-        if (launches > 0) {
-            n = (nsteps - k + launches - 1) / launches;
-            --launches;
-            StageTimer t(c, kStageCollide, s, kPerLaunch, n);
+        if (tiles) n = (nsteps - k + launches - 1) / launches--;
+        StageTimer t(c, kStageCollide, s, kPerLaunch, n);
+        if (tiles && n >= plans.fewest) {
             e = launch_stream_collide_tile(a, b, c->force(), c->dims, c->lbm.tau0, c->lbm.cs,
                                            c->lbm.mu, c->storage(), s, plans.p[n], n);
         } else {
-            StageTimer t(c, kStageCollide, s, kPerLaunch, n);
             e = n == 2 ? launch_stream_collide2(a, b, c->force(), c->dims, c->lbm.tau0, c->lbm.cs,
                                                 c->lbm.mu, c->storage(), s)
                        : launch_stream_collide(a, b, c->force(), c->dims, c->lbm.tau0, c->lbm.cs,

@@ -149,6 +149,7 @@ struct StepPlan {
 constexpr int kMostSteps = 6;
 struct StepPlans {
     int most;
+    int fewest;  // launches of fewer steps go to the single-step and pair kernels
     StepPlan p[kMostSteps + 1];
     double us[kMostSteps + 1];
 };

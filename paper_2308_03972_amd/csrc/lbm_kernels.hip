@@ -907,6 +907,13 @@ StepPlans step_plans(LbmDims d, int storage) {
     }
     for (int n = 1; n <= kMostSteps; ++n)
         if (out.us[n] < 1e29) out.most = n;
+    // Launches too short to gain from the tiles, which split a line's members: single steps
+    // for all but small ensembles, pairs for 16 FP32 members.  us of two single steps, plain /
+    // tiled: 1 member 21 / 16 at P = 6.6e4, 5 members 28 / 19 at 3e5 but 10.6 / 11.8 at 3e3, FP64 50 members 900 / 1329 at 1.3e7, 33 members 143 / 212 at 2.2e6; FP32 12 members
+    // 1.17 times at 4e6, 0.73 at 1e5; four steps of 16 FP32 members as pairs / tiled 167 / 190 at 4e6.
+    const bool tiled = (M <= 2 && P >= 2e4) || (M <= 5 && P >= 1e5) ||
+                       (M <= 12 && M * (int)state_elem_bytes(storage) <= 56 && P >= 2e5);
+    out.fewest = tiled ? 1 : (M == 16 && P > 1e5 ? 3 : 2);
     return out;
 }
 
