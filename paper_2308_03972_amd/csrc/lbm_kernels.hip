@@ -345,11 +345,19 @@ __device__ __forceinline__ void two_step_dev_body(const float* __restrict__ fin,
     const int tiles_x = (nx + kTwoT - 1) / kTwoT;
     const int units = tiles_x * ((ny + kTwoT - 1) / kTwoT) * groups;
     const int mp = 2 * threadIdx.x;          // first member of the pair within the block
-    const int u = b * (MG / gsize) + mp / gsize;
-    const bool on = gsize == MG || u < units;  // (the last block may hold one unit)
-    const int mg = on ? u % groups : 0, tile = on ? u / groups : 0;
+    // a block of one unit (uniform: its divisions stay on the scalar unit; per thread they cost
+    // a single problem's launch 6% at 68^2 x 64) or of several
+    int mg = b % groups, tile = b / groups, m = mp;
+    bool on = true;
+    if (gsize != MG) {
+        const int u = b * (MG / gsize) + mp / gsize;
+        on = u < units;  // (the last block may hold one unit)
+        mg = on ? u % groups : 0;
+        tile = on ? u / groups : 0;
+        m = mp % gsize;
+    }
+    m += mg * gsize;
     const int x0 = (tile % tiles_x) * kTwoT, y0 = (tile / tiles_x) * kTwoT;
-    const int m = mg * gsize + mp % gsize;
     const int r = threadIdx.y, rx = r % kTwoR, ry = r / kTwoR;
     const int gx = (x0 - 1 + rx + nx) % nx, gy = (y0 - 1 + ry + ny) % ny;
     const int plane = nx * ny;
