@@ -69,60 +69,107 @@ __device__ __forceinline__ void mac(double2& acc, double2 z, double2 w) {
 }
 
 // The transform of `lines` lines z[line][n] (LDS): Y in y[line][n], then emit(line, k, Z).
-// Four lines at a time share each twiddle factor.
-template <typename Emit>
+// L lines at a time share each twiddle factor; a thread past the last line repeats it, so that
+// the loops have no branches (all passes, us, with a branch per line / without: 97^2 x 8 85 / 28,
+// 254^2 x 8 209 / 86).  A prime n takes k and n - k from the same four sums (251^2 x 64, both:
+// 1026 / 318).
+template <int L, typename Emit>
 __device__ __forceinline__ void transform(const double2* z, double2* y, const double2* tw, int n,
                                           int n1, int n2, int lines, Emit emit) {
-    const int lb = (lines + 3) / 4, ls = spec_stride(n, n1);
+    const int lb = (lines + L - 1) / L, ls = spec_stride(n, n1);
     __syncthreads();
-    if (n1 > 1) {
-        for (int t = threadIdx.x; t < lb * n; t += kSpecBlock) {
-            const int q = t / n, i = t - q * n;  // i = c n2 + b
-            const int c = i / n2, b = i - c * n2;
-            double2 acc[4];
+    if (n1 == 1) {
+        // k and n - k together: the sums of x c, y s, y c and x s (twiddle c - i s) give both
+        const int half = n / 2 + 1;
+        for (int t = threadIdx.x; t < lb * half; t += kSpecBlock) {
+            const int q = t / half, k = t - q * half;
+            const double2* at[L];
+            double2 even[L], odd[L];  // (sum x c, sum y c), (sum y s, sum x s)
 #pragma unroll
-            for (int l = 0; l < 4; ++l) acc[l] = make_double2(0.0, 0.0);
+            for (int l = 0; l < L; ++l) {
+                at[l] = z + min(L * q + l, lines - 1) * ls;
+                even[l] = odd[l] = make_double2(0.0, 0.0);
+            }
             int p = 0;
-            const int dp = c * n2;  // < n
-            for (int a = 0; a < n1; ++a) {
+#pragma unroll 4
+            for (int b = 0; b < n; ++b) {
                 const double2 w = tw[p];
 #pragma unroll
-                for (int l = 0; l < 4; ++l)
-                    if (4 * q + l < lines) mac(acc[l], z[(4 * q + l) * ls + n2 * a + b], w);
-                p += dp;
+                for (int l = 0; l < L; ++l) {
+                    const double2 v = at[l][b];
+                    even[l].x = fma(v.x, w.x, even[l].x);
+                    even[l].y = fma(v.y, w.x, even[l].y);
+                    odd[l].x = fma(v.y, -w.y, odd[l].x);
+                    odd[l].y = fma(v.x, -w.y, odd[l].y);
+                }
+                p += k;
                 if (p >= n) p -= n;
             }
 #pragma unroll
-            for (int l = 0; l < 4; ++l)
-                if (4 * q + l < lines) y[(4 * q + l) * ls + i + c] = acc[l];
+            for (int l = 0; l < L; ++l) {
+                if (L * q + l >= lines) break;
+                emit(L * q + l, k, make_double2(even[l].x + odd[l].x, even[l].y - odd[l].y));
+                if (k > 0 && 2 * k < n)
+                    emit(L * q + l, n - k,
+                         make_double2(even[l].x - odd[l].x, even[l].y + odd[l].y));
+            }
         }
         __syncthreads();
+        return;
     }
-    const double2* src = n1 > 1 ? y : z;
+    for (int t = threadIdx.x; t < lb * n; t += kSpecBlock) {
+        const int q = t / n, i = t - q * n;  // i = c n2 + b
+        const int c = i / n2, b = i - c * n2;
+        const double2* at[L];
+        double2 acc[L];
+#pragma unroll
+        for (int l = 0; l < L; ++l) {
+            at[l] = z + min(L * q + l, lines - 1) * ls + b;
+            acc[l] = make_double2(0.0, 0.0);
+        }
+        int p = 0;
+        const int dp = c * n2;  // < n
+#pragma unroll 4
+        for (int a = 0; a < n1; ++a) {
+            const double2 w = tw[p];
+#pragma unroll
+            for (int l = 0; l < L; ++l) mac(acc[l], at[l][n2 * a], w);
+            p += dp;
+            if (p >= n) p -= n;
+        }
+#pragma unroll
+        for (int l = 0; l < L; ++l)
+            if (L * q + l < lines) y[(L * q + l) * ls + i + c] = acc[l];
+    }
+    __syncthreads();
     for (int t = threadIdx.x; t < lb * n; t += kSpecBlock) {
         const int q = t / n, k = t - q * n;
-        const int c = n1 > 1 ? k % n1 : 0;
-        double2 acc[4];
+        const int c = k % n1;
+        const double2* at[L];
+        double2 acc[L];
 #pragma unroll
-        for (int l = 0; l < 4; ++l) acc[l] = make_double2(0.0, 0.0);
+        for (int l = 0; l < L; ++l) {
+            at[l] = y + min(L * q + l, lines - 1) * ls + c * (n2 + 1);
+            acc[l] = make_double2(0.0, 0.0);
+        }
         int p = 0;
+#pragma unroll 4
         for (int b = 0; b < n2; ++b) {
             const double2 w = tw[p];
 #pragma unroll
-            for (int l = 0; l < 4; ++l)
-                if (4 * q + l < lines) mac(acc[l], src[(4 * q + l) * ls + c * (n2 + 1) + b], w);
+            for (int l = 0; l < L; ++l) mac(acc[l], at[l][b], w);
             p += k;
             if (p >= n) p -= n;
         }
 #pragma unroll
-        for (int l = 0; l < 4; ++l)
-            if (4 * q + l < lines) emit(4 * q + l, k, acc[l]);
+        for (int l = 0; l < L; ++l)
+            if (L * q + l < lines) emit(L * q + l, k, acc[l]);
     }
     __syncthreads();
 }
 
 // Row pass: block = (row y, group of `lines` members); out[m][y][kx].
-template <typename T>
+template <typename T, int L>
 __global__ __launch_bounds__(kSpecBlock) void spectrum_rows_kernel(const T* __restrict__ f, int n,
                                                                    int n1, int members, int lines,
                                                                    double2* __restrict__ out) {
@@ -149,13 +196,14 @@ __global__ __launch_bounds__(kSpecBlock) void spectrum_rows_kernel(const T* __re
         }
         z[m * ls + x] = make_double2(jx / rho, jy / rho);
     }
-    transform(z, y2, tw, n, n1, n / n1, nm, [&](int l, int k, double2 v) {
+    transform<L>(z, y2, tw, n, n1, n / n1, nm, [&](int l, int k, double2 v) {
         out[((size_t)(m0 + l) * n + y) * n + k] = v;
     });
 }
 
 // Column pass: block = (tile of `lines` kx, group of kColMembers members);
 // e[group][ky][kx] = sum over the group's members of |Z|^2 / 2.
+template <int L>
 __global__ __launch_bounds__(kSpecBlock) void spectrum_cols_kernel(const double2* __restrict__ rows,
                                                                    int n, int n1, int members,
                                                                    int lines,
@@ -177,7 +225,7 @@ __global__ __launch_bounds__(kSpecBlock) void spectrum_cols_kernel(const double2
             z[l * ls + y] = rows[((size_t)m * n + y) * n + kx0 + l];
         }
         const bool first = m == group * kColMembers;
-        transform(z, y2, tw, n, n1, n / n1, nl, [&](int l, int k, double2 v) {
+        transform<L>(z, y2, tw, n, n1, n / n1, nl, [&](int l, int k, double2 v) {
             // (the same thread visits (l, k) for every member)
             double* p = eg + (size_t)k * n + kx0 + l;
             const double w = 0.5 * (v.x * v.x + v.y * v.y);
@@ -367,8 +415,9 @@ __global__ __launch_bounds__(kSpecBlock) void spectrum_fold_kernel(double* __res
 // Shell pass: block k.  E[k] = sum over the modes of shell k, floor(|k'| + 1/2) = k, of e,
 // / (M n^4): a thread takes one sign of ky and the columns kx = t, t + 128, ..., whose
 // modes of the shell lie within two of sqrt((k +- 1/2)^2 - kx^2), in ascending |ky|.
+// e: the sums of `groups` groups of members, added up here in group order.
 __global__ __launch_bounds__(kSpecBlock) void spectrum_shell_kernel(const double* __restrict__ e,
-                                                                    int n, int members,
+                                                                    int n, int groups, int members,
                                                                     double* __restrict__ E) {
     __shared__ double red[kSpecBlock];
     const int k = blockIdx.x;
@@ -380,11 +429,16 @@ __global__ __launch_bounds__(kSpecBlock) void spectrum_shell_kernel(const double
         if (abs(kxs) > k + 1) continue;
         const double in2 = (k - 0.5) * (k - 0.5) - (double)kxs * kxs;
         const double out2 = (k + 0.5) * (k + 0.5) - (double)kxs * kxs;
-        const int hi = min(out2 > 0.0 ? (int)sqrt(out2) + 2 : 1, top);
-        const int lo = max(k > 0 && in2 > 0.0 ? (int)sqrt(in2) - 2 : 0, neg ? 1 : 0);
+        const int hi = min(out2 > 0.0 ? (int)sqrtf((float)out2) + 2 : 1, top);
+        const int lo = max(k > 0 && in2 > 0.0 ? (int)sqrtf((float)in2) - 2 : 0, neg ? 1 : 0);
+        // floor(|k'| + 1/2) = k in whole numbers: k^2 - k < |k'|^2 <= k^2 + k (0 for k = 0)
+#pragma unroll 4
         for (int s = lo; s <= hi; ++s) {
-            if ((int)floor(sqrt((double)(kxs * kxs + s * s)) + 0.5) != k) continue;
-            acc += e[(size_t)(neg ? n - s : s) * n + kx];
+            const int r2 = kxs * kxs + s * s;
+            const double* at = e + (size_t)(neg ? n - s : s) * n + kx;
+            double mode = at[0];
+            for (int g = 1; g < groups; ++g) mode += at[(size_t)g * n * n];
+            acc += r2 <= k * k + k && (k == 0 || r2 > k * k - k) ? mode : 0.0;
         }
     }
     red[threadIdx.x] = acc;
@@ -406,31 +460,52 @@ hipError_t allow_spec_lds(K kernel, size_t bytes) {
                                (int)bytes);
 }
 
+template <typename T, int L>
+hipError_t launch_rows_any(const void* f, int n, int n1, int members, int lines, double2* rows,
+                           hipStream_t s) {
+    const size_t lds = spec_lds(n, n1, lines);
+    hipError_t err = allow_spec_lds(spectrum_rows_kernel<T, L>, lds);
+    if (err != hipSuccess) return err;
+    spectrum_rows_kernel<T, L><<<n * ((members + lines - 1) / lines), kSpecBlock, lds, s>>>(
+        (const T*)f, n, n1, members, lines, rows);
+    return hipGetLastError();
+}
+
+template <int L>
+hipError_t launch_cols_any(const double2* rows, int n, int n1, int members, int lines, double* e,
+                           hipStream_t s) {
+    const size_t lds = spec_lds(n, n1, lines);
+    hipError_t err = allow_spec_lds(spectrum_cols_kernel<L>, lds);
+    if (err != hipSuccess) return err;
+    spectrum_cols_kernel<L><<<col_groups(members) * ((n + lines - 1) / lines), kSpecBlock, lds, s>>>(
+        rows, n, n1, members, lines, e);
+    return hipGetLastError();
+}
+
 // Row and column passes: e[group][ky][kx] from the state.
 hipError_t launch_passes_any(const void* f, int n, int members, int storage, double2* rows, double* e,
                              hipStream_t s) {
     const int n1 = spec_factor(n);
     int most = 1;
     while (most < members && most < 16) most *= 2;
-    const int rl = spec_lines(n, n1, most), cl = spec_lines(n, n1, 8);
-    const size_t row_lds = spec_lds(n, n1, rl), col_lds = spec_lds(n, n1, cl);
-    const int row_blocks = n * ((members + rl - 1) / rl);
-    hipError_t err;
-    if (storage == kStoreF32Dev) {
-        if ((err = allow_spec_lds(spectrum_rows_kernel<float>, row_lds)) != hipSuccess) return err;
-        spectrum_rows_kernel<float><<<row_blocks, kSpecBlock, row_lds, s>>>((const float*)f, n, n1,
-                                                                            members, rl, rows);
-    } else {
-        if ((err = allow_spec_lds(spectrum_rows_kernel<double>, row_lds)) != hipSuccess) return err;
-        spectrum_rows_kernel<double><<<row_blocks, kSpecBlock, row_lds, s>>>((const double*)f, n, n1,
-                                                                             members, rl, rows);
-    }
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    if ((err = allow_spec_lds(spectrum_cols_kernel, col_lds)) != hipSuccess) return err;
-    const int groups = col_groups(members);
-    spectrum_cols_kernel<<<groups * ((n + cl - 1) / cl), kSpecBlock, col_lds, s>>>(rows, n, n1,
-                                                                                   members, cl, e);
-    return hipGetLastError();
+    int rl = spec_lines(n, n1, most), cl = spec_lines(n, n1, 8);
+    // (lines shared by a block save LDS reads, but few members leave few blocks: then fewer
+    // lines each until two blocks per CU have work.  us, all passes, 16 and 8
+    // lines / this: 251^2 x 1 161 / 76)
+    while (rl > 1 && n * ((members + rl - 1) / rl) < 512) rl /= 2;
+    while (cl > 1 && col_groups(members) * ((n + cl - 1) / cl) < 512) cl /= 2;
+    hipError_t err =
+        storage == kStoreF32Dev
+            ? (rl >= 4   ? launch_rows_any<float, 4>(f, n, n1, members, rl, rows, s)
+               : rl == 2 ? launch_rows_any<float, 2>(f, n, n1, members, rl, rows, s)
+                         : launch_rows_any<float, 1>(f, n, n1, members, rl, rows, s))
+            : (rl >= 4   ? launch_rows_any<double, 4>(f, n, n1, members, rl, rows, s)
+               : rl == 2 ? launch_rows_any<double, 2>(f, n, n1, members, rl, rows, s)
+                         : launch_rows_any<double, 1>(f, n, n1, members, rl, rows, s));
+    if (err != hipSuccess) return err;
+    return cl >= 4   ? launch_cols_any<4>(rows, n, n1, members, cl, e, s)
+           : cl == 2 ? launch_cols_any<2>(rows, n, n1, members, cl, e, s)
+                     : launch_cols_any<1>(rows, n, n1, members, cl, e, s);
 }
 
 template <typename T, int N1, int N2>
@@ -471,7 +546,7 @@ hipError_t launch_energy_spectrum(const void* f, int n, int members, int storage
                                   void* scratch, double* E, hipStream_t s) {
     double2* rows = reinterpret_cast<double2*>(scratch);
     double* e = reinterpret_cast<double*>(rows + (size_t)members * n * n);
-    const int groups = col_groups(members);
+    int groups = col_groups(members);
     // (the sizes whose two factors are 8 or 16 transform in registers, 252 -> 91 us for both passes
     // at 256^2 x 64; same results to rounding)
     hipError_t err = n == 256   ? launch_passes<16, 16>(f, members, storage, rows, e, s)
@@ -479,12 +554,15 @@ hipError_t launch_energy_spectrum(const void* f, int n, int members, int storage
                      : n == 64  ? launch_passes<8, 8>(f, members, storage, rows, e, s)
                                 : launch_passes_any(f, n, members, storage, rows, e, s);
     if (err != hipSuccess) return err;
-    if (groups > 1) {
+    // (few modes in few groups: the shells add them up themselves, a launch less: 16^2 x 8
+    // 20.6 -> 18.2 us; 31^2 x 64 in 32 groups 38 -> 80)
+    if (groups > 4 || (groups > 1 && n * n * groups > 32768)) {
         spectrum_fold_kernel<<<(n * n + kSpecBlock - 1) / kSpecBlock, kSpecBlock, 0, s>>>(e, n * n,
                                                                                           groups);
         if ((err = hipGetLastError()) != hipSuccess) return err;
+        groups = 1;
     }
-    spectrum_shell_kernel<<<kmax + 1, kSpecBlock, 0, s>>>(e, n, members, E);
+    spectrum_shell_kernel<<<kmax + 1, kSpecBlock, 0, s>>>(e, n, groups, members, E);
     return hipGetLastError();
 }
 
