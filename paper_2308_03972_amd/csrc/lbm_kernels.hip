@@ -576,27 +576,30 @@ __global__ __launch_bounds__(1024) void stream_collide_tile_kernel(
 
 // ---------------------------------------------------------------------------
 // conversions between the member-fastest storage and x-fastest fields.  A block takes
-// `tile` consecutive nodes of one lattice row for `mg` members (128 bytes of one
+// `tile` consecutive nodes (across the ends of lattice rows) for `mg` members (128 bytes of one
 // population where the ensemble has that many) and all nine populations through an LDS
 // tile [9][mg][tile + 1], so that both sides move whole cache lines: HBM-bound.  (One
 // thread per element with one side strided by 9 M elements fetched every line once
-// per member: 256^2 x 64 FP64 import 391 us, export 715, moments 645.)
+// per member: 256^2 x 64 FP64 import 391 us, export 715, moments 645.)  The member groups of a
+// tile follow each other on one XCD: where a group is no whole number of lines they share
+// some, which its L2 then completes.
 // ---------------------------------------------------------------------------
 struct ConvTile {
     int nx, ny, members;
     int log_tile, mg, groups, tiles;  // tile = 1 << log_tile nodes
-    // block -> (row, first node, first member, members and nodes of this block)
-    __device__ __forceinline__ void at(int b, int* y, int* x0, int* m0, int* nm, int* nn) const {
-        const int g = b % groups, t = b / groups;
-        *y = t / tiles;
-        *x0 = (t % tiles) << log_tile;
-        *m0 = g * mg;
+    // block -> (first node, first member, members and nodes of this block)
+    __device__ __forceinline__ void at(int b, int blocks, int* i0, int* m0, int* nm,
+                                       int* nn) const {
+        b = dev::xcd_remap(b, blocks);
+        const int t = b / groups;
+        *i0 = t << log_tile;
+        *m0 = (b - t * groups) * mg;
         *nm = min(mg, members - *m0);
-        *nn = min(1 << log_tile, nx - *x0);
+        *nn = min(1 << log_tile, nx * ny - *i0);
     }
 };
 
-// Threads 0 .. 255 step through (row = a * nm + m, x) with x fastest ...
+// Threads 0 .. 255 step through (row = a * nm + m, x) with x fastest, a thread's x fixed ...
 template <typename F>
 __device__ __forceinline__ void for_rows(int rows, int log_tile, int nn, F f) {
     const int x = threadIdx.x & ((1 << log_tile) - 1);
@@ -620,18 +623,19 @@ __global__ __launch_bounds__(kBlock) void import_kernel(const double* __restrict
                                                         T* __restrict__ f, ConvTile c) {
     extern __shared__ char lds_raw[];
     T* tile = reinterpret_cast<T*>(lds_raw);
-    int y, x0, m0, nm, nn;
-    c.at(blockIdx.x, &y, &x0, &m0, &nm, &nn);
+    int i0, m0, nm, nn;
+    c.at(blockIdx.x, gridDim.x, &i0, &m0, &nm, &nn);
     const int ts = (1 << c.log_tile) + 1;
     const size_t plane = (size_t)c.nx * c.ny;
+    const int node = i0 + (threadIdx.x & (ts - 2)), ny = node / c.nx, nx = node - ny * c.nx;
     for_rows(9 * nm, c.log_tile, nn, [&](int row, int x) {
         const int a = row / nm, m = row - a * nm;
-        const int xs = wrap1(x0 + x + cx_dyn(a), c.nx), ys = wrap1(y + cy_dyn(a), c.ny);
+        const int xs = wrap1(nx + cx_dyn(a), c.nx), ys = wrap1(ny + cy_dyn(a), c.ny);
         tile[(size_t)row * ts + x] = PopIO<T>::pack(
             canon[((size_t)(m0 + m) * 9 + a) * plane + (size_t)ys * c.nx + xs], w_dyn(a));
     });
     __syncthreads();
-    T* const out = f + ((size_t)y * c.nx + x0) * 9 * c.members + m0;
+    T* const out = f + (size_t)i0 * 9 * c.members + m0;
     for_members(9 * nn, nm, [&](int row, int m) {
         const int x = row / 9, a = row - 9 * x;
         out[(size_t)row * c.members + m] = tile[(size_t)(a * nm + m) * ts + x];
@@ -644,19 +648,20 @@ __global__ __launch_bounds__(kBlock) void export_kernel(const T* __restrict__ f,
                                                         double* __restrict__ canon, ConvTile c) {
     extern __shared__ char lds_raw[];
     T* tile = reinterpret_cast<T*>(lds_raw);
-    int y, x0, m0, nm, nn;
-    c.at(blockIdx.x, &y, &x0, &m0, &nm, &nn);
+    int i0, m0, nm, nn;
+    c.at(blockIdx.x, gridDim.x, &i0, &m0, &nm, &nn);
     const int ts = (1 << c.log_tile) + 1;
     const size_t plane = (size_t)c.nx * c.ny;
-    const T* const in = f + ((size_t)y * c.nx + x0) * 9 * c.members + m0;
+    const T* const in = f + (size_t)i0 * 9 * c.members + m0;
     for_members(9 * nn, nm, [&](int row, int m) {
         const int x = row / 9, a = row - 9 * x;
         tile[(size_t)(a * nm + m) * ts + x] = in[(size_t)row * c.members + m];
     });
     __syncthreads();
+    const int node = i0 + (threadIdx.x & (ts - 2)), ny = node / c.nx, nx = node - ny * c.nx;
     for_rows(9 * nm, c.log_tile, nn, [&](int row, int x) {
         const int a = row / nm, m = row - a * nm;
-        const int xs = wrap1(x0 + x + cx_dyn(a), c.nx), ys = wrap1(y + cy_dyn(a), c.ny);
+        const int xs = wrap1(nx + cx_dyn(a), c.nx), ys = wrap1(ny + cy_dyn(a), c.ny);
         canon[((size_t)(m0 + m) * 9 + a) * plane + (size_t)ys * c.nx + xs] =
             PopIO<T>::unpack(tile[(size_t)row * ts + x], w_dyn(a));
     });
@@ -670,24 +675,25 @@ __global__ __launch_bounds__(kBlock) void init_equilibrium_kernel(
     ConvTile c) {
     extern __shared__ char lds_raw[];
     double* tile = reinterpret_cast<double*>(lds_raw);
-    int y, x0, m0, nm, nn;
-    c.at(blockIdx.x, &y, &x0, &m0, &nm, &nn);
+    int i0, m0, nm, nn;
+    c.at(blockIdx.x, gridDim.x, &i0, &m0, &nm, &nn);
     const int ts = (1 << c.log_tile) + 1;
-    const size_t plane = (size_t)c.nx * c.ny, row0 = (size_t)y * c.nx + x0;
-    for_rows(3 * nm, c.log_tile, nn, [&](int row, int x) {
+    const size_t plane = (size_t)c.nx * c.ny;
+    for_rows((rho_in ? 3 : 2) * nm, c.log_tile, nn, [&](int row, int x) {
         const int k = row / nm, m = m0 + row - k * nm;
         const double* src = k == 2 ? rho_in + (size_t)m * plane : uv + ((size_t)m * 2 + k) * plane;
-        tile[(size_t)row * ts + x] = (k == 2 && !rho_in) ? 1.0 : src[row0 + x];
+        tile[(size_t)row * ts + x] = src[i0 + x];
     });
     __syncthreads();
-    for_members(nn, nm, [&](int x, int m) {
-        const double u = tile[(size_t)m * ts + x], v = tile[(size_t)(nm + m) * ts + x];
-        const double rho = tile[(size_t)(2 * nm + m) * ts + x];
+    for_members(nn, nm, [&](int i, int m) {
+        const int y = (i0 + i) / c.nx, x = i0 + i - y * c.nx;
+        const double u = tile[(size_t)m * ts + i], v = tile[(size_t)(nm + m) * ts + i];
+        const double rho = rho_in ? tile[(size_t)(2 * nm + m) * ts + i] : 1.0;
         const double usq = 1.5 * (u * u + v * v);
 #pragma unroll
         for (int a = 0; a < 9; ++a) {
             const double cu = cx_of(a) * u + cy_of(a) * v;
-            PopIO<T>::store(f + slot(src_node(x0 + x, y, a, c.nx, c.ny), a, m0 + m, c.members), a,
+            PopIO<T>::store(f + slot(src_node(x, y, a, c.nx, c.ny), a, m0 + m, c.members), a,
                             rho * w_of(a) * (1.0 + 3.0 * cu + 4.5 * cu * cu - usq));
         }
     });
@@ -699,29 +705,29 @@ __global__ __launch_bounds__(kBlock) void moments_kernel(const T* __restrict__ f
                                                          double* __restrict__ out, ConvTile c) {
     extern __shared__ char lds_raw[];
     double* tile = reinterpret_cast<double*>(lds_raw);
-    int y, x0, m0, nm, nn;
-    c.at(blockIdx.x, &y, &x0, &m0, &nm, &nn);
+    int i0, m0, nm, nn;
+    c.at(blockIdx.x, gridDim.x, &i0, &m0, &nm, &nn);
     const int ts = (1 << c.log_tile) + 1;
     const size_t plane = (size_t)c.nx * c.ny;
-    for_members(nn, nm, [&](int x, int m) {
+    for_members(nn, nm, [&](int i, int m) {
+        const int y = (i0 + i) / c.nx, x = i0 + i - y * c.nx;
         double rho = 0.0, jx = 0.0, jy = 0.0;
 #pragma unroll
         for (int a = 0; a < 9; ++a) {
             const double fa = PopIO<T>::load(
-                f + slot(src_node(x0 + x, y, a, c.nx, c.ny), a, m0 + m, c.members), a);
+                f + slot(src_node(x, y, a, c.nx, c.ny), a, m0 + m, c.members), a);
             rho += fa;
             jx += cx_of(a) * fa;
             jy += cy_of(a) * fa;
         }
-        tile[(size_t)m * ts + x] = rho;
-        tile[(size_t)(nm + m) * ts + x] = jx / rho;
-        tile[(size_t)(2 * nm + m) * ts + x] = jy / rho;
+        tile[(size_t)m * ts + i] = rho;
+        tile[(size_t)(nm + m) * ts + i] = jx / rho;
+        tile[(size_t)(2 * nm + m) * ts + i] = jy / rho;
     });
     __syncthreads();
     for_rows(3 * nm, c.log_tile, nn, [&](int row, int x) {
         const int k = row / nm, m = row - k * nm;
-        out[((size_t)(m0 + m) * 3 + k) * plane + (size_t)y * c.nx + x0 + x] =
-            tile[(size_t)row * ts + x];
+        out[((size_t)(m0 + m) * 3 + k) * plane + i0 + x] = tile[(size_t)row * ts + x];
     });
 }
 
@@ -733,7 +739,7 @@ ConvTile conv_tile(LbmDims d, int elem_bytes) {
     c.groups = (d.members + most - 1) / most;
     c.mg = (d.members + c.groups - 1) / c.groups;
     while (c.log_tile < 8 && (c.mg * elem_bytes << (c.log_tile + 1)) <= 128 * 32) ++c.log_tile;
-    c.tiles = (d.nx + (1 << c.log_tile) - 1) >> c.log_tile;
+    c.tiles = (d.nx * d.ny + (1 << c.log_tile) - 1) >> c.log_tile;
     return c;
 }
 
@@ -1097,7 +1103,7 @@ hipError_t launch_stream_collide2_batch(const LbmTask* d_tasks, int ntasks, int 
 hipError_t launch_import(const double* canon, void* f, LbmDims d, int storage, hipStream_t s) {
     const int eb = (int)state_elem_bytes(storage);
     const ConvTile c = conv_tile(d, eb);
-    const int blocks = d.ny * c.tiles * c.groups;
+    const int blocks = c.tiles * c.groups;
     const size_t lds = (size_t)9 * c.mg * ((1 << c.log_tile) + 1) * eb;
     if (storage == kStoreF32Dev) import_kernel<float><<<blocks, kBlock, lds, s>>>(canon, (float*)f, c);
     else import_kernel<double><<<blocks, kBlock, lds, s>>>(canon, (double*)f, c);
@@ -1107,7 +1113,7 @@ hipError_t launch_import(const double* canon, void* f, LbmDims d, int storage, h
 hipError_t launch_export(const void* f, double* canon, LbmDims d, int storage, hipStream_t s) {
     const int eb = (int)state_elem_bytes(storage);
     const ConvTile c = conv_tile(d, eb);
-    const int blocks = d.ny * c.tiles * c.groups;
+    const int blocks = c.tiles * c.groups;
     const size_t lds = (size_t)9 * c.mg * ((1 << c.log_tile) + 1) * eb;
     if (storage == kStoreF32Dev)
         export_kernel<float><<<blocks, kBlock, lds, s>>>((const float*)f, canon, c);
@@ -1119,7 +1125,7 @@ hipError_t launch_export(const void* f, double* canon, LbmDims d, int storage, h
 hipError_t launch_init_equilibrium(const double* rho, const double* uv, void* f, LbmDims d,
                                    int storage, hipStream_t s) {
     const ConvTile c = conv_tile(d, (int)state_elem_bytes(storage));
-    const int blocks = d.ny * c.tiles * c.groups;
+    const int blocks = c.tiles * c.groups;
     const size_t lds = (size_t)3 * c.mg * ((1 << c.log_tile) + 1) * sizeof(double);
     if (storage == kStoreF32Dev)
         init_equilibrium_kernel<float><<<blocks, kBlock, lds, s>>>(rho, uv, (float*)f, c);
@@ -1130,7 +1136,7 @@ hipError_t launch_init_equilibrium(const double* rho, const double* uv, void* f,
 
 hipError_t launch_moments(const void* f, double* out, LbmDims d, int storage, hipStream_t s) {
     const ConvTile c = conv_tile(d, (int)state_elem_bytes(storage));
-    const int blocks = d.ny * c.tiles * c.groups;
+    const int blocks = c.tiles * c.groups;
     const size_t lds = (size_t)3 * c.mg * ((1 << c.log_tile) + 1) * sizeof(double);
     if (storage == kStoreF32Dev)
         moments_kernel<float><<<blocks, kBlock, lds, s>>>((const float*)f, out, c);
