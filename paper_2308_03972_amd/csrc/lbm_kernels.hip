@@ -789,15 +789,17 @@ constexpr TileFit kTileFit[3][2] = {  // FP64, FP32, FP32 pairs of members; item
      {3.78, 1.19, 0.0339, 0.0396, 0.245, 0.0, 0.0, 0.0399, 0.0126}}};
 constexpr int kMostTileLds = 80 * 1024;  // two blocks per CU
 
-// Lines of `line` bytes that a block's members of one population touch, mean over the
-// rows' alignments and the member groups.
-double lines_touched(int members, int mg, int elem, int line) {
+// Lines of 1 << log_line bytes that a block's members of one population touch, mean over the
+// rows' alignments (they repeat after a line's worth of elements) and the member groups.
+double lines_touched(int members, int mg, int elem, int log_line) {
+    int rows = 1;
+    while ((rows * members * elem) & ((1 << log_line) - 1)) rows *= 2;
     int total = 0, n = 0;
-    for (int row = 0; row < 32; ++row)
+    for (int row = 0; row < rows; ++row)
         for (int m0 = 0; m0 < members; m0 += mg, ++n) {
             const int first = (row * members + m0) * elem;
             const int last = first + (members - m0 < mg ? members - m0 : mg) * elem - 1;
-            total += last / line - first / line + 1;
+            total += (last >> log_line) - (first >> log_line) + 1;
         }
     return (double)total / n;
 }
@@ -810,27 +812,43 @@ struct TileCost {
         : members(d.members), elem((int)state_elem_bytes(storage)), V(V_), mg(mg_),
           groups((d.members + mg_ - 1) / mg_),
           fit(kTileFit[V_ == 2 ? 2 : (storage == kStoreF32Dev ? 1 : 0)]),
-          l64(lines_touched(d.members, mg_, elem, 64)),
-          l128(lines_touched(d.members, mg_, elem, 128)) {}
-    // us per step of a launch of pl.steps, or a large number where it does not fit
+          l64(lines_touched(d.members, mg_, elem, 6)),
+          l128(lines_touched(d.members, mg_, elem, 7)) {}
+    int lds(int rx, int ry) const { return 9 * rx * ry * mg * elem; }
+    int threads(int rx, int ry, int items) const {
+        const int n = rx * ry * mg >> (V - 1);  // (V, items: 1 or 2)
+        return (((n + items - 1) >> (items - 1)) + kWave - 1) / kWave * kWave;
+    }
+    // us per step of a launch of pl.steps on `tiles` tiles, or a large number where it does
+    // not fit
     double operator()(LbmDims d, const StepPlan& pl) const {
         const int tx = pl.rx - 2 * (pl.steps - 1), ty = pl.ry - 2 * (pl.steps - 1);
-        const int lds = 9 * pl.rx * pl.ry * mg * elem;
-        const int items = pl.rx * pl.ry * mg / V;
-        const int threads = ((items + pl.items - 1) / pl.items + kWave - 1) / kWave * kWave;
-        if (lds > kMostTileLds || threads > 1024) return 1e30;
-        const int blocks = ((d.nx + tx - 1) / tx) * ((d.ny + ty - 1) / ty) * groups;
-        const int per_cu = std::min(160 * 1024 / lds, 1024 / threads);
-        const int round = 256 * per_cu;
-        const int rounds = (blocks + round - 1) / round;
-        const int mine = blocks / round * per_cu + (blocks % round + 255) / 256;
-        const double waves = (double)mine * threads / kWave * pl.items;
+        return (*this)(pl, ((d.nx + tx - 1) / tx) * ((d.ny + ty - 1) / ty));
+    }
+    // (or takes more than `limit` us per step)
+    double operator()(const StepPlan& pl, int tiles, double limit = 1e30) const {
+        const int tx = pl.rx - 2 * (pl.steps - 1), ty = pl.ry - 2 * (pl.steps - 1);
+        const int bytes = lds(pl.rx, pl.ry);
+        const int thr = threads(pl.rx, pl.ry, pl.items);
+        if (bytes > kMostTileLds || thr > 1024) return 1e30;
+        const int blocks = tiles * groups;
         const double rows = (double)(pl.rx * pl.ry + tx * ty) * 9;  // of one block
-        const double kb = rows * mine / 1e3, mb = rows * blocks / 1e6;
+        const double mb = rows * blocks / 1e6;
         const TileFit& f = fit[pl.items - 1];
-        return (f.launch + f.round_step * rounds * pl.steps + waves * (f.wave + f.wave_step * pl.steps) +
-                kb * (f.lines64 * l64 + f.lines128 * l128 + f.bytes * mg * elem) +
-                mb * (f.all_bytes * mg * elem + f.all_lines * l128 * 128)) / pl.steps;
+        const double wave = (double)thr / kWave * pl.items * (f.wave + f.wave_step * pl.steps);
+        const double lines = f.lines64 * l64 + f.lines128 * l128 + f.bytes * mg * elem;
+        const double all = mb * (f.all_bytes * mg * elem + f.all_lines * l128 * 128);
+        // (a CU has at least blocks / 256 blocks, in one round or more)
+        if (f.launch + f.round_step * pl.steps + all + blocks / 256.0 * (wave + rows / 1e3 * lines) >
+            1.000001 * limit * pl.steps)
+            return 1e30;
+        const int per_cu = std::min(160 * 1024 / bytes, 1024 / thr);
+        const int round = 256 * per_cu;
+        const int full = blocks / round, rest = blocks - full * round;
+        const int rounds = full + (rest > 0);
+        const int mine = full * per_cu + (rest + 255) / 256;
+        return (f.launch + f.round_step * rounds * pl.steps + mine * (wave + rows / 1e3 * lines) + all) /
+               pl.steps;
     }
 };
 
@@ -893,20 +911,35 @@ StepPlans step_plans(LbmDims d, int storage) {
             guard[n] = 0.92 * out.us[n];
         }
     }
+    constexpr int kLeastTile = 4, kMostTile = 32;
+    int tiles_x[kMostTile + 1], tiles_y[kMostTile + 1];
+    for (int t = kLeastTile; t <= kMostTile; ++t) {
+        tiles_x[t] = (d.nx + t - 1) / t;
+        tiles_y[t] = (d.ny + t - 1) / t;
+    }
     auto search = [&](int mg, int k0, int k1) {
         if (mg > M || mg % V) return;
         const TileCost cost(d, storage, V, mg);
         for (int k = k0; k <= k1; ++k)
-            for (int tx = 4; tx <= 32; ++tx)
-                for (int ty = 4; ty <= 32; ++ty)
-                    for (int i = 1; i <= 2; ++i) {
-                        const StepPlan pl{k, tx + 2 * (k - 1), ty + 2 * (k - 1), mg, i};
-                        const double t = k * cost(d, pl);
+            for (int tx = kLeastTile; tx <= kMostTile; ++tx) {
+                // (a wider tile costs more unless it saves one)
+                if (tx > kLeastTile && tiles_x[tx] == tiles_x[tx - 1]) continue;
+                for (int ty = kLeastTile; ty <= kMostTile; ++ty) {
+                    if (ty > kLeastTile && tiles_y[ty] == tiles_y[ty - 1]) continue;
+                    StepPlan pl{k, tx + 2 * (k - 1), ty + 2 * (k - 1), mg, 1};
+                    // (both grow with ty)
+                    if (cost.lds(pl.rx, pl.ry) > kMostTileLds ||
+                        cost.threads(pl.rx, pl.ry, 2) > 1024)
+                        break;
+                    for (; pl.items <= 2; ++pl.items) {
+                        const double t = k * cost(pl, tiles_x[tx] * tiles_y[ty], guard[k] / k);
                         if (t < guard[k]) {
                             guard[k] = out.us[k] = t;
                             out.p[k] = pl;
                         }
                     }
+                }
+            }
     };
     if (P > 5e3) search(base.members, 2, base.steps);
     if (pairs) {
