@@ -414,13 +414,9 @@ hipError_t launch_adjoint_tile_t(const void* fhi, const void* flast, size_t stri
     constexpr size_t kMostLds = 80 * 1024;  // every plan's region: two blocks per CU
     if (tile < 1 || threads > 1024 || lds > kMostLds || blocks > capacity)
         return hipErrorInvalidValue;
-    static bool attr = false;
-    if (!attr) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(adjoint_tile_kernel<T>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMostLds);
-        if (e != hipSuccess) return e;
-        attr = true;
-    }
+    static std::atomic<uint64_t> lds_ok{0};
+    const hipError_t e = allow_lds(adjoint_tile_kernel<T>, kMostLds, &lds_ok);
+    if (e != hipSuccess) return e;
     adjoint_tile_kernel<T><<<blocks, threads, lds, s>>>(
         (const T*)fhi, (const T*)flast, stride_bytes / sizeof(T), lam_in, lam_out, force, d.nx, d.ny,
         d.members, tau0, K, mu, R, pl.members, steps, k_partial);

@@ -4,6 +4,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstddef>
 #include <cstdint>
 
@@ -29,6 +30,23 @@ __host__ __device__ __forceinline__ double w_dyn(int a) {
 }
 
 constexpr int kWave = 64;
+
+// Dynamic LDS beyond 64 KiB needs the kernel's permission, on every device it is launched on:
+// `devices` (one per kernel, a bit per device, any thread) holds where it has been given.
+// A kernel asks for the same `bytes` every time.
+template <typename K>
+inline hipError_t allow_lds(K kernel, size_t bytes, std::atomic<uint64_t>* devices) {
+    if (bytes <= 65536) return hipSuccess;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = dev < 64 ? uint64_t{1} << dev : 0;
+    if (devices->load(std::memory_order_acquire) & bit) return hipSuccess;
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e == hipSuccess) devices->fetch_or(bit, std::memory_order_release);
+    return e;
+}
 
 // Population storage layout: [node][a][member], node = y * nx + x, members
 // fastest, so the M values of one population of one node are contiguous and a
@@ -327,13 +345,13 @@ hipError_t launch_zero_ints(int* v, int n, hipStream_t s);
 // the most any of these kernels keeps resident), at most `items`; blocks
 // beyond what fits start later and find the queue drained or nearly so.
 inline int persistent_blocks(int threads, int items) {
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0;
+    static const int cus = [] {
+        int dev = 0, n = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-            cus = 256;
-    }
+            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+            n = 256;
+        return n;
+    }();
     const int g = cus * 16 * 64 / threads;  // a multiple of 8: every XCD range has blocks
     return g < items ? g : items;           // items < g: one block per entry
 }

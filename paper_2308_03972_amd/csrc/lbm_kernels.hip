@@ -1006,14 +1006,9 @@ hipError_t launch_tile_t(const void* fin, void* fout, const double* force, LbmDi
     const size_t lds = (size_t)9 * pl.rx * pl.ry * pl.members * sizeof(T);
     constexpr size_t kMostLds = kMostTileLds;
     if (threads > 1024 || lds > kMostLds || pl.members % V) return hipErrorInvalidValue;
-    static bool attr = false;
-    if (!attr) {
-        hipError_t e = hipFuncSetAttribute(
-            reinterpret_cast<const void*>(stream_collide_tile_kernel<T, V, I>),
-            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMostLds);
-        if (e != hipSuccess) return e;
-        attr = true;
-    }
+    static std::atomic<uint64_t> lds_ok{0};
+    const hipError_t e = allow_lds(stream_collide_tile_kernel<T, V, I>, kMostLds, &lds_ok);
+    if (e != hipSuccess) return e;
     stream_collide_tile_kernel<T, V, I><<<blocks, threads, lds, s>>>(
         (const T*)fin, (T*)fout, force, d.nx, d.ny, d.members, tau0, smag, mu, pl.rx, pl.ry,
         pl.members, steps, (T*)fmid, mid_bytes / sizeof(T));
@@ -1051,25 +1046,19 @@ hipError_t launch_stream_collide2(const void* fin, void* fout, const double* for
     const double smag = 18.0 * sqrt(2.0) * cs * cs;
     hipError_t e = hipSuccess;
     if (storage == kStoreF32Dev) {
-        static bool attr32 = false, attr16 = false;
+        static std::atomic<uint64_t> ok32{0}, ok16{0};
         if (d.members % 32 == 0) {
             const size_t bytes = (size_t)kTwoR * kTwoR * 9 * 32 * sizeof(float);
-            if (!attr32)
-                e = hipFuncSetAttribute(reinterpret_cast<const void*>(stream_collide2_dev_kernel<32>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+            e = allow_lds(stream_collide2_dev_kernel<32>, bytes, &ok32);
             if (e != hipSuccess) return e;
-            attr32 = true;
             stream_collide2_dev_kernel<32><<<tiles * (d.members / 32), dim3(16, kTwoR * kTwoR),
                                              bytes, s>>>((const float*)fin, (float*)fout, force,
                                                          d.nx, d.ny, d.members, (float)tau0,
                                                          (float)smag, (float)mu, (float*)fmid);
         } else {
             const size_t bytes = (size_t)kTwoR * kTwoR * 9 * 16 * sizeof(float);
-            if (!attr16)
-                e = hipFuncSetAttribute(reinterpret_cast<const void*>(stream_collide2_dev_kernel<16>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+            e = allow_lds(stream_collide2_dev_kernel<16>, bytes, &ok16);
             if (e != hipSuccess) return e;
-            attr16 = true;
             stream_collide2_dev_kernel<16><<<tiles * (d.members / 16), dim3(8, kTwoR * kTwoR),
                                              bytes, s>>>((const float*)fin, (float*)fout, force,
                                                          d.nx, d.ny, d.members, (float)tau0,
@@ -1079,12 +1068,9 @@ hipError_t launch_stream_collide2(const void* fin, void* fout, const double* for
     }
     const dim3 grid(tiles * (d.members / kTwoMG)), block(kTwoMG, kTwoR * kTwoR);
     const size_t bytes = (size_t)two_step_lds_doubles() * sizeof(double);
-    static bool attr = false;
-    if (!attr)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(stream_collide2_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    static std::atomic<uint64_t> lds_ok{0};
+    e = allow_lds(stream_collide2_kernel, bytes, &lds_ok);
     if (e != hipSuccess) return e;
-    attr = true;
     stream_collide2_kernel<<<grid, block, bytes, s>>>(
         (const double*)fin, (double*)fout, force, d.nx, d.ny, d.members, tau0, smag, mu,
         (double*)fmid);
@@ -1109,24 +1095,18 @@ int two_step_blocks(LbmDims d, int storage) {
 
 hipError_t launch_stream_collide2_batch(const LbmTask* d_tasks, int ntasks, int nblocks,
                                         int storage, hipStream_t s) {
-    static bool attr64 = false, attr32 = false;
+    static std::atomic<uint64_t> ok64{0}, ok32{0};
     hipError_t e = hipSuccess;
     if (storage == kStoreF32Dev) {
         const size_t bytes = (size_t)kTwoR * kTwoR * 9 * kTwoMG32 * sizeof(float);
-        if (!attr32)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(stream_collide2_batch_kernel<float>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        e = allow_lds(stream_collide2_batch_kernel<float>, bytes, &ok32);
         if (e != hipSuccess) return e;
-        attr32 = true;
         stream_collide2_batch_kernel<float><<<nblocks, dim3(kTwoMG32 / 2, kTwoR * kTwoR), bytes,
                                               s>>>(d_tasks, ntasks);
     } else {
         const size_t bytes = (size_t)two_step_lds_doubles() * sizeof(double);
-        if (!attr64)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(stream_collide2_batch_kernel<double>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        e = allow_lds(stream_collide2_batch_kernel<double>, bytes, &ok64);
         if (e != hipSuccess) return e;
-        attr64 = true;
         stream_collide2_batch_kernel<double><<<nblocks, dim3(kTwoMG, kTwoR * kTwoR), bytes, s>>>(
             d_tasks, ntasks);
     }

@@ -444,16 +444,6 @@ void analysis_eig_batch_kernel(const AnalysisParams* P, const int4* waves, int n
     else eig_body<N>(p, nodes, d.y, d.z, gout);
 }
 
-// Dynamic LDS beyond 64 KiB needs the kernel's permission (set once per kernel).
-template <typename K>
-hipError_t allow_lds(K kernel, size_t bytes, bool* done) {
-    if (bytes <= 65536 || *done) return hipSuccess;
-    hipError_t e = hipFuncSetAttribute((const void*)kernel,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    if (e == hipSuccess) *done = true;
-    return e;
-}
-
 __host__ __device__ inline int apply_lds_doubles(int n) {
     // G and h, dX [9][64], B [9][n], C [n][10], sw [n], mean increment [9],
     // x_bar [9], q [n]
@@ -736,7 +726,7 @@ hipError_t launch_jacobi_n(const AnalysisParams& p, const int* nodes, int count,
                            hipStream_t s) {
     const size_t bytes = (size_t)eig_lds_doubles<N>() * sizeof(double);
     constexpr int segs = kSplitRows<N> ? 1 : 64 / N;
-    static bool lds_ok = false;
+    static std::atomic<uint64_t> lds_ok{0};
     hipError_t e = allow_lds(analysis_eig_kernel<N>, bytes, &lds_ok);
     if (e != hipSuccess) return e;
     analysis_eig_kernel<N><<<(count + segs - 1) / segs, eig_threads<N>(), bytes, s>>>(p, nodes,
@@ -770,14 +760,14 @@ hipError_t launch_jacobi_batch_n(const AnalysisParams* d_params, const int4* d_e
     const size_t bytes = (size_t)eig_lds_doubles<N>() * sizeof(double);
     hipError_t e;
     if (counters) {
-        static bool lds_ok = false;
+        static std::atomic<uint64_t> lds_ok{0};
         e = allow_lds(analysis_eig_queue_kernel<N>, bytes, &lds_ok);
         if (e != hipSuccess) return e;
         analysis_eig_queue_kernel<N><<<persistent_blocks(eig_threads<N>(), n_eig), eig_threads<N>(),
                                        bytes, s>>>(d_params, d_eig_waves, n_eig, d_nodes, gbuf,
                                                    counters);
     } else {
-        static bool lds_ok = false;
+        static std::atomic<uint64_t> lds_ok{0};
         e = allow_lds(analysis_eig_batch_kernel<N>, bytes, &lds_ok);
         if (e != hipSuccess) return e;
         analysis_eig_batch_kernel<N><<<n_eig, eig_threads<N>(), bytes, s>>>(
