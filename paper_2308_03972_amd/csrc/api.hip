@@ -33,7 +33,7 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-    size_t fbuf, force, loc_pt, loc_g, pts, ybar, dY, dvec, K, yf, partial, counters, nodes, gbuf,
+    size_t fbuf, force, loc_pt, loc_g, pts, ybar, dY, dvec, K, partial, counters, nodes, gbuf,
         diag_node, diag_fold, total;
 };
 
@@ -120,7 +120,6 @@ struct Ctx {
     double* dY() const { return reinterpret_cast<double*>(ws + L.dY); }
     double* dvec() const { return reinterpret_cast<double*>(ws + L.dvec); }
     double* K() const { return route == 2 ? reinterpret_cast<double*>(ws + L.K) : nullptr; }
-    double* yf() const { return reinterpret_cast<double*>(ws + L.yf); }
     double* partial() const { return reinterpret_cast<double*>(ws + L.partial); }
     int* counters() const { return reinterpret_cast<int*>(ws + L.counters); }
     int* nodes() const { return reinterpret_cast<int*>(ws + L.nodes); }
@@ -321,7 +320,6 @@ Layout make_layout(const lbmletkf_lbm_params* p, const lbmletkf_obs_params* o, i
     L.dY = take(nobs * p->members * sizeof(double));
     L.dvec = take(nobs * sizeof(double));
     L.K = take(route == 2 ? nobs * nobs * sizeof(double) : 0);
-    L.yf = take(nobs * p->members * sizeof(double));
     L.partial = take((size_t)diag_blocks_for((int)plane) * 8 * sizeof(double));
     L.counters = take(16 * sizeof(int));
     L.nodes = take(plane * sizeof(int));
