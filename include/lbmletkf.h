@@ -160,8 +160,8 @@ lbmletkf_status observe(lbmletkf_ctx* ctx, const void* d_f, double* d_yf, void* 
 
 /* LETKF analysis (Sec. 3.2.1, Sec. 3.2.2), in place on d_f:
  * ensemble statistics of d_yf against d_yo[nvar * n_points], then at every
- * node the localized ensemble-space problem, its symmetric
- * eigendecomposition, w_bar, dW = [(M-1) P~a]^(1/2) and
+ * node the localized ensemble-space problem, the functions of its symmetric
+ * matrix that give w_bar and dW = [(M-1) P~a]^(1/2), and
  * x_m^a = x_bar + dX (w_bar + dW[:, m]) applied to the nine populations. */
 lbmletkf_status letkf_analyze(lbmletkf_ctx* ctx, void* d_f, const double* d_yf, const double* d_yo,
                               void* stream);
@@ -263,8 +263,9 @@ lbmletkf_status lbmletkf_set_matrix_core_transform(lbmletkf_ctx* ctx, int32_t en
  * of (|u_hat_m(k')|^2 + |v_hat_m(k')|^2) / 2, u_hat = n^-2 sum_xi u e^{-i k'.xi}
  * (xi in cells, k' in units of 2 pi / n), u = j / rho of member m.  Square
  * grids n <= 2048 only (LBMLETKF_ESHAPE otherwise).  Uses the workspace's
- * ping-pong buffer as scratch (free between calls).  Direct DFT sums in FP64,
- * deterministic; not for the hot loop (about 1 ms at 256^2 x 64 members). */
+ * ping-pong buffer as scratch (free between calls).  Transforms in two
+ * factors of n (direct sums for a prime n) in FP64, deterministic; for report
+ * times (about 0.1 ms at 256^2 x 64 members). */
 lbmletkf_status lbmletkf_energy_spectrum(lbmletkf_ctx* ctx, const void* d_f, double* d_E, int32_t kmax,
                                          void* stream);
 
@@ -309,7 +310,11 @@ lbmletkf_status lbmletkf_local_histogram(lbmletkf_ctx* ctx, int32_t* hist, int32
  * every steps_per_obs steps), two sets of the steps_per_obs - 1 states between
  * two checkpoints that the reverse sweep recomputes (one interval is
  * recomputed on a library-owned stream while the caller's stream runs the
- * adjoint steps of the next), two FP64 adjoint states and the partial sums.  lbmletkf_misfit_forward writes the checkpoints;
+ * adjoint steps of the next), two FP64 adjoint states and the partial sums.
+ * lbmletkf_misfit_forward writes the checkpoints, and into the two sets the
+ * states of the last two intervals while reverse sweeps follow (not when the
+ * one before was evaluated alone, nor once a reverse sweep of the context has
+ * been captured);
  * lbmletkf_misfit_backward reads them, so call it after a forward call with
  * the same d_f0, cs, steps_per_obs, n_times and workspace (checked; the
  * contents of d_f0, d_yo and the workspace must not change in between, which
@@ -349,9 +354,11 @@ lbmletkf_status lbmletkf_misfit_backward(lbmletkf_ctx* ctx, const void* d_f0, do
  *   - the forecast of all problems is one launch per step over the
  *     concatenated (problem, node tile) list, or one launch per pair of steps
  *     over the concatenated (problem, tile, member group) blocks;
- *   - H and the observation statistics run per problem;
+ *   - H and the observation statistics take one launch for up to 32 problems,
+ *     the Gram matrices another;
  *   - the analyses are grouped across problems by eigenproblem size (one
- *     eigen + one apply launch, or one ensemble-route launch, per size),
+ *     solver launch and one update launch per class of 16 members, or one
+ *     ensemble-route launch, per size and solver),
  *     spread over the launch stream and three batch-owned side streams;
  *   - with use_graph, the whole cycle is captured once as a hipGraph and
  *     replayed by every lbmletkf_batch_run_cycle.
@@ -377,8 +384,8 @@ typedef struct {
                                    with a block per (problem, node tile) item; 1: persistent
                                    launches (16 wavefronts per CU) whose blocks take the items
                                    from per-XCD queues in the batch workspace, four at a time;
-                                   the same bits (measured ~4x slower on the twelve-problem
-                                   batch: the loop costs the eigen kernels occupancy) */
+                                   the same bits (measured 1.5 to 1.9 times slower on batches
+                                   of four and twelve problems: the loop costs registers) */
 } lbmletkf_batch_config;
 
 lbmletkf_status lbmletkf_batch_workspace_bytes(lbmletkf_ctx* const* ctxs, int32_t n, size_t* bytes);

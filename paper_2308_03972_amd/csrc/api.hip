@@ -240,9 +240,12 @@ int local_counts(const lbmletkf_lbm_params* p, const lbmletkf_obs_params* o,
 int even_up(int n) { return (n + 1) & ~1; }
 
 // Analysis cost per node in nanoseconds at each instantiated eigenproblem
-// size, measured on MI355X (192 x 192 grid, no localization so that every node
-// has the same size, FP64 storage; M barely matters on the observation route).
-// Only the ratios between entries are used.
+// size with the iterative (Jacobi) solvers, measured on MI355X (192 x 192 grid, no
+// localization so that every node has the same size, FP64 storage; M barely matters on the
+// observation route).  Only the ratios between entries are used: for AUTO's choice of route,
+// which stays what it was when these solvers were the only ones (the route decides what a
+// workspace holds), and for the order of a batch's groups.  The direct solvers' times
+// are in letkf_direct.hip.
 double obs_node_cost(int n) {
     switch (n) {
         case 8: return 6;     case 10: return 8;    case 12: return 11;   case 14: return 16;
@@ -712,8 +715,8 @@ ObsTask obs_task(const Ctx* c, const void* d_f, const double* d_yo) {
             c->K(),   c->obs.n_points, c->obs.nvar, c->dims.nx, c->dims.ny, c->dims.members};
 }
 
-// The analysis of letkf_analyze (d_yf = NULL: of d_f's own observations); with diag_node, the analysis kernels also
-// write every node's diagnostics record of the forecast and of the analysis.
+// The analysis of letkf_analyze (d_yf = NULL: of d_f's own observations); with diag_node, the
+// analysis kernels also write every node's diagnostics record of the forecast and of the analysis.
 lbmletkf_status analyze_impl(Ctx* c, void* d_f, const double* d_yf, const double* d_yo,
                              const double* d_truth_uv, double* diag_node, hipStream_t s) {
     if (!d_yf) {

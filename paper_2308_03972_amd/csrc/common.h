@@ -268,7 +268,7 @@ hipError_t launch_diag_nodes_final(const double* diag_node, int plane, double* p
 // Ensemble route (M x M eigenproblem of size n >= M), every node.
 hipError_t launch_analysis_ens(const AnalysisParams& p, int n, hipStream_t s);
 int ens_size_for(int n);              // instantiated size >= n, or 0
-int ens_lds_bytes(int n, int nz);
+int ens_lds_bytes(int n, int nz);     // likewise, ensemble route
 int ens_segments(int n, bool direct); // nodes per wavefront of the ensemble route
 // Batched ensemble route: wavefront w handles waves[w] = (problem, first node of
 // its ens_segments(n, direct) consecutive nodes of that problem); nz_max
@@ -282,7 +282,7 @@ hipError_t launch_analysis_ens_batch(const AnalysisParams* d_params, const int2*
 hipError_t launch_analysis_obs(const AnalysisParams& p, const int* nodes, int count, int n,
                                double* gbuf, hipStream_t s);
 int obs_size_for(int n);              // instantiated size >= n, or 0
-int obs_lds_bytes(int n);             // the larger of the two kernels' LDS
+int obs_lds_bytes(int n);             // LDS of the iterative solver (what planning admits)
 size_t obs_gbuf_doubles(int n, int count);
 int obs_segments(int n, bool direct); // nodes per block of the eigen kernel
 // The analysis solves its small symmetric problems without iterating unless the caller

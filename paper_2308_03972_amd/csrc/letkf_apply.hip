@@ -282,6 +282,8 @@ __device__ __forceinline__ void apply_rows(const AnalysisParams& p, const int* n
     }
 }
 
+// Wavefronts per SIMD (four slots of observations with three or four of members keep 20 and 60
+// registers in scratch memory).
 template <int NS>
 constexpr int apply_waves() { return 2; }
 

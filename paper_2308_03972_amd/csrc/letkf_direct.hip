@@ -235,7 +235,10 @@ __device__ __forceinline__ void direct_node(const AnalysisParams p, const int* n
 template <int N>
 constexpr int direct_segs() { return kRows16<N> ? 4 : (kPairs<N> ? 2 : 1); }
 
-// Wavefronts per SIMD the registers allow without spilling.
+// Wavefronts per SIMD.  At these N = 20 and 30 and 32 members keep two to four registers in
+// scratch memory, the queue forms of 14 to 48 up to 73, and N = 56 and 64 about 180 (their queue
+// forms 215 and 231): those hold NS x 16 matrix entries of two registers each beside
+// the pole sums.  One wavefront per SIMD, with twice the registers, is not measured.
 template <int N>
 constexpr int direct_waves() { return N <= 16 ? 4 : (N <= 20 ? 3 : 2); }
 
