@@ -1292,9 +1292,9 @@ struct BatchLayout {
     size_t params, tasks, yo, queue, groups, total, group_bytes;
 };
 
-// Work-queue counters of the batched analysis, kGroupCounters per group; 104 groups fit, more
+// Work-queue counters of the batched analysis, kGroupCounters per group; 52 groups fit, more
 // than there are of (route, instantiated size, solver): (17 + 6) x 2.
-constexpr int kQueueInts = 16 * 4 * 65;
+constexpr int kQueueInts = 52 * kGroupCounters;
 
 BatchLayout batch_layout(const std::vector<Ctx*>& ctx) {
     BatchLayout L{};
